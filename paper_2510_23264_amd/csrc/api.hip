@@ -132,7 +132,7 @@ size_t layout(pahq_model* M, char* base) {
   M->out_codes = mlp ? b.take<uint8_t>(L * d * Kmo) : nullptr; M->out_scale = mlp ? b.take<float>(L) : nullptr;
   M->u_codes = b.take<uint8_t>(V * Kdo); M->u_scale = b.take<float>(1);
   M->amax_tmp = b.take<unsigned>((L * H + 4 + 3) / 4 * 4); M->flag_tmp = b.take<int>(4);
-  M->tok_clean = b.take<int>(T); M->tok_corrupt = b.take<int>(T); M->send_dev = b.take<int>(M->ncap);
+  M->tok_clean = b.take<int>(T); M->tok_corrupt = b.take<int>(T); M->row_of = b.take<int>(T); M->row_pos = b.take<int>(T); M->send_dev = b.take<int>(M->ncap);
   M->clean = b.take<float>(Ns * tile); M->corrupt = b.take<float>(Ns * tile); M->delta = b.take<float>((Ns + 1) * tile);   // tile Ns stays zero
   M->rc = b.take<float>((2 * L + 1) * tile); M->rx = b.take<float>((2 * L + 1) * tile);
   M->logits_clean = b.take<float>(B * Vp); M->logits_corrupt = b.take<float>(B * Vp); M->logz_clean = b.take<double>(B);
@@ -560,10 +560,24 @@ int pahq_clean_cache(pahq_model* M, const int32_t* clean_tok, const int32_t* cor
   if (!M || !clean_tok || !corrupt_tok) return PAHQ_EINVAL;
   for (int i = 0; i < M->T; i++)
     if (clean_tok[i] < 0 || clean_tok[i] >= M->V || corrupt_tok[i] < 0 || corrupt_tok[i] >= M->V) return PAHQ_EINVAL;
-  HIPCHK(hipMemcpyAsync(M->tok_clean, clean_tok, M->T * sizeof(int), hipMemcpyHostToDevice, M->stream));
-  HIPCHK(hipMemcpyAsync(M->tok_corrupt, corrupt_tok, M->T * sizeof(int), hipMemcpyHostToDevice, M->stream));
-  HIPCHK(launch_embed(M->tok_clean, M->W_E, M->W_pos, M->clean, M->T, M->S, M->d, M->stream));
-  HIPCHK(launch_embed(M->tok_corrupt, M->W_E, M->W_pos, M->corrupt, M->T, M->S, M->d, M->stream));
+  // The order of a tile's rows for this prompt pair ("Rows of a pass" in engine.hip): by position, then by sequence, so
+  // that the rows at the last position are the last B.
+  const int T = M->T, B = M->B, S = M->S;
+  std::vector<int> table(4 * (size_t)T);                // row_of | row_pos | clean tokens | corrupt tokens
+  int *row_of = table.data(), *row_pos = row_of + T, *tc = row_pos + T, *tx = tc + T;
+  for (int s = 0, row = 0; s < S; s++)
+    for (int b = 0; b < B; b++, row++) {
+      const int t = b * S + s;
+      row_of[t] = row; row_pos[row] = s; tc[row] = clean_tok[t]; tx[row] = corrupt_tok[t];
+    }
+  M->has_cache = false;                                 // what is cached no longer matches the order of the rows
+  M->row_of_host.assign(row_of, row_of + T);
+  HIPCHK(hipMemcpyAsync(M->row_of, row_of, T * sizeof(int), hipMemcpyHostToDevice, M->stream));
+  HIPCHK(hipMemcpyAsync(M->row_pos, row_pos, T * sizeof(int), hipMemcpyHostToDevice, M->stream));
+  HIPCHK(hipMemcpyAsync(M->tok_clean, tc, T * sizeof(int), hipMemcpyHostToDevice, M->stream));
+  HIPCHK(hipMemcpyAsync(M->tok_corrupt, tx, T * sizeof(int), hipMemcpyHostToDevice, M->stream));
+  HIPCHK(launch_embed(M->tok_clean, M->row_pos, M->W_E, M->W_pos, M->clean, T, M->d, M->stream));
+  HIPCHK(launch_embed(M->tok_corrupt, M->row_pos, M->W_E, M->W_pos, M->corrupt, T, M->d, M->stream));
   PassArgs a; a.p0 = 0; a.n = 1; a.pl = a.ph = -1; a.v = -1; a.patch_mode = 0;
   a.kind = BASE_CLEAN; PCHK(run_pass(M, a, nullptr));
   a.kind = BASE_CORRUPT; PCHK(run_pass(M, a, nullptr));
@@ -1036,7 +1050,7 @@ int pahq_round_rows_bf16(pahq_model* M, int32_t site, const float* x, int32_t ro
       AttnSrc src; memset(&src, 0, sizeof(src));
       src.q = src.k = src.v = M->logits; src.q_ld = src.k_ld = src.v_ld = cols;
       src.n_heads = 1; src.h0 = 0; src.head_cols = 0; src.qbits = 16;
-      HIPCHK(launch_attention(src, M->xcodes, 0, M->xscale, 0, nullptr, 0, 0ull, 0ull, 1, (int)nr, 1, 1, cols, 2 * cols, 0, nullptr, M->stream));
+      HIPCHK(launch_attention(src, M->xcodes, M->xscale, nullptr, 0ull, 0ull, 1, (int)nr, 1, 1, cols, 2 * cols, 0, nullptr, M->stream));
     }
     HIPCHK(hipMemcpyAsync(out + r0 * cols, M->xcodes, nr * cols * 2, hipMemcpyDeviceToHost, M->stream));
     HIPCHK(hipStreamSynchronize(M->stream));
@@ -1068,7 +1082,7 @@ int pahq_quantize_rows_site(pahq_model* M, int32_t site, const float* x, int32_t
       AttnSrc src; memset(&src, 0, sizeof(src));
       src.q = src.k = src.v = M->logits; src.q_ld = src.k_ld = src.v_ld = cols;
       src.n_heads = 1; src.h0 = 0; src.head_cols = 0; src.qbits = M->qbits;
-      HIPCHK(launch_attention(src, M->xcodes, 0, M->xscale, 0, nullptr, 0, 0ull, 0ull, 1, (int)nr, 1, 1, cols, (int)ldc, 0, nullptr, M->stream));
+      HIPCHK(launch_attention(src, M->xcodes, M->xscale, nullptr, 0ull, 0ull, 1, (int)nr, 1, 1, cols, (int)ldc, 0, nullptr, M->stream));
     }
     HIPCHK(hipMemcpy2DAsync(codes + r0 * cols, (size_t)cols, M->xcodes, ldc, (size_t)cols, nr, hipMemcpyDeviceToHost, M->stream));
     HIPCHK(hipMemcpyAsync(scales + r0, M->xscale, nr * sizeof(float), hipMemcpyDeviceToHost, M->stream));
@@ -1130,8 +1144,11 @@ int pahq_get_sender_output(pahq_model* M, int32_t which, int32_t sender, float* 
   if (!M || !out || (which != 0 && which != 1) || sender < 0 || sender >= M->g.Ns) return PAHQ_EINVAL;
   if (!M->has_cache) return PAHQ_ESTATE;
   const float* src = (which == 0 ? M->clean : M->corrupt) + (long long)sender * M->tile;
-  HIPCHK(hipMemcpyAsync(out, src, (size_t)M->tile * sizeof(float), hipMemcpyDeviceToHost, M->stream));
+  std::vector<float> rows((size_t)M->tile);
+  HIPCHK(hipMemcpyAsync(rows.data(), src, (size_t)M->tile * sizeof(float), hipMemcpyDeviceToHost, M->stream));
   HIPCHK(hipStreamSynchronize(M->stream));
+  for (int t = 0; t < M->T; t++)                        // from the order of the tile's rows to [sequence][position]
+    memcpy(out + (size_t)t * M->d, rows.data() + (size_t)M->row_of_host[t] * M->d, M->d * sizeof(float));
   return PAHQ_OK;
 }
 

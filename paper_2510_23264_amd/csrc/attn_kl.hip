@@ -24,12 +24,13 @@ typedef float v4f_a __attribute__((ext_vector_type(4)));
 // q, k and v each come with their own base pointer, instance stride and row
 // stride (AttnSrc), so one head can take a per-candidate query, key or value
 // while the other two are shared by all instances.
+// Rows are looked up (AttnSrc.row_of): a sequence's positions need not be neighbours in memory, and the rows below rp0
+// are instance 0's whichever instance the wave works for, so their keys and values come from the caches after the first
+// wave.  With last_only only the last query tile is computed and only its last row leaves.
 template <int ST, int DH, bool ROPE, bool STG>
-__global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zcodes,
-                                                         long long zc_is, float* zscale, long long zs_is, float* zf32,
-                                                         long long zf_is, unsigned long long f32_mask, unsigned long long dead_mask,
-                                                         int n_pairs, int B, int S, int H,
-                                                         int ldz, int rope, const float2* rope_tab) {
+__global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zcodes, float* zscale, float* zf32,
+                                                         unsigned long long f32_mask, unsigned long long dead_mask,
+                                                         int n_pairs, int B, int S, int H, int ldz, const float2* rope_tab) {
   constexpr int CH = DH / 4;        // columns of q / k per lane
   constexpr int NT = DH / 16;       // output column tiles
   const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -39,9 +40,20 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
   if ((dead_mask >> h) & 1ull) return;                                 // this head is not computed (a wave owns a pair: no barrier follows)
   const int inst = sb / B, b = sb % B;
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-  const float* qb = src.q + inst * src.q_is + (long long)b * S * src.q_ld + hl * src.head_cols;
-  const float* kb = src.k + inst * src.k_is + (long long)b * S * src.k_ld + hl * src.head_cols;
-  const float* vb = src.v + inst * src.v_is + (long long)b * S * src.v_ld + hl * src.head_cols;
+  const float* const q0 = src.q + hl * src.head_cols;
+  const float* const k0 = src.k + hl * src.head_cols;
+  const float* const v0 = src.v + hl * src.head_cols;
+  // tile row of position 16 a + i (past the end: the last position's), and a row's address in a matrix
+  int rw[ST];
+#pragma unroll
+  for (int a = 0; a < ST; a++) {
+    const int pos = min(16 * a + i, S - 1);
+    rw[a] = src.row_of ? src.row_of[b * S + pos] : b * S + pos;
+  }
+  auto at = [&](const float* base, long long is, int ld, int row) {
+    return base + (row < src.rp0 ? 0 : inst) * is + (long long)row * ld;
+  };
+  const int a0 = src.last_only ? ST - 1 : 0;                           // first query tile that is needed
 
   float q[ST][CH], k[ST][CH];
   // STG (one 16-position tile, d_head 64): the three 16 x 64 blocks go from global memory straight into this
@@ -52,14 +64,15 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
   __shared__ __attribute__((aligned(1024))) float stage[STG ? 4 * 2 * 1024 : 4];
   float* const sq = stage + (STG ? (threadIdx.x >> 6) * 2048 : 0);
   if (STG) {
-    const float* mats[2] = {qb, kb};
+    const float* mats[2] = {q0, k0};
+    const long long iss_[2] = {src.q_is, src.k_is};
     const int lds_[2] = {src.q_ld, src.k_ld};
 #pragma unroll
     for (int mtx = 0; mtx < 2; mtx++)
 #pragma unroll
       for (int t = 0; t < 4; t++) {
         const int r = 4 * t + (lane >> 4);
-        const float* gp = mats[mtx] + (long long)min(r, S - 1) * lds_[mtx] + (((lane & 15) ^ r) * 4);
+        const float* gp = at(mats[mtx], iss_[mtx], lds_[mtx], __shfl(rw[0], r, 64)) + (((lane & 15) ^ r) * 4);
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
                                          (__attribute__((address_space(3))) void*)(sq + mtx * 1024 + t * 256), 16, 0, 2);
       }
@@ -78,7 +91,7 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
 #pragma unroll
     for (int t = 0; t < 4; t++) {             // v into q's place; waited for after the softmax
       const int r = 4 * t + (lane >> 4);
-      const float* gp = vb + (long long)min(r, S - 1) * src.v_ld + (((lane & 15) ^ r) * 4);
+      const float* gp = at(v0, src.v_is, src.v_ld, __shfl(rw[0], r, 64)) + (((lane & 15) ^ r) * 4);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
                                        (__attribute__((address_space(3))) void*)(sq + t * 256), 16, 0, 2);
     }
@@ -86,12 +99,12 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
 #pragma unroll
   for (int a = 0; a < ST; a++) {
     int pos = 16 * a + i;
-    const float* qrow = qb + (long long)pos * src.q_ld + CH * g;
-    const float* krow = kb + (long long)pos * src.k_ld + CH * g;
+    const float* qrow = at(q0, src.q_is, src.q_ld, rw[a]) + CH * g;
+    const float* krow = at(k0, src.k_is, src.k_ld, rw[a]) + CH * g;
 #pragma unroll
     for (int c = 0; c < CH; c += 4) {
       float4 vq = make_float4(0, 0, 0, 0), vk = vq;
-      if (pos < S) { vq = *(const float4*)(qrow + c); vk = *(const float4*)(krow + c); }
+      if (pos < S) { if (a >= a0) vq = *(const float4*)(qrow + c); vk = *(const float4*)(krow + c); }
       q[a][c] = vq.x; q[a][c + 1] = vq.y; q[a][c + 2] = vq.z; q[a][c + 3] = vq.w;
       k[a][c] = vk.x; k[a][c + 1] = vk.y; k[a][c + 2] = vk.z; k[a][c + 3] = vk.w;
     }
@@ -123,6 +136,7 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
   for (int a = 0; a < ST; a++)
 #pragma unroll
     for (int bk = 0; bk <= a; bk++) {
+      if (a < a0) continue;
       v4f_a acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < CH; c++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(k[bk][c], q[a][c], acc, 0, 0, 0);
@@ -130,6 +144,7 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
     }
 #pragma unroll
   for (int a = 0; a < ST; a++) {
+    if (a < a0) continue;
     const int qpos = 16 * a + i;
     float mx = -3.0e38f;
 #pragma unroll
@@ -176,7 +191,7 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
         for (int t = 0; t < NT; t++)
           vv[bk][r][t] = (kpos < S) ? sq[kpos * 64 + (((4 * t + (i >> 2)) ^ kpos) * 4) + (i & 3)] : 0.f;
       } else {
-        const float* row = vb + (long long)kpos * src.v_ld + i;
+        const float* row = at(v0, src.v_is, src.v_ld, __shfl(rw[bk], 4 * g + r, 64)) + i;
 #pragma unroll
         for (int t = 0; t < NT; t++) vv[bk][r][t] = (kpos < S) ? row[16 * t] : 0.f;
       }
@@ -185,8 +200,13 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
   const bool f32 = (f32_mask >> h) & 1ull;
   // place of this head among the fp32 heads, and their number
   const int f32_slot = __popcll(f32_mask & ((1ull << h) - 1ull)), f32_n = __popcll(f32_mask);
+  const int inst_o = src.inst0 + inst;
+  // output row of tile row r, and whether this wave writes it
+  auto out_row = [&](int r) { return (long long)r + (r < src.rp0 ? 0ll : (long long)inst_o * (B * S - src.rp0)); };
+  auto writes = [&](int pos, int r) { return pos < S && (r >= src.rp0 || inst_o == 0) && (!src.last_only || pos == S - 1); };
 #pragma unroll
   for (int a = 0; a < ST; a++) {
+    if (a < a0) continue;
     v4f_a z[NT];
 #pragma unroll
     for (int t = 0; t < NT; t++) {
@@ -201,10 +221,12 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
 #pragma unroll
     for (int rr = 0; rr < 4; rr++) {
       int pos = 16 * a + 4 * g + rr;
-      long long tok = (long long)b * S + pos;
+      const int trow = __shfl(rw[a], 4 * g + rr, 64);
+      const long long tok = out_row(trow);
+      const bool on = writes(pos, trow);
       if (f32) {
-        if (pos < S) {
-          float* o = zf32 + inst * zf_is + (tok * f32_n + f32_slot) * DH + i;
+        if (on) {
+          float* o = zf32 + (tok * f32_n + f32_slot) * DH + i;
 #pragma unroll
           for (int t = 0; t < NT; t++) o[16 * t] = z[t][rr];
         }
@@ -218,11 +240,11 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
         float inv = 1.0f / scale;
         if (!STG && src.qbits == 16) {
           // bfloat16 patterns, two bytes per value, no scale
-          if (pos < S) {
-            uint8_t* o = zcodes + inst * zc_is + (tok * H + h) * ldz + 2 * i;
+          if (on) {
+            uint8_t* o = zcodes + (tok * H + h) * ldz + 2 * i;
 #pragma unroll
             for (int t = 0; t < NT; t++) *(uint16_t*)(o + 32 * t) = (uint16_t)bf16_rne(z[t][rr]);
-            if (i == 0) zscale[inst * zs_is + tok * H + h] = 1.0f;
+            if (i == 0) zscale[tok * H + h] = 1.0f;
           }
         } else if (STG) {
           // codes of the 16 x 64 block are collected in this wave's LDS (the k block is no longer needed) and
@@ -230,12 +252,12 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
           uint8_t* zb = (uint8_t*)(sq + 1024) + pos * 64 + i;
 #pragma unroll
           for (int t = 0; t < NT; t++) zb[16 * t] = (uint8_t)q_encode(z[t][rr] * inv, src.qbits);
-          if (pos < S && i == 0) zscale[inst * zs_is + tok * H + h] = scale;
-        } else if (pos < S) {
-          uint8_t* o = zcodes + inst * zc_is + (tok * H + h) * ldz + i;
+          if (on && i == 0) zscale[tok * H + h] = scale;
+        } else if (on) {
+          uint8_t* o = zcodes + (tok * H + h) * ldz + i;
 #pragma unroll
           for (int t = 0; t < NT; t++) o[16 * t] = (uint8_t)q_encode(z[t][rr] * inv, src.qbits);
-          if (i == 0) zscale[inst * zs_is + tok * H + h] = scale;
+          if (i == 0) zscale[tok * H + h] = scale;
         }
       }
     }
@@ -244,9 +266,10 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
     __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): the byte writes above
     __builtin_amdgcn_wave_barrier();
     const int pos = lane >> 2;                // token of the block, 16-byte piece lane & 3 of its 64 codes
-    if (pos < S) {
+    const int trow = __shfl(rw[0], pos, 64);
+    if (writes(pos, trow)) {
       const uint4 w = *(const uint4*)((const uint8_t*)(sq + 1024) + lane * 16);
-      *(uint4*)(zcodes + inst * zc_is + (((long long)b * S + pos) * H + h) * ldz + (lane & 3) * 16) = w;
+      *(uint4*)(zcodes + (out_row(trow) * H + h) * ldz + (lane & 3) * 16) = w;
     }
   }
 }
@@ -259,26 +282,33 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
 // tiles then the lane's four keys then the four lanes, P V over key tiles and keys ascending -- so that for a
 // sequence both kernels accept they give the same bits.
 template <int STM, int DH, bool ROPE>
-__global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* zcodes, long long zc_is, float* zscale,
-                                                          long long zs_is, float* zf32, long long zf_is,
+__global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* zcodes, float* zscale, float* zf32,
                                                           unsigned long long f32_mask, unsigned long long dead_mask,
                                                           int n_pairs, int B, int S, int H, int ldz, const float2* rope_tab) {
   constexpr int CH = DH / 4, NT = DH / 16;
-  const int ST = (S + 15) >> 4;
+  const int ST = (S + 15) >> 4, QT = src.last_only ? 1 : ST;           // key tiles of a sequence, query tiles of the launch
   const int job = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (job >= n_pairs * ST) return;
-  const int a = job % ST, pair = job / ST;                             // query tile, (instance, sequence, head)
+  if (job >= n_pairs * QT) return;
+  const int a = ST - QT + job % QT, pair = job / QT;                   // query tile, (instance, sequence, head)
   const int hl = pair % src.n_heads, sb = pair / src.n_heads;
   const int h = src.h0 + hl;
   if ((dead_mask >> h) & 1ull) return;
   const int inst = sb / B, b = sb % B;
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-  const float* qb = src.q + inst * src.q_is + (long long)b * S * src.q_ld + hl * src.head_cols;
-  const float* kb = src.k + inst * src.k_is + (long long)b * S * src.k_ld + hl * src.head_cols;
-  const float* vb = src.v + inst * src.v_is + (long long)b * S * src.v_ld + hl * src.head_cols;
+  const float* const q0 = src.q + hl * src.head_cols;
+  const float* const k0 = src.k + hl * src.head_cols;
+  const float* const v0 = src.v + hl * src.head_cols;
+  auto row_at = [&](int pos) { pos = min(pos, S - 1); return src.row_of ? src.row_of[b * S + pos] : b * S + pos; };
+  auto at = [&](const float* base, long long is, int ld, int row) {
+    return base + (row < src.rp0 ? 0 : inst) * is + (long long)row * ld;
+  };
+  const int inst_o = src.inst0 + inst;
+  const int qrow = row_at(16 * a + i);                                 // tile row of query i of the tile
+  auto writes = [&](int pos, int r) { return pos < S && (r >= src.rp0 || inst_o == 0) && (!src.last_only || pos == S - 1); };
+  if (!__ballot(writes(16 * a + i, qrow))) return;                     // every row of the tile is instance 0's
   // row `pos` of a matrix: this lane's CH consecutive columns, rotated when the model has rotary positions
-  auto load_rows = [&](float (&x)[CH], const float* base, int ld, int pos) {
-    const float* row = base + (long long)pos * ld + CH * g;
+  auto load_rows = [&](float (&x)[CH], const float* base, long long is, int ld, int pos, int trow) {
+    const float* row = at(base, is, ld, trow) + CH * g;
 #pragma unroll
     for (int c = 0; c < CH; c += 4) {
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -297,14 +327,14 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
     }
   };
   float q[CH];
-  load_rows(q, qb, src.q_ld, 16 * a + i);
+  load_rows(q, q0, src.q_is, src.q_ld, 16 * a + i, qrow);
   v4f_a sc[STM];
   const float scl = 1.0f / sqrtf((float)DH);
 #pragma unroll
   for (int bk = 0; bk < STM; bk++) {
     if (bk > a) continue;                                              // (wave-uniform)
     float kk[CH];
-    load_rows(kk, kb, src.k_ld, 16 * bk + i);
+    load_rows(kk, k0, src.k_is, src.k_ld, 16 * bk + i, row_at(16 * bk + i));
     v4f_a acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < CH; c++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[c], q[c], acc, 0, 0, 0);
@@ -357,7 +387,7 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       const int kpos = 16 * bk + 4 * g + r;
-      const float* row = vb + (long long)kpos * src.v_ld + i;
+      const float* row = at(v0, src.v_is, src.v_ld, row_at(kpos)) + i;
 #pragma unroll
       for (int t = 0; t < NT; t++) {
         const float vv = (kpos < S) ? row[16 * t] : 0.f;
@@ -371,10 +401,12 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
 #pragma unroll
   for (int rr = 0; rr < 4; rr++) {
     const int pos = 16 * a + 4 * g + rr;
-    const long long tok = (long long)b * S + pos;
+    const int trow = __shfl(qrow, 4 * g + rr, 64);
+    const long long tok = (long long)trow + (trow < src.rp0 ? 0ll : (long long)inst_o * (B * S - src.rp0));
+    const bool on = writes(pos, trow);
     if (f32) {
-      if (pos < S) {
-        float* o = zf32 + inst * zf_is + (tok * f32_n + f32_slot) * DH + i;
+      if (on) {
+        float* o = zf32 + (tok * f32_n + f32_slot) * DH + i;
 #pragma unroll
         for (int t = 0; t < NT; t++) o[16 * t] = z[t][rr];
       }
@@ -386,17 +418,17 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
       for (int o = 8; o > 0; o >>= 1) am = fmaxf(am, __shfl_xor(am, o, 64));
       const float scale = (am == 0.f || src.qbits == 16) ? 1.0f : am / q_top(src.qbits);
       const float inv = 1.0f / scale;
-      if (pos < S) {
+      if (on) {
         if (src.qbits == 16) {
-          uint8_t* o = zcodes + inst * zc_is + (tok * H + h) * ldz + 2 * i;
+          uint8_t* o = zcodes + (tok * H + h) * ldz + 2 * i;
 #pragma unroll
           for (int t = 0; t < NT; t++) *(uint16_t*)(o + 32 * t) = (uint16_t)bf16_rne(z[t][rr]);
-          if (i == 0) zscale[inst * zs_is + tok * H + h] = 1.0f;
+          if (i == 0) zscale[tok * H + h] = 1.0f;
         } else {
-          uint8_t* o = zcodes + inst * zc_is + (tok * H + h) * ldz + i;
+          uint8_t* o = zcodes + (tok * H + h) * ldz + i;
 #pragma unroll
           for (int t = 0; t < NT; t++) o[16 * t] = (uint8_t)q_encode(z[t][rr] * inv, src.qbits);
-          if (i == 0) zscale[inst * zs_is + tok * H + h] = scale;
+          if (i == 0) zscale[tok * H + h] = scale;
         }
       }
     }
@@ -419,21 +451,21 @@ hipError_t launch_rope_table(float* tab, int n_pos, int dh, float theta, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, long long zc_is, float* zscale,
-                            long long zs_is, float* zf32, long long zf_is, unsigned long long f32_mask, unsigned long long dead_mask, int n_inst, int B, int S,
-                            int H, int dh, int ldz, int rope, const float* rope_tab, hipStream_t s) {
+hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, float* zscale, float* zf32, unsigned long long f32_mask,
+                            unsigned long long dead_mask, int n_inst, int B, int S, int H, int dh, int ldz, int rope,
+                            const float* rope_tab, hipStream_t s) {
   if (n_inst == 0) return hipSuccess;
   if (S > 128) return hipErrorInvalidValue;
   int n_pairs = n_inst * B * src.n_heads;
   if (src.form == 1 || S > 64 || (S > 32 && dh == 128)) {
     // one wave per tile of 16 queries, up to eight key tiles
-    const long long jobs = (long long)n_pairs * ((S + 15) / 16);
+    const long long jobs = (long long)n_pairs * (src.last_only ? 1 : (S + 15) / 16);
     if (jobs > 0x7fffffffLL) return hipErrorInvalidValue;
     dim3 qgrid((unsigned)((jobs + 3) / 4));
-#define ATQ(DH_) do { if (rope) hipLaunchKernelGGL((attention_qtile_k<8, DH_, true>), qgrid, dim3(256), 0, s, src, zcodes, zc_is, zscale, zs_is, zf32, \
-                                                  zf_is, f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab); \
-                      else hipLaunchKernelGGL((attention_qtile_k<8, DH_, false>), qgrid, dim3(256), 0, s, src, zcodes, zc_is, zscale, zs_is, zf32, \
-                                              zf_is, f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab); } while (0)
+#define ATQ(DH_) do { if (rope) hipLaunchKernelGGL((attention_qtile_k<8, DH_, true>), qgrid, dim3(256), 0, s, src, zcodes, zscale, zf32, \
+                                                  f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab); \
+                      else hipLaunchKernelGGL((attention_qtile_k<8, DH_, false>), qgrid, dim3(256), 0, s, src, zcodes, zscale, zf32, \
+                                              f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab); } while (0)
     if (dh == 16) ATQ(16); else if (dh == 32) ATQ(32); else if (dh == 64) ATQ(64); else if (dh == 128) ATQ(128);
     else return hipErrorInvalidValue;
 #undef ATQ
@@ -441,8 +473,8 @@ hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, long long zc_is
   }
   dim3 grid((n_pairs + 3) / 4);
   // the staged form (one tile, d_head 64, no rotation) collects one-byte codes in LDS: bfloat16 outputs take the plain form
-#define ATT0(ST_, DH_, R_, G_) hipLaunchKernelGGL((attention_mfma_k<ST_, DH_, R_, G_>), grid, dim3(256), 0, s, src, zcodes, \
-                                              zc_is, zscale, zs_is, zf32, zf_is, f32_mask, dead_mask, n_pairs, B, S, H, ldz, rope, (const float2*)rope_tab)
+#define ATT0(ST_, DH_, R_, G_) hipLaunchKernelGGL((attention_mfma_k<ST_, DH_, R_, G_>), grid, dim3(256), 0, s, src, zcodes, zscale, zf32, \
+                                              f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab)
 #define ATT1(ST_, DH_, R_) do { if ((ST_ == 1 && DH_ == 64 && !R_) && src.qbits != 16) ATT0(ST_, DH_, R_, (ST_ == 1 && DH_ == 64 && !R_)); \
                                 else ATT0(ST_, DH_, R_, false); } while (0)
 #define ATT(ST_, DH_) do { if (rope) ATT1(ST_, DH_, true); else ATT1(ST_, DH_, false); } while (0)

@@ -73,7 +73,9 @@ struct pahq_model {
   uint8_t *qkv_codes, *o_codes, *in_codes, *gate_codes, *out_codes, *u_codes;
   float *qkv_scale, *o_scale, *in_scale, *gate_scale, *out_scale, *u_scale;
   unsigned* amax_tmp; int* flag_tmp;
-  int *tok_clean, *tok_corrupt, *send_dev;
+  int *tok_clean, *tok_corrupt, *send_dev;       // tokens in the order of a tile's rows
+  int *row_of, *row_pos;                  // row of (sequence, position) in a tile [B * S]; position of a row [T]
+  std::vector<int> row_of_host;           // host copy of row_of
   float *clean, *corrupt, *delta;         // [Ns] tiles each (delta has one more, all zero)
   float *rc, *rx;                         // [2L+1] residual prefixes (entry 0 unused: it is sender 0's tile)
   float *logits_clean, *logits_corrupt;   // [B][V]

@@ -13,6 +13,14 @@
 // and the cheaper form is chosen per receiver.  D_s of senders below the start
 // position comes from the cache (clean - corrupt); for recomputed senders it is
 // written by the kernel that adds the sender's output to the stream.
+//
+// Rows of a pass.  A tile holds the B * S token rows in an order made for the prompt pair (pahq_clean_cache): the rows
+// at the last position come last, in the order of the sequences.  What a pass computes last is read at that position
+// only: the output node takes the B last rows, so in the last layer the queries, the output projection and the MLP are
+// needed there alone, and keys and values everywhere.  Passes that end in a score compute just that (`last` below);
+// the cache passes, whose sender outputs are kept, compute every row.  (Of a layer's matrix products that leaves a
+// sixth and a sixteenth of the rest at 16 positions: candidates into layer 5 of 12 at the GPT-2-small shape 330 -> 302
+// ms, into the last layer of a 7B-class model 82 -> 34 ms.)
 #include "engine.h"
 #include <map>
 #include <string.h>
@@ -95,6 +103,7 @@ struct Builder {
   std::vector<Op> ops;
   bool general, has_pi, f32_rest;
   int nstat;
+  int rp0, rpi;        // rows of a tile that only instance 0 has, and rows every instance has (rp0 + rpi = T)
   // stand-ins of dead blocks the stream has not taken yet: cached corrupted outputs (tiles) and block biases (rows)
   std::vector<const float*> pend_tiles, pend_rows;
   std::vector<std::pair<int, long long>> new_tags;     // (layer, tag) of the dead-head sums this pass makes
@@ -108,7 +117,19 @@ struct Builder {
       else has_pi = a.pl >= 0;
     }
     nstat = M->g.n_static(a.p0);
+    rp0 = 0;
+    rpi = M->T - rp0;
   }
+  // elements between instances of a tensor with ld elements per row, and rows of all instances
+  long long inst_stride(long long ld) const { return rpi * ld; }
+  int rows_of(int n) const { return rp0 + n * rpi; }
+  int rows(bool last) const { return last ? a.n * M->B : rows_of(a.n); }
+  // the last layer of a pass that ends in a score: only its rows at the last position are read (see "Rows of a pass")
+  bool last_rows(int l) const {
+    return l == M->L - 1 && (a.kind == CAND || a.kind == STATE || a.kind == PI_REF || a.kind == PI_REF_LAYER);
+  }
+  // offset of the last position's rows in a tensor with ld elements per row
+  long long last_off(bool last, long long ld) const { return last ? (long long)(M->T - M->B) * ld : 0; }
 
   // heads of layer l whose projections run on the fp32 masters
   unsigned long long mask_of(int l) const {
@@ -150,14 +171,15 @@ struct Builder {
     }
   }
 
-  // Mr rows per instance; the problem covers all a.n instances (rows numbered across instances)
+  // The problem covers the rows of all a.n instances; last: of each, the B rows at the last position (A, ascale and C
+  // then point at the first of those).
   GemmProb prob8(const void* A, long long a_is, int lda, const float* as, long long as_is, int as_stride,
                  const void* W, int ldw, const float* ws, int ws_block, const float* bias, float* C, long long c_is,
-                 int ldc, int act, int Mr, int N, int K, int k_real) {
+                 int ldc, int act, bool last, int N, int K, int k_real) {
     GemmProb p; memset(&p, 0, sizeof(p));
     p.A = A; p.a_is = a_is; p.lda = lda; p.ascale = as; p.as_is = as_is; p.as_stride = as_stride;
     p.W = W; p.ldw = ldw; p.wscale = ws; p.wscale_block = ws_block; p.bias = bias;
-    p.C = C; p.c_is = c_is; p.ldc = ldc; p.act = act; p.rpi = Mr; p.M = Mr * a.n; p.N = N; p.K = K; p.k_real = k_real;
+    p.C = C; p.c_is = c_is; p.ldc = ldc; p.act = act; p.rpi = last ? M->B : rpi; p.rp0 = last ? 0 : rp0; p.M = rows(last); p.N = N; p.K = K; p.k_real = k_real;
     p.ws_shift = -1;
     if (ws_block > 0 && (ws_block & (ws_block - 1)) == 0) { p.ws_shift = 0; while ((1 << p.ws_shift) < ws_block) p.ws_shift++; }
     return p;
@@ -183,7 +205,7 @@ struct Builder {
       f += 2.0 * M_ * N_ * K_;
       by += eb * (M_ * K_ + N_ * K_) + (q.C ? 4.0 * M_ * N_ : 0.0) + (q.kl_ref ? 4.0 * (double)q.rpi * N_ : 0.0) +
             (q.ascale ? 4.0 * M_ : 0.0) + (q.add ? 4.0 * M_ * N_ : 0.0) +
-            (q.aux ? 4.0 * M_ * N_ : 0.0) + (q.aux_sub ? 4.0 * (double)q.rpi * N_ : 0.0);
+            (q.aux ? 4.0 * M_ * N_ : 0.0) + (q.aux_sub ? 4.0 * (double)(q.rp0 + q.rpi) * N_ : 0.0);
     }
     ops.back().flops = f;
     ops.back().bytes = by;
@@ -193,20 +215,19 @@ struct Builder {
     for (int i = g0; i < g0 + n_groups; i++) {
       if (i == skip) continue;
       const GroupDesc& gd = groups[i];
-      double rows = gd.last_only ? M->B : M->T, d = M->d;
+      double nr = rows(gd.last_only != 0), d = M->d;
       double reads = (gd.base ? 1 : 0) + (gd.run ? 1 : 0) + gd.term_count;
-      by += rows * d * 4.0 * reads + (gd.out_f32 ? rows * d * 4.0 : 0) + (gd.out_codes ? rows * (d + 4.0) : 0);
+      by += nr * d * 4.0 * reads + (gd.out_f32 ? nr * d * 4.0 : 0) + (gd.out_codes ? nr * (d + 4.0) : 0);
     }
-    ops.back().bytes = by * a.n;
+    ops.back().bytes = by;
   }
   // the edge-batched patch of group gi: per instance one delta tile (+ the shared current input once)
   void add_patch(int gi, int inst0 = 0, int count = 0, float* xv = nullptr) {
     const int n = count ? count : a.n;        // instances inst0 .. inst0 + n - 1 (the group's outputs start at inst0)
     add_op(OP_PATCH, gi, inst0, n, 0, xv ? xv : M->xv);
     const GroupDesc& gd = groups[gi];
-    double rows = gd.last_only ? M->B : M->T, d = M->d;
-    ops.back().bytes = n * (rows * d * 4.0 * (1.0 + 1.0 / n) + (gd.out_f32 ? rows * d * 4.0 : 0) +
-                            (gd.out_codes ? rows * (d + 4.0) : 0));
+    double tr = gd.last_only ? M->B : M->T, nr = gd.last_only ? n * M->B : rows_of(n), d = M->d;
+    ops.back().bytes = (nr + tr) * d * 4.0 + (gd.out_f32 ? nr * d * 4.0 : 0) + (gd.out_codes ? nr * (d + 4.0) : 0);
   }
   void add_build(int g0, int n_groups, int patch_group) {
     if (n_groups - (patch_group >= 0 ? 1 : 0) > 0) {
@@ -241,7 +262,7 @@ struct Builder {
       case BASE_CLEAN: r.p = M->rc + (long long)canon(M, p_after) * M->tile; r.is = 0; break;
       case BASE_CORRUPT: r.p = M->rx + (long long)canon(M, p_after) * M->tile; r.is = 0; break;
       case PI_CORRUPT: r.p = M->rxpi + (long long)canon(M, p_after) * M->tile; r.is = 0; break;
-      default: r.p = scratch; r.is = M->tile; break;
+      default: r.p = scratch; r.is = inst_stride(M->d); break;
     }
     return r;
   }
@@ -251,8 +272,9 @@ struct Builder {
     gd.offset = (M->cfg.norm == PAHQ_NORM_RMS || !offset) ? M->zeros_d : offset;
   }
 
-  void add_attention(const AttnSrc& src, unsigned long long f32_mask, unsigned long long dead_mask = 0) {
+  void add_attention(const AttnSrc& src, bool last, unsigned long long f32_mask, unsigned long long dead_mask = 0) {
     asrcs.push_back(src);
+    asrcs.back().rp0 = rp0; asrcs.back().last_only = last ? 1 : 0; asrcs.back().row_of = M->row_of;
     add_op(OP_ATTN, (int)asrcs.size() - 1);
     ops.back().u64 = f32_mask;
     ops.back().u64b = dead_mask;
@@ -273,7 +295,7 @@ struct Builder {
   }
   void take_standins(Stream& run) {
     if (pend_tiles.empty() && pend_rows.empty()) return;
-    Stream nx; nx.p = run.p == M->run_a ? M->run_b : M->run_a; nx.is = M->tile;
+    Stream nx; nx.p = run.p == M->run_a ? M->run_b : M->run_a; nx.is = inst_stride(M->d);
     CombineDesc cd; memset(&cd, 0, sizeof(cd));
     cd.run_in = run.p; cd.run_in_is = run.is; cd.run_out = nx.p; cd.run_out_is = nx.is;
     cd.bias = nullptr; cd.src_begin = (int)csrcs.size(); cd.n_src = (int)(pend_tiles.size() + pend_rows.size());
@@ -308,7 +330,8 @@ struct Builder {
   // are per candidate.
   void first_block_split(int l, Stream& run) {
     const GraphDims& g = M->g;
-    const int H = M->H, dh = M->dh, d = M->d, T = M->T;
+    const int H = M->H, dh = M->dh, d = M->d;
+    const bool last = last_rows(l);
     int vk, vl, hv, cv;
     g.receiver_info(a.v, vk, vl, hv, cv);
     // instances [off, off + cnt[c]) patch input c (query, key, value) of the investigated head: one receiver's
@@ -324,65 +347,70 @@ struct Builder {
       // a head with a single input: every instance patches it, and all three projections read the patched rows
       GroupDesc gd; memset(&gd, 0, sizeof(gd));
       norm_params(gd, M->ln1_g + (long long)l * d, M->ln1_b + (long long)l * d);
-      gd.out_f32 = M->xf32; gd.out_f32_is = M->tile;
+      gd.out_f32 = M->xf32; gd.out_f32_is = inst_stride(d);
       int g1 = (int)groups.size();
       groups.push_back(gd);
       add_patch(g1);
-      const long long blk = (long long)a.n * T * dh;              // q, k, v of all instances one after the other
+      const long long blk = (long long)rows(false) * dh;              // q, k, v of all instances one after the other
       int pq = (int)probs.size();
       for (int c = 0; c < 3; c++)
-        probs.push_back(prob8(M->xf32, M->tile, d, nullptr, 0, 0, Wc[c], dh, nullptr, 1, bc[c],
-                              M->qv + c * blk, (long long)T * dh, dh, 0, T, dh, d, d));
-      add_op(OP_GEMM32, pq, 3, T * a.n, dh); work_gemm(pq);
+        probs.push_back(prob8(M->xf32, inst_stride(d), d, nullptr, 0, 0, Wc[c], dh, nullptr, 1, bc[c],
+                              M->qv + c * blk, inst_stride(dh), dh, 0, false, dh, d, d));
+      add_op(OP_GEMM32, pq, 3, rows(false), dh); work_gemm(pq);
       AttnSrc src; memset(&src, 0, sizeof(src));
       src.q = M->qv; src.k = M->qv + blk; src.v = M->qv + 2 * blk;
-      src.q_is = src.k_is = src.v_is = (long long)T * dh;
+      src.q_is = src.k_is = src.v_is = inst_stride(dh);
       src.q_ld = src.k_ld = src.v_ld = dh;
       src.n_heads = 1; src.h0 = hv; src.head_cols = 0;
-      add_attention(src, 1ull << hv);
+      add_attention(src, last, 1ull << hv);
     } else {
     if (multi) { for (int c = 0; c < 3; c++) cnt[c] = a.chan_count[c]; } else cnt[cv] = a.n;
-    // patched rows of every range, then their projections in one launch, then the head's attention per range
-    int gi[3] = {-1, -1, -1};
-    for (int c = 0, off = 0; c < 3; off += cnt[c], c++) {
+    // patched rows of every range, then their projections in one launch, then the head's attention per range.  A
+    // range's rows are numbered like a pass of its own (its first instance has the rp0 rows all share), from row
+    // at[c] of xf32 and qv on.
+    int gi[3] = {-1, -1, -1}, at[3] = {0, 0, 0};
+    for (int c = 0, off = 0, row = 0; c < 3; off += cnt[c], c++) {
       if (!cnt[c]) continue;
+      at[c] = row; row += rows_of(cnt[c]);
       GroupDesc gd; memset(&gd, 0, sizeof(gd));
       norm_params(gd, M->ln1_g + (long long)l * d, M->ln1_b + (long long)l * d);
-      gd.out_f32 = M->xf32 + (long long)off * M->tile; gd.out_f32_is = M->tile;
+      gd.out_f32 = M->xf32 + (long long)at[c] * d; gd.out_f32_is = inst_stride(d);
       gi[c] = (int)groups.size();
       groups.push_back(gd);
       add_patch(gi[c], off, cnt[c], multi ? M->xvc + (long long)c * M->tile : M->xv);
     }
-    int pq0 = (int)probs.size(), np = 0;
-    for (int c = 0, off = 0; c < 3; off += cnt[c], c++) {
+    int pq0 = (int)probs.size(), np = 0, max_rows = 0;
+    for (int c = 0; c < 3; c++) {
       if (!cnt[c]) continue;
-      GemmProb pq = prob8(M->xf32 + (long long)off * M->tile, M->tile, d, nullptr, 0, 0, Wc[c], dh, nullptr, 1,
-                          bc[c], M->qv + (long long)off * T * dh, (long long)T * dh, dh, 0, T, dh, d, d);
-      pq.M = T * cnt[c];
+      GemmProb pq = prob8(M->xf32 + (long long)at[c] * d, inst_stride(d), d, nullptr, 0, 0, Wc[c], dh, nullptr, 1,
+                          bc[c], M->qv + (long long)at[c] * dh, inst_stride(dh), dh, 0, false, dh, d, d);
+      pq.M = rows_of(cnt[c]);
+      max_rows = std::max(max_rows, pq.M);
       probs.push_back(pq); np++;
     }
-    add_op(OP_GEMM32, pq0, np, T * a.n, dh); work_gemm(pq0);
+    add_op(OP_GEMM32, pq0, np, max_rows, dh); work_gemm(pq0);
     for (int c = 0, off = 0; c < 3; off += cnt[c], c++) {
       if (!cnt[c]) continue;
-      const float* own = M->qv + (long long)off * T * dh;
+      const float* own = M->qv + (long long)at[c] * dh;
       AttnSrc src; memset(&src, 0, sizeof(src));
-      src.q = c == 0 ? own : shared0;               src.q_is = c == 0 ? (long long)T * dh : 0; src.q_ld = c == 0 ? dh : ld_sh;
-      src.k = c == 1 ? own : shared0 + H * dh;      src.k_is = c == 1 ? (long long)T * dh : 0; src.k_ld = c == 1 ? dh : ld_sh;
-      src.v = c == 2 ? own : shared0 + 2 * H * dh;  src.v_is = c == 2 ? (long long)T * dh : 0; src.v_ld = c == 2 ? dh : ld_sh;
-      src.n_heads = 1; src.h0 = hv; src.head_cols = 0;
-      add_attention(src, 1ull << hv);
-      ops.back().i1 = off; ops.back().i2 = cnt[c];
+      src.q = c == 0 ? own : shared0;               src.q_is = c == 0 ? inst_stride(dh) : 0; src.q_ld = c == 0 ? dh : ld_sh;
+      src.k = c == 1 ? own : shared0 + H * dh;      src.k_is = c == 1 ? inst_stride(dh) : 0; src.k_ld = c == 1 ? dh : ld_sh;
+      src.v = c == 2 ? own : shared0 + 2 * H * dh;  src.v_is = c == 2 ? inst_stride(dh) : 0; src.v_ld = c == 2 ? dh : ld_sh;
+      src.n_heads = 1; src.h0 = hv; src.head_cols = 0; src.inst0 = off;
+      add_attention(src, last, 1ull << hv);
+      ops.back().i2 = cnt[c];
     }
     }
     Stream nxt = next_run(2 * l + 1, run.p == M->run_a ? M->run_b : M->run_a);
     int s = g.head(l, hv);
     const int pf = (int)probs.size();
-    GemmProb pp = prob8(M->zf32, (long long)T * dh, dh, nullptr, 0, 0, w32_ptr(M, 3, l, hv), d, nullptr, 1, nullptr,
-                        nxt.p, nxt.is, d, 0, T, d, dh, dh);
-    pp.add = M->oth; pp.add_is = 0;
-    if (plan->slot_of[s] >= 0) { pp.aux = slot_ptr(s); pp.aux_is = slot_is(s); pp.aux_sub = corrupt_ref_tile(s); }
+    const long long lo = last_off(last, d);
+    GemmProb pp = prob8(M->zf32 + last_off(last, dh), inst_stride(dh), dh, nullptr, 0, 0, w32_ptr(M, 3, l, hv), d, nullptr, 1, nullptr,
+                        nxt.p + lo, nxt.is, d, 0, last, d, dh, dh);
+    pp.add = M->oth + lo; pp.add_is = 0;
+    if (plan->slot_of[s] >= 0) { pp.aux = slot_ptr(s) + lo; pp.aux_is = slot_is(s); pp.aux_sub = corrupt_ref_tile(s) + lo; }
     probs.push_back(pp);
-    add_op(OP_GEMM32, pf, 1, T * a.n, d); work_gemm(pf);
+    add_op(OP_GEMM32, pf, 1, rows(last), d); work_gemm(pf);
     w32_end(l, 1ull << hv);
     run = nxt;
   }
@@ -397,6 +425,8 @@ struct Builder {
     const int H = M->H, dh = M->dh, d = M->d, T = M->T, Kd = M->Kd, Kh = M->Kh;
     const unsigned long long all_heads = H >= 64 ? ~0ull : ((1ull << H) - 1ull);
     const long long qkv_ld = 3LL * H * dh;
+    const bool last = last_rows(l);
+    const long long lo = last_off(last, d);
     GroupDesc gd; memset(&gd, 0, sizeof(gd));
     fill_input(gd, nullptr, 2 * l, run);
     norm_params(gd, M->ln1_g + (long long)l * d, M->ln1_b + (long long)l * d);
@@ -411,7 +441,7 @@ struct Builder {
     int pb = (int)probs.size();
     GemmProb p8 = prob8(gd.out_codes, gd.out_codes_is, Kd, gd.out_scale, gd.out_scale_is, 1,
                         M->qkv_codes + (long long)l * 3 * H * dh * Kd, Kd, M->qkv_scale + (long long)l * 3 * H, dh,
-                        M->bqkv + (long long)l * 3 * H * dh, M->qkv_sh, (long long)T * qkv_ld, (int)qkv_ld, 0, T, 3 * H * dh, Kd, d);
+                        M->bqkv + (long long)l * 3 * H * dh, M->qkv_sh, (long long)T * qkv_ld, (int)qkv_ld, 0, false, 3 * H * dh, Kd, d);
     p8.M = T; p8.b16 = M->qbits == 16;
     probs.push_back(p8);
     add_op(OP_GEMM8, pb, 1, T, 3 * H * dh); work_gemm(pb);
@@ -420,7 +450,7 @@ struct Builder {
     for (int h = 0; h < H; h++)
       for (int c = 0; c < 3; c++) {
         GemmProb pq = prob8(gd.out_f32, gd.out_f32_is, d, nullptr, 0, 0, w32_ptr(M, c, l, h), dh, nullptr, 1, w32_ptr(M, 4 + c, l, h),
-                            M->qkv + ((long long)c * H + h) * dh, (long long)T * qkv_ld, (int)qkv_ld, 0, T, dh, d, d);
+                            M->qkv + ((long long)c * H + h) * dh, (long long)T * qkv_ld, (int)qkv_ld, 0, false, dh, d, d);
         pq.M = T;
         probs.push_back(pq);
       }
@@ -431,32 +461,33 @@ struct Builder {
       src.q = buf; src.k = buf + H * dh; src.v = buf + 2 * H * dh;
       src.q_ld = src.k_ld = src.v_ld = (int)qkv_ld;
       src.n_heads = H; src.h0 = 0; src.head_cols = dh;
-      add_attention(src, f32 ? all_heads : 0ull);
-      ops.back().i1 = 0; ops.back().i2 = 1;                          // one instance
+      add_attention(src, last, f32 ? all_heads : 0ull);
+      ops.back().i2 = 1;                                             // one instance
     }
     // every head's fp32 output (H problems, one launch), then per instance the fused projection of the other heads
     pf = (int)probs.size();
     for (int h = 0; h < H; h++) {
-      GemmProb pp = prob8(M->zf32 + (long long)h * dh, (long long)T * H * dh, H * dh, nullptr, 0, 0,
-                          w32_ptr(M, 3, l, h), d, nullptr, 1, nullptr, M->headout + (long long)h * M->tile, M->tile, d, 0, T, d, dh, dh);
-      pp.M = T;
+      GemmProb pp = prob8(M->zf32 + (long long)h * dh + last_off(last, (long long)H * dh), (long long)T * H * dh, H * dh, nullptr, 0, 0,
+                          w32_ptr(M, 3, l, h), d, nullptr, 1, nullptr, M->headout + (long long)h * M->tile + lo, M->tile, d, 0, last, d, dh, dh);
+      pp.M = last ? M->B : T;
       probs.push_back(pp);
     }
-    add_op(OP_GEMM32, pf, H, T, d); work_gemm(pf);
+    add_op(OP_GEMM32, pf, H, last ? M->B : T, d); work_gemm(pf);
     w32_end(l, all_heads);
     Stream nxt = next_run(2 * l + 1, run.p == M->run_a ? M->run_b : M->run_a);
     for (int h = 0; h < H; h++) {
       OprojDesc od; memset(&od, 0, sizeof(od));
-      od.zc = M->zcodes; od.zc_is = (long long)T * H * Kh; od.zs = M->zscale; od.zs_is = (long long)T * H;
+      od.zc = M->zcodes + last_off(last, (long long)H * Kh); od.zc_is = (long long)T * H * Kh;
+      od.zs = M->zscale + last_off(last, H); od.zs_is = (long long)T * H;
       od.W = M->o_codes + (long long)l * H * d * Kh; od.ws = M->o_scale + (long long)l * H;
-      od.run_in = run.p; od.run_in_is = run.is; od.run_out = nxt.p + (long long)h * nxt.is; od.run_out_is = nxt.is;
+      od.run_in = run.p + lo; od.run_in_is = run.is; od.run_out = nxt.p + (long long)h * nxt.is + lo; od.run_out_is = nxt.is;
       od.bias = M->b_O + (long long)l * d;
-      od.H = H; od.Kh = Kh; od.skip_mask = 1ull << h; od.rpi = T; od.M = T; od.N = d;
+      od.H = H; od.Kh = Kh; od.skip_mask = 1ull << h; od.rpi = od.M = last ? M->B : T; od.N = d;
       od.aux_begin = -1; od.dh = M->dh;
-      od.extra = M->headout + (long long)h * M->tile; od.extra_is = M->tile;
+      od.extra = M->headout + (long long)h * M->tile + lo; od.extra_is = M->tile;
       odescs.push_back(od);
-      add_op(OP_OPROJ, (int)odescs.size() - 1, T, d);
-      ops.back().flops = 2.0 * T * d * dh * (H - 1);
+      add_op(OP_OPROJ, (int)odescs.size() - 1, od.M, d);
+      ops.back().flops = 2.0 * od.M * d * dh * (H - 1);
     }
     run = nxt;
   }
@@ -470,6 +501,8 @@ struct Builder {
     const unsigned long long off8 = fmask | dead;              // heads that take no part in the quantised kernels
     const int nf = __builtin_popcountll(fmask);
     const bool prefix = a.kind == PREFIX;
+    const bool last = last_rows(l);
+    const long long lo = last_off(last, d);
     float* const qkv_buf = prefix ? M->qkv_sh : M->qkv;
     std::vector<int> dead_list;
     for (int h = 0; h < H; h++) if ((dead >> h) & 1ull) dead_list.push_back(g.head(l, h));
@@ -496,6 +529,7 @@ struct Builder {
     std::map<std::pair<int, std::vector<int>>, int> seen;
     std::vector<int> grp_of(3 * H, -1);          // index into `groups` per (h, c) block
     int g_begin = (int)groups.size(), n_f32 = 0, patch_group = -1;
+    std::vector<char> all_rows(3 * H + 1, 0);    // groups some key or value input reads: in the last layer the others are needed at the last position only
     for (int h = 0; h < H; h++)
       for (int c = 0; c < 3; c++) {
         if ((dead >> h) & 1ull) continue;
@@ -525,32 +559,46 @@ struct Builder {
         int local = gi - g_begin;
         if (is_pi) {
           // fp32 rows of a group: a.n instances back to back, one block per group that needs them
-          if (!gd.out_f32) { gd.out_f32 = M->xf32 + (long long)n_f32 * a.n * M->tile; gd.out_f32_is = M->tile; n_f32++; }
+          if (!gd.out_f32) { gd.out_f32 = M->xf32 + (long long)n_f32 * a.n * M->tile; gd.out_f32_is = inst_stride(d); n_f32++; }
         } else if (!gd.out_codes) {
-          gd.out_codes = M->xcodes + (long long)local * M->nmax * T * Kd; gd.out_codes_is = (long long)T * Kd;
-          gd.out_scale = M->xscale + (long long)local * M->nmax * T; gd.out_scale_is = T;
+          gd.out_codes = M->xcodes + (long long)local * M->nmax * T * Kd; gd.out_codes_is = inst_stride(Kd);
+          gd.out_scale = M->xscale + (long long)local * M->nmax * T; gd.out_scale_is = inst_stride(1);
         }
+        if (c != 0) all_rows[local] = 1;
       }
     int n_groups = (int)groups.size() - g_begin;
+    if (last)
+      for (int i = 0; i < n_groups; i++) {
+        GroupDesc& gd = groups[g_begin + i];
+        if (all_rows[i]) continue;
+        gd.last_only = 1;                          // its rows then lie side by side, B per instance
+        gd.out_f32_is = (long long)M->B * d; gd.out_codes_is = (long long)M->B * Kd; gd.out_scale_is = M->B;
+      }
     add_build(g_begin, n_groups, patch_group);
     // ---- fp8 projections: runs of consecutive column blocks of quantised heads that read the same group
-    int pb = (int)probs.size(), maxN = 0;
+    int pb = (int)probs.size(), maxN = 0, maxM = 0;
     const long long qkv_ld = 3LL * H * dh;
-    for (int nb = 0; nb < 3 * H;) {
+    // (in the last layer the queries, needed at the last position only, are problems of their own and come last)
+    for (int part = last ? 1 : 0; part >= 0; part--)
+    for (int nb = last && part ? H : 0, end = last && !part ? H : 3 * H; nb < end;) {
       int gi = grp_of[nb];
       if ((off8 >> (nb % H)) & 1ull) { nb++; continue; }
       int e = nb + 1;
-      while (e < 3 * H && grp_of[e] == gi && !((off8 >> (e % H)) & 1ull)) e++;
+      while (e < end && grp_of[e] == gi && !((off8 >> (e % H)) & 1ull)) e++;
       const GroupDesc& gd = groups[gi];
-      probs.push_back(prob8(gd.out_codes, gd.out_codes_is, Kd, gd.out_scale, gd.out_scale_is, 1,
+      const bool lq = last && nb < H;
+      probs.push_back(prob8(gd.out_codes + last_off(lq && !gd.last_only, Kd), gd.out_codes_is, Kd,
+                            gd.out_scale + last_off(lq && !gd.last_only, 1), gd.out_scale_is, 1,
                             M->qkv_codes + ((long long)l * 3 * H * dh + (long long)nb * dh) * Kd, Kd,
                             M->qkv_scale + (long long)l * 3 * H + nb, dh, M->bqkv + (long long)l * 3 * H * dh + (long long)nb * dh,
-                            qkv_buf + (long long)nb * dh, (long long)T * qkv_ld, (int)qkv_ld, 0, T, (e - nb) * dh, Kd, d));
+                            qkv_buf + (long long)nb * dh + last_off(lq, qkv_ld), inst_stride(qkv_ld), (int)qkv_ld, 0, lq,
+                            (e - nb) * dh, Kd, d));
       probs.back().b16 = M->qbits == 16;
-      if ((e - nb) * dh > maxN) maxN = (e - nb) * dh;
+      maxN = std::max(maxN, (e - nb) * dh);
+      maxM = std::max(maxM, probs.back().M);
       nb = e;
     }
-    if ((int)probs.size() > pb) { add_op(OP_GEMM8, pb, (int)probs.size() - pb, T * a.n, maxN); work_gemm(pb); }
+    if ((int)probs.size() > pb) { add_op(OP_GEMM8, pb, (int)probs.size() - pb, maxM, maxN); work_gemm(pb); }
     // ---- fp32 projections of the heads in the precision set
     if (nf) {
       int pf = (int)probs.size();
@@ -559,12 +607,13 @@ struct Builder {
         if (!((fmask >> h) & 1ull)) continue;
         for (int c = 0; c < 3; c++) {
           const GroupDesc& gd = groups[grp_of[c * H + h]];
-          probs.push_back(prob8(gd.out_f32, gd.out_f32_is, d, nullptr, 0, 0, w32_ptr(M, c, l, h), dh, nullptr, 1,
-                                w32_ptr(M, 4 + c, l, h), qkv_buf + ((long long)c * H + h) * dh, (long long)T * qkv_ld,
-                                (int)qkv_ld, 0, T, dh, d, d));
+          const bool lq = last && c == 0;
+          probs.push_back(prob8(gd.out_f32 + last_off(lq && !gd.last_only, d), gd.out_f32_is, d, nullptr, 0, 0, w32_ptr(M, c, l, h), dh, nullptr, 1,
+                                w32_ptr(M, 4 + c, l, h), qkv_buf + ((long long)c * H + h) * dh + last_off(lq, qkv_ld), inst_stride(qkv_ld),
+                                (int)qkv_ld, 0, lq, dh, d, d));
         }
       }
-      add_op(OP_GEMM32, pf, 3 * nf, T * a.n, dh); work_gemm(pf);
+      add_op(OP_GEMM32, pf, 3 * nf, rows(false), dh); work_gemm(pf);
       if (prefix) w32_end(l, fmask);                    // a prefix pass stops before the output projection
     }
     if (prefix && off8 == all_heads) {
@@ -577,10 +626,10 @@ struct Builder {
     {
       AttnSrc src; memset(&src, 0, sizeof(src));
       src.q = qkv_buf; src.k = qkv_buf + H * dh; src.v = qkv_buf + 2 * H * dh;
-      src.q_is = src.k_is = src.v_is = (long long)T * qkv_ld;
+      src.q_is = src.k_is = src.v_is = inst_stride(qkv_ld);
       src.q_ld = src.k_ld = src.v_ld = (int)qkv_ld;
       src.n_heads = H; src.h0 = 0; src.head_cols = dh;
-      add_attention(src, fmask, dead);
+      add_attention(src, last, fmask, dead);
     }
     // ---- output projections of all heads fused with the stream update.  Only heads whose
     // individual output is needed (cache passes; a downstream receiver that treats the head's
@@ -589,13 +638,14 @@ struct Builder {
     if (prefix) { nxt.p = M->oth; nxt.is = 0; }       // stream + bias + every head but the investigated one
     const bool store_raw = (a.kind == BASE_CLEAN || a.kind == BASE_CORRUPT || a.kind == PI_CORRUPT);
     OprojDesc od; memset(&od, 0, sizeof(od));
-    od.zc = M->zcodes; od.zc_is = (long long)T * H * Kh; od.zs = M->zscale; od.zs_is = (long long)T * H;
+    od.zc = M->zcodes + last_off(last, (long long)H * Kh); od.zc_is = inst_stride((long long)H * Kh);
+    od.zs = M->zscale + last_off(last, H); od.zs_is = inst_stride(H);
     od.W = M->o_codes + (long long)l * H * d * Kh; od.ws = M->o_scale + (long long)l * H;
-    od.run_in = run.p; od.run_in_is = run.is; od.run_out = nxt.p; od.run_out_is = nxt.is;
+    od.run_in = run.p + lo; od.run_in_is = run.is; od.run_out = nxt.p + lo; od.run_out_is = nxt.is;
     od.bias = M->b_O + (long long)l * d;
-    od.H = H; od.Kh = Kh; od.skip_mask = off8; od.rpi = T; od.M = T * a.n; od.N = d;
+    od.H = H; od.Kh = Kh; od.skip_mask = off8; od.rpi = last ? M->B : rpi; od.rp0 = last ? 0 : rp0; od.M = rows(last); od.N = d;
     od.aux_begin = -1; od.dh = M->dh;
-    od.extra = deadsum; od.extra_is = 0;              // replaced below when fp32 heads are chained in front of it
+    od.extra = deadsum ? deadsum + lo : nullptr; od.extra_is = 0;              // replaced below when fp32 heads are chained in front of it
     bool any_aux = false;
     std::vector<HeadAux> hx(H);
     for (int h = 0; h < H; h++) {
@@ -604,8 +654,9 @@ struct Builder {
       if (store_raw) { Stream dst = sender_dest(s, nullptr, 0); hx[h].dst = dst.p; hx[h].dst_is = dst.is; }
       else if (general && plan->slot_of[s] >= 0) {
         hx[h].dst = slot_ptr(s); hx[h].dst_is = slot_is(s);
-        hx[h].sub = corrupt_ref_tile(s);
+        hx[h].sub = corrupt_ref_tile(s) + lo;
       }
+      if (hx[h].dst) hx[h].dst += lo;
       if (hx[h].dst && !((fmask >> h) & 1ull)) any_aux = true;
     }
     if (nf && !prefix) {
@@ -616,17 +667,17 @@ struct Builder {
       for (int h = 0; h < H; h++) {
         if (!((fmask >> h) & 1ull)) continue;
         int pf = (int)probs.size();
-        GemmProb pp = prob8(M->zf32 + (long long)k * dh, (long long)T * nf * dh, nf * dh, nullptr, 0, 0,
-                            w32_ptr(M, 3, l, h), d, nullptr, 1, nullptr, M->headout, M->tile, d, 0, T, d, dh, dh);
-        if (k > 0) { pp.add = M->headout; pp.add_is = M->tile; }
-        else if (deadsum) { pp.add = deadsum; pp.add_is = 0; }          // the chain starts from the dead heads' stand-ins
+        GemmProb pp = prob8(M->zf32 + (long long)k * dh + last_off(last, (long long)nf * dh), inst_stride((long long)nf * dh), nf * dh, nullptr, 0, 0,
+                            w32_ptr(M, 3, l, h), d, nullptr, 1, nullptr, M->headout + lo, inst_stride(d), d, 0, last, d, dh, dh);
+        if (k > 0) { pp.add = M->headout + lo; pp.add_is = inst_stride(d); }
+        else if (deadsum) { pp.add = deadsum + lo; pp.add_is = 0; }          // the chain starts from the dead heads' stand-ins
         pp.aux = hx[h].dst; pp.aux_is = hx[h].dst_is; pp.aux_sub = hx[h].sub;
         probs.push_back(pp);
-        add_op(OP_GEMM32, pf, 1, T * a.n, d); work_gemm(pf);
+        add_op(OP_GEMM32, pf, 1, rows(last), d); work_gemm(pf);
         k++;
       }
       w32_end(l, fmask);
-      od.extra = M->headout; od.extra_is = M->tile;
+      od.extra = M->headout + lo; od.extra_is = inst_stride(d);
     }
     if (off8 == all_heads && nf && !prefix) {
       // nothing is quantised in this layer: next = run + b_O + (sum of the fp32 heads)
@@ -634,23 +685,28 @@ struct Builder {
       cd.run_in = run.p; cd.run_in_is = run.is; cd.run_out = nxt.p; cd.run_out_is = nxt.is;
       cd.bias = M->b_O + (long long)l * d; cd.src_begin = (int)csrcs.size(); cd.n_src = 1;
       CombineSrc cs; memset(&cs, 0, sizeof(cs));
-      cs.src = M->headout; cs.src_is = M->tile;
+      cs.src = M->headout; cs.src_is = inst_stride(d);
       csrcs.push_back(cs);
       cdescs.push_back(cd);
       add_op(OP_COMBINE, (int)cdescs.size() - 1);
-      ops.back().bytes = 3.0 * a.n * (double)M->tile * 4.0;
+      ops.back().bytes = 3.0 * rows(false) * (double)d * 4.0;
     } else {
       if (any_aux) { od.aux_begin = (int)haux.size(); haux.insert(haux.end(), hx.begin(), hx.end()); }
       odescs.push_back(od);
-      add_op(OP_OPROJ, (int)odescs.size() - 1, T * a.n, d);
-      ops.back().flops = 2.0 * T * a.n * d * dh * (H - __builtin_popcountll(off8));
+      add_op(OP_OPROJ, (int)odescs.size() - 1, od.M, d);
+      ops.back().flops = 2.0 * od.M * d * dh * (H - __builtin_popcountll(off8));
     }
     run = nxt;
   }
 
   void mlp_block(int l, Stream& run) {
     const GraphDims& g = M->g;
-    const int d = M->d, T = M->T, Kd = M->Kd, Km = M->Km, m = M->m;
+    const int d = M->d, m = M->m;
+    const bool last = last_rows(l);
+    const long long lo = last_off(last, d);
+    const int R = rows(last);
+    // in the last layer the block's own tensors hold the B rows of every instance side by side
+    auto own_is = [&](long long ld) { return last ? M->B * ld : inst_stride(ld); };
     int w = g.mlpin(l), s = g.mlp(l);
     if (general && plan && !plan->live[s]) {
       // a dead MLP: the stream moves on with the corrupted run's output in its place
@@ -664,10 +720,11 @@ struct Builder {
     else fill_input(gd, general ? &plan->spec[w] : nullptr, 2 * l + 1, run);
     norm_params(gd, M->ln2_g + (long long)l * d, M->ln2_b + (long long)l * d);
     const int Ko = M->Kd_o, Kmo = M->Km_o, b16 = M->nb16 ? 1 : 0;      // row bytes of this block's operands (bfloat16: two per element)
-    if (f32_rest) { gd.out_f32 = M->xf32; gd.out_f32_is = M->tile; }
+    gd.last_only = last ? 1 : 0;
+    if (f32_rest) { gd.out_f32 = M->xf32; gd.out_f32_is = own_is(d); }
     else {
-      gd.out_codes = M->xcodes; gd.out_codes_is = (long long)T * Ko;
-      gd.out_scale = M->xscale; gd.out_scale_is = T;
+      gd.out_codes = M->xcodes; gd.out_codes_is = own_is(Ko);
+      gd.out_scale = M->xscale; gd.out_scale_is = own_is(1);
       if (b16) gd.qbits = 16;
     }
     groups.push_back(gd);
@@ -678,53 +735,53 @@ struct Builder {
     auto second_output = [&](GemmProb& po) {
       // the sender's own output (cache passes) or its difference to the corrupted run (a slot some receiver
       // reads) leaves through the second output
-      if (store_raw) { Stream dest = sender_dest(s, nullptr, 0); po.aux = dest.p; po.aux_is = dest.is; }
-      else if (general && plan->slot_of[s] >= 0) { po.aux = slot_ptr(s); po.aux_is = slot_is(s); po.aux_sub = corrupt_ref_tile(s); }
+      if (store_raw) { Stream dest = sender_dest(s, nullptr, 0); po.aux = dest.p + lo; po.aux_is = dest.is; }
+      else if (general && plan->slot_of[s] >= 0) { po.aux = slot_ptr(s) + lo; po.aux_is = slot_is(s); po.aux_sub = corrupt_ref_tile(s) + lo; }
     };
     if (f32_rest) {
       // all-fp32 mode: both matrix products on the fp32 masters; GELU in the first one's epilogue, SwiGLU by an
       // elementwise kernel over the two results
       int pb = (int)probs.size();
       probs.push_back(prob8(gd.out_f32, gd.out_f32_is, d, nullptr, 0, 0, M->W_in + (long long)l * d * m, m, nullptr, 1,
-                            M->b_in + (long long)l * m, M->hid, (long long)T * m, m, M->cfg.act == PAHQ_ACT_GELU ? 1 : 0, T, m, d, d));
+                            M->b_in + (long long)l * m, M->hid, own_is(m), m, M->cfg.act == PAHQ_ACT_GELU ? 1 : 0, last, m, d, d));
       if (swiglu)
         probs.push_back(prob8(gd.out_f32, gd.out_f32_is, d, nullptr, 0, 0, M->W_gate + (long long)l * d * m, m, nullptr, 1,
-                              nullptr, M->hid2, (long long)T * m, m, 0, T, m, d, d));
-      add_op(OP_GEMM32, pb, swiglu ? 2 : 1, T * a.n, m); work_gemm(pb);
-      if (swiglu) { add_op(OP_SWIGLU32); ops.back().bytes = 3.0 * a.n * T * (double)m * 4.0; }
+                              nullptr, M->hid2, own_is(m), m, 0, last, m, d, d));
+      add_op(OP_GEMM32, pb, swiglu ? 2 : 1, R, m); work_gemm(pb);
+      if (swiglu) { add_op(OP_SWIGLU32, R); ops.back().bytes = 3.0 * R * (double)m * 4.0; }
       pb = (int)probs.size();
-      GemmProb po = prob8(M->hid, (long long)T * m, m, nullptr, 0, 0, M->W_out + (long long)l * m * d, d, nullptr, 1,
-                          M->b_out + (long long)l * d, nxt.p, nxt.is, d, 0, T, d, m, m);
-      po.add = run.p; po.add_is = run.is;
+      GemmProb po = prob8(M->hid, own_is(m), m, nullptr, 0, 0, M->W_out + (long long)l * m * d, d, nullptr, 1,
+                          M->b_out + (long long)l * d, nxt.p + lo, nxt.is, d, 0, last, d, m, m);
+      po.add = run.p + lo; po.add_is = run.is;
       second_output(po);
       probs.push_back(po);
-      add_op(OP_GEMM32, pb, 1, T * a.n, d); work_gemm(pb);
+      add_op(OP_GEMM32, pb, 1, R, d); work_gemm(pb);
       run = nxt;
       return;
     }
     int pb = (int)probs.size();
     probs.push_back(prob8(gd.out_codes, gd.out_codes_is, Ko, gd.out_scale, gd.out_scale_is, 1,
                           M->in_codes + (long long)l * m * Ko, Ko, M->in_scale + l, m, M->b_in + (long long)l * m, M->hid,
-                          (long long)T * m, m, 0, T, m, Ko, d));       // the activation is applied by the hidden quantiser
+                          own_is(m), m, 0, last, m, Ko, d));           // the activation is applied by the hidden quantiser
     probs.back().b16 = b16;
     if (swiglu) {
       probs.push_back(prob8(gd.out_codes, gd.out_codes_is, Ko, gd.out_scale, gd.out_scale_is, 1,
                             M->gate_codes + (long long)l * m * Ko, Ko, M->gate_scale + l, m, nullptr, M->hid2,
-                            (long long)T * m, m, 0, T, m, Ko, d));
+                            own_is(m), m, 0, last, m, Ko, d));
       probs.back().b16 = b16;
     }
-    add_op(OP_GEMM8, pb, swiglu ? 2 : 1, T * a.n, m); work_gemm(pb);
-    add_op(OP_HIDQ, swiglu ? 2 : (M->cfg.act == PAHQ_ACT_GELU ? 1 : 0));
-    ops.back().bytes = (double)a.n * T * m * ((swiglu ? 8.0 : 4.0) + (b16 ? 2.0 : 1.0));
+    add_op(OP_GEMM8, pb, swiglu ? 2 : 1, R, m); work_gemm(pb);
+    add_op(OP_HIDQ, swiglu ? 2 : (M->cfg.act == PAHQ_ACT_GELU ? 1 : 0), R);
+    ops.back().bytes = (double)R * m * ((swiglu ? 8.0 : 4.0) + (b16 ? 2.0 : 1.0));
     // output projection fused with the stream update: next = run + b_out + out
     pb = (int)probs.size();
-    GemmProb po = prob8(M->hcodes, (long long)T * Kmo, Kmo, M->hscale, T, 1, M->out_codes + (long long)l * d * Kmo, Kmo,
-                        M->out_scale + l, d, M->b_out + (long long)l * d, nxt.p, nxt.is, d, 0, T, d, Kmo, m);
+    GemmProb po = prob8(M->hcodes, own_is(Kmo), Kmo, M->hscale, own_is(1), 1, M->out_codes + (long long)l * d * Kmo, Kmo,
+                        M->out_scale + l, d, M->b_out + (long long)l * d, nxt.p + lo, nxt.is, d, 0, last, d, Kmo, m);
     po.b16 = b16;
-    po.add = run.p; po.add_is = run.is;
+    po.add = run.p + lo; po.add_is = run.is;
     second_output(po);
     probs.push_back(po);
-    add_op(OP_GEMM8, pb, 1, T * a.n, d); work_gemm(pb);
+    add_op(OP_GEMM8, pb, 1, R, d); work_gemm(pb);
     run = nxt;
   }
 
@@ -778,7 +835,7 @@ struct Builder {
     if (f32_rest) {
       // all-fp32 mode: the unembedding on the fp32 master, logits in memory, log-softmax + KL over them
       probs.push_back(prob8(gd.out_f32, gd.out_f32_is, d, nullptr, 0, 0, M->W_U, V, nullptr, 1, M->b_U, lg, lg_is, Vp, 0,
-                            B, V, d, d));
+                            true, V, d, d));
       add_op(OP_GEMM32, pb, 1, B * a.n, V); work_gemm(pb);
       if (a.kind == BASE_CLEAN) { add_op(OP_LOGZ, 0, 0, 0, 0, M->logits_clean, M->logz_clean); ops.back().bytes = (double)B * V * 4.0; }
       else if (general) {
@@ -788,7 +845,7 @@ struct Builder {
       return;
     }
     probs.push_back(prob8(gd.out_codes, gd.out_codes_is, M->Kd_o, gd.out_scale, gd.out_scale_is, 1, M->u_codes, M->Kd_o,
-                          M->u_scale, V, M->b_U, lg, lg_is, Vp, 0, B, V, M->Kd_o, d));
+                          M->u_scale, V, M->b_U, lg, lg_is, Vp, 0, true, V, M->Kd_o, d));
     probs.back().b16 = M->nb16 ? 1 : 0;
     // With exact sums the unembedding itself reduces its rows to the parts of a log-sum-exp and of the KL
     // against the reference (one row of parts instead of one row of logits per candidate and sequence); the
@@ -835,6 +892,15 @@ struct Builder {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// A problem all of whose tensors hold the rows of the instances side by side is a problem of one instance: the kernels
+// then find a tile's rows without walking over instances (a 256-row tile crosses five of them with 50 rows each).
+void join_instances(GemmProb& p) {
+  auto joined = [&](long long is, long long ld) { return is == p.rpi * ld; };
+  if (p.aux || p.kl_part || !joined(p.a_is, p.lda) || (p.ascale && !joined(p.as_is, p.as_stride)) || !joined(p.c_is, p.ldc) ||
+      (p.add && !joined(p.add_is, p.ldc)) || (long long)p.M * p.ldc >= (1ll << 31)) return;
+  p.rpi = p.M; p.rp0 = 0;
+}
+
 }  // namespace
 
 int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
@@ -873,6 +939,7 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
       }
   }
   for (GroupDesc& gd : b.groups) if (!gd.qbits) gd.qbits = M->qbits;      // groups of bfloat16 blocks have said 16
+  for (GemmProb& p : b.probs) join_instances(p);
   for (AttnSrc& as : b.asrcs) { as.qbits = M->qbits; as.form = M->attn_form; }
   // ---- upload the descriptor tables
   Arena& A = M->arena;
@@ -935,18 +1002,18 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
         // the patched receiver's group (if any) is built by the edge-batched patch kernel
         int pg = o.i2;
         if (pg < 0) {
-          HIPCHK(launch_build_inputs(d_groups + o.i0, o.i1, d_terms, o.u64 ? 1 : n, T, B, S, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
+          HIPCHK(launch_build_inputs(d_groups + o.i0, o.i1, d_terms, o.u64 ? 1 : n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
         } else {
           if (pg > o.i0)
-            HIPCHK(launch_build_inputs(d_groups + o.i0, pg - o.i0, d_terms, n, T, B, S, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
+            HIPCHK(launch_build_inputs(d_groups + o.i0, pg - o.i0, d_terms, n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
           if (o.i0 + o.i1 > pg + 1)
-            HIPCHK(launch_build_inputs(d_groups + pg + 1, o.i0 + o.i1 - pg - 1, d_terms, n, T, B, S, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
+            HIPCHK(launch_build_inputs(d_groups + pg + 1, o.i0 + o.i1 - pg - 1, d_terms, n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
         }
         break;
       }
       case OP_PATCH:
         HIPCHK(launch_patch_build(d_groups + o.i0, (const float*)o.p0, M->delta, M->tile, M->send_dev + a.io_off + o.i1, o.i2, a.patch_mode,
-                                  T, B, S, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, st));
+                                  T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, st));
         break;
       case OP_GEMM8:
         for (int q = 0; q < o.i1; q++)
@@ -970,23 +1037,21 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
       }
       case OP_GEMM32: HIPCHK(launch_gemm_f32(d_probs + o.i0, o.i1, o.i2, o.i3, st)); break;
       case OP_ATTN: {
-        // o.i2 instances starting at o.i1 (0: all of the pass); the sources of such a range are already offset
-        const long long zc_is = (long long)T * M->H * M->Kh, zs_is = (long long)T * M->H,
-                        zf_is = (long long)T * M->dh * __builtin_popcountll(o.u64);
-        HIPCHK(launch_attention(b.asrcs[o.i0], M->zcodes + o.i1 * zc_is, zc_is, M->zscale + o.i1 * zs_is, zs_is,
-                                M->zf32 + o.i1 * zf_is, zf_is, o.u64, o.u64b, o.i2 ? o.i2 : n, B, S, M->H,
+        // o.i2 instances (0: all of the pass)
+        HIPCHK(launch_attention(b.asrcs[o.i0], M->zcodes, M->zscale, M->zf32, o.u64, o.u64b, o.i2 ? o.i2 : n, B, S, M->H,
                                 M->dh, M->Kh, M->cfg.pos == PAHQ_POS_ROPE, M->rope_tab, st));
         break;
       }
-      case OP_COMBINE: HIPCHK(launch_combine(d_cdesc, o.i0, d_csrc, o.i1 ? 1 : n, M->tile, d, st)); break;
+      case OP_COMBINE: HIPCHK(launch_combine(d_cdesc, o.i0, d_csrc, o.i1 ? 1 : n, M->tile, (long long)b.rp0 * d, d, st)); break;
       case OP_OPROJ:
         HIPCHK(launch_oproj_fused(d_odesc, o.i0, d_haux, o.i1, o.i2, M->H, M->dh, M->cfg.mma == PAHQ_MMA_F16_EXACT, M->qbits == 16, st));
         break;
       case OP_HIDQ:
-        HIPCHK(launch_hidden_quant(M->hid, o.i0 == 2 ? M->hid2 : nullptr, (long long)T * M->m, M->hcodes, (long long)T * M->Km_o,
-                                   M->hscale, T, n, T, M->m, M->Km_o, o.i0, M->nb16 ? 16 : M->qbits, st));
+        // the rows of all instances lie side by side: o.i1 of them
+        HIPCHK(launch_hidden_quant(M->hid, o.i0 == 2 ? M->hid2 : nullptr, 0, M->hcodes, 0, M->hscale, 0, 1, o.i1, M->m, M->Km_o, o.i0,
+                                   M->nb16 ? 16 : M->qbits, st));
         break;
-      case OP_SWIGLU32: HIPCHK(launch_swiglu_f32(M->hid, M->hid2, (long long)n * T * M->m, st)); break;
+      case OP_SWIGLU32: HIPCHK(launch_swiglu_f32(M->hid, M->hid2, (long long)o.i0 * M->m, st)); break;
       case OP_LD: {
         double* ld = o.i0 ? M->row_kl : (double*)o.p0;
         if (M->all_f32) HIPCHK(launch_logit_pair_f32(M->xf32, (long long)B * d, d, M->W_U, M->V, M->b_U, M->ans_dev, M->dis_dev, n, B, ld, st));

@@ -61,13 +61,6 @@ struct EpiPre {
   float sw[TN];      // column scale of columns nbase + 16 j + 4 lg .. + 3 (they share one weight slice)
   float4 bias[TN];   // bias of those columns (zero without a bias)
 };
-// Row m0 + r of a problem whose instances have rpi rows each: (instance, row in the instance), from the
-// split (i0, r0) of m0.  One wrap covers tiles that are not taller than an instance; shorter
-// instances take the loop.
-__device__ __forceinline__ void split_row(int i0, int r0, int r, int rpi, int& inst, int& row) {
-  inst = i0; row = r0 + r;
-  while (row >= rpi) { row -= rpi; inst++; }
-}
 __device__ __forceinline__ int wscale_index(const GemmProb& P, int n) {
   if (P.wscale_block >= P.N) return 0;
   return P.ws_shift >= 0 ? (n >> P.ws_shift) : n / P.wscale_block;
@@ -78,7 +71,7 @@ __device__ __forceinline__ void epi_prefetch(EpiPre<TM, TN>& E, const GemmProb& 
 #pragma unroll
   for (int i = 0; i < TM; i++) {
     int m = min(mbase + i * 16 + li, P.M - 1);
-    split_row(i0, r0, m - m0, P.rpi, E.inst[i], E.row[i]);
+    split_row(i0, r0, m - m0, P.rpi, P.rp0, E.inst[i], E.row[i]);
     E.sa[i] = GCF(P.ascale)[E.inst[i] * P.as_is + (long long)E.row[i] * P.as_stride];
   }
 #pragma unroll
@@ -219,13 +212,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gemm_x_k(const GemmP
   const uint8_t* src[NI];
   const int cg = ((lane & 7) ^ (lane >> 3)) * 16;
   auto set_src = [&](int m0, int n0) {
-    const int i0 = m0 / P.rpi, r0 = m0 - i0 * P.rpi;
+    int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
 #pragma unroll
     for (int t = 0; t < NI; t++) {
       int r = 8 * (wave * NI + t) + (lane >> 3);
       if (r < BM) {
         int m = min(m0 + r, P.M - 1), inst, row;
-        split_row(i0, r0, m - m0, P.rpi, inst, row);
+        split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
         src[t] = (const uint8_t*)P.A + (long long)inst * P.a_is + (long long)row * P.lda + cg;
       } else {
         int n = min(n0 + r - BM, P.N - 1);
@@ -323,7 +316,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gemm_x_k(const GemmP
     else wait_all_then_barrier();
     if (128 < P.K) issue(st1, 128);
     EpiPre<TM, TN> E;
-    { const int i0 = m0 / P.rpi; epi_prefetch<TM, TN>(E, P, m0, i0, m0 - i0 * P.rpi, mbase, nbase, li, lg); }
+    { int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0); epi_prefetch<TM, TN>(E, P, m0, i0, r0, mbase, nbase, li, lg); }
     compute(st0);
     for (int k0 = 128; k0 < P.K; k0 += 256) {        // slabs k0 (in st1) and k0 + 128 (in st0)
       wait_all_then_barrier();                       // the slab has landed for everyone, the other stage is free
@@ -392,13 +385,13 @@ __global__ __launch_bounds__(512, 1) void gemm_p_k(const GemmProb* probs) {
   const uint8_t* src[NI];
   const int cg = ((lane & 7) ^ (lane >> 3)) * 16;
   auto set_src = [&](int m0, int n0) {
-    const int i0 = m0 / P.rpi, r0 = m0 - i0 * P.rpi;
+    int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
 #pragma unroll
     for (int t = 0; t < NI; t++) {
       int r = 8 * (wave * NI + t) + (lane >> 3);
       if (r < BM) {
         int m = min(m0 + r, P.M - 1), inst, row;
-        split_row(i0, r0, m - m0, P.rpi, inst, row);
+        split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
         src[t] = (const uint8_t*)P.A + (long long)inst * P.a_is + (long long)row * P.lda + cg;
       } else {
         // LDS row 16 jj + li of a wave's 64-column block holds column 4 li + jj of the block, so that a lane's four
@@ -433,9 +426,9 @@ __global__ __launch_bounds__(512, 1) void gemm_p_k(const GemmProb* probs) {
     const float* g;
     float* dst;
     if (wave < 4) {
-      const int i0 = m0 / P.rpi;
+      int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
       int m = min(m0 + wave * 64 + lane, P.M - 1), inst, row;
-      split_row(i0, m0 - i0 * P.rpi, m - m0, P.rpi, inst, row);
+      split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
       g = P.ascale + inst * P.as_is + (long long)row * P.as_stride;
       dst = e_rs + wave * 64;
     } else {
@@ -524,7 +517,7 @@ __global__ __launch_bounds__(512, 1) void gemm_p_k(const GemmProb* probs) {
     const int nbase = n0 + wn * 64 + li * 4;
     const bool interior = (m0 + BM <= P.M) && (n0 + BN <= P.N);
     const bool col_on = interior || nbase < P.N;
-    const int i0 = m0 / P.rpi, r0 = m0 - i0 * P.rpi;
+    int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
     const float cs = e_cs[wn * 64 + li * 4];
     const float4 bias = *(const float4*)(e_bi + wn * 64 + li * 4);
     int inst[TM][4];
@@ -539,7 +532,7 @@ __global__ __launch_bounds__(512, 1) void gemm_p_k(const GemmProb* probs) {
         const int m = m0 + wm * 64 + i * 16 + lg * 4 + r;
         live[i][r] = col_on && (interior || m < P.M);
         int row;
-        split_row(i0, r0, min(m, P.M - 1) - m0, P.rpi, inst[i][r], row);
+        split_row(i0, r0, min(m, P.M - 1) - m0, P.rpi, P.rp0, inst[i][r], row);
         roff[i][r] = row * (int)P.ldc + nbase;
       }
     }
@@ -615,8 +608,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_k(const GemmPr
   for (int c = 0; c < A_CH; c++) {
     int ch = tid + c * NT, r = ch >> 3, kc = ch & 7;
     int m = m0 + r;
-    pa[c] = (m < P.M) ? (const uint8_t*)P.A + (long long)(m / P.rpi) * P.a_is + (long long)(m % P.rpi) * P.lda + kc * 16
-                      : nullptr;
+    int inst, row; row_origin(m, P.rpi, P.rp0, inst, row);
+    pa[c] = (m < P.M) ? (const uint8_t*)P.A + (long long)inst * P.a_is + (long long)row * P.lda + kc * 16 : nullptr;
   }
 #pragma unroll
   for (int c = 0; c < B_CH; c++) {
@@ -653,7 +646,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_k(const GemmPr
   load_slab(0);
   const int mbase = m0 + wm * WM, nbase = n0 + wn * WN;
   EpiPre<TM, TN> E;
-  { const int i0 = m0 / P.rpi; epi_prefetch<TM, TN>(E, P, m0, i0, m0 - i0 * P.rpi, mbase, nbase, li, lg); }
+  { int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0); epi_prefetch<TM, TN>(E, P, m0, i0, r0, mbase, nbase, li, lg); }
   for (int k0 = 0; k0 < P.K; k0 += 128) {
     __syncthreads();                 // previous slab fully consumed
     store_slab();
@@ -762,8 +755,8 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const GemmProb* probs) {
 #pragma unroll
   for (int c = 0; c < 2; c++) {
     int m = m0 + (tid >> 3) + 32 * c;
-    pa[c] = (m < P.M) ? (const float*)P.A + (long long)(m / P.rpi) * P.a_is + (long long)(m % P.rpi) * P.lda + (tid & 7) * 4
-                      : nullptr;
+    int inst, row; row_origin(m, P.rpi, P.rp0, inst, row);
+    pa[c] = (m < P.M) ? (const float*)P.A + (long long)inst * P.a_is + (long long)row * P.lda + (tid & 7) * 4 : nullptr;
   }
   // B tile 32 x 64 floats = 512 float4: thread -> k rows (tid >> 4) and (tid >> 4) + 16, float4 column tid & 15
   const int bn = n0 + (tid & 15) * 4;
@@ -820,7 +813,7 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const GemmProb* probs) {
     for (int r = 0; r < 4; r++) {
       int m = m0 + wm * 32 + i * 16 + lg * 4 + r;
       if (m >= P.M) continue;
-      int inst = m / P.rpi, row = m % P.rpi;
+      int inst, row; row_origin(m, P.rpi, P.rp0, inst, row);
 #pragma unroll
       for (int j = 0; j < 2; j++) {
         int n = n0 + wn * 32 + j * 16 + li;

@@ -29,9 +29,10 @@ struct GroupDesc {
   int qbits;          // grid of the codes: 4 = 4-bit round-to-nearest, anything else E4M3 (device_util.h, q_encode)
 };
 
-// One GEMM problem.  Rows are numbered 0 .. M-1 over all instances: row m belongs
-// to instance m / rpi and is row m % rpi of it, so a launch needs no instance
-// dimension and row tiles may straddle instances.
+// One GEMM problem.  Rows are numbered 0 .. M-1 over all instances, so a launch needs no instance dimension and row
+// tiles may straddle instances.  Instance 0 has rp0 + rpi rows, every other one rpi: row m belongs to instance
+// i = max(0, (m - rp0) / rpi) and is row m - i * rpi of it (rows rp0 .. rp0 + rpi - 1 of the instances after the
+// first; see "Rows of a pass" in engine.hip).
 //   val[m][n] = (sum_k A[m][k] * W[n][k]) * ascale[m] * wscale[n / wscale_block]
 //   C[m][n]   = act(val + bias[n]) + add[m][n]
 //   aux[m][n] = val - aux_sub[m % rpi][n]            (optional second output)
@@ -54,6 +55,7 @@ struct GemmProb {
   // (reference logits), kl_ref_logz [rpi]; both may be null (then the third value is 0).  C may be null.
   const float* kl_ref; const double* kl_ref_logz; float* kl_part; int kl_npart;
   int b16;             // operands are bfloat16 patterns, two bytes per element (lda, ldw, K stay in bytes), not e4m3 codes
+  int rp0;             // rows of instance 0 in front of the rpi rows every instance has
 };
 // Parts per row of the log-softmax / KL epilogue (128-column tiles, two wavefronts across).
 inline int kl_parts_per_row(int N) { return (N + 127) / 128 * 2; }
@@ -67,7 +69,7 @@ inline bool gemm8_prob_ok(const GemmProb& p) {
          p.a_is % 16 == 0 && a16(p.A) && a16(p.W) && p.ldc % 4 == 0 && p.c_is % 4 == 0 && p.add_is % 4 == 0 &&
          p.aux_is % 4 == 0 && (p.wscale_block % 4 == 0 || p.wscale_block >= p.N) && a16(p.C) && a16(p.add) && a16(p.aux) && a16(p.aux_sub) &&
          a16(p.bias) && (p.N + 3) / 4 * 4 <= p.ldc && p.lda >= p.K && p.ldw >= p.K &&
-         (long long)p.rpi * p.ldc < (1ll << 31) && (p.C || p.kl_part) &&
+         p.rp0 >= 0 && ((long long)p.rp0 + p.rpi) * p.ldc < (1ll << 31) && (p.C || p.kl_part) &&
          (p.act == 0 || p.M < 8192) &&      // the kernel of the large problems applies no activation (the path asks for none)
          (!p.kl_part || (p.kl_npart == kl_parts_per_row(p.N) && a16(p.kl_part) && a16(p.kl_ref) &&
                          (!p.kl_ref == !p.kl_ref_logz) && !p.add && !p.aux && p.act == 0));
@@ -99,7 +101,7 @@ struct OprojDesc {
   const float* run_in; long long run_in_is;
   float* run_out;      long long run_out_is;
   const float* bias;                        // [N] or null
-  int H, Kh, rpi, pad_;
+  int H, Kh, rpi, rp0;                      // rows of an instance, rows of instance 0 in front of them (as in GemmProb)
   int M, N, aux_begin, dh;                  // M = rows over all instances; aux_begin: first of H HeadAux, or -1; dh = d_head (Kh = dh padded to 128)
   unsigned long long skip_mask;             // bit h set: head h is computed in fp32 elsewhere (it arrives in `extra`)
 };
@@ -113,18 +115,20 @@ hipError_t launch_slice_absmax(const float* w, long long slice_elems, int n_slic
 hipError_t launch_quant_transpose(const float* w, int K, int N, const unsigned* amax_bits, float* scale_out,
                                   uint8_t* codes_out, int ldq, int qbits, hipStream_t s);
 
-hipError_t launch_embed(const int* tok, const float* W_E, const float* W_pos, float* out, int T, int S, int d,
+// out[r] = W_E[tok[r]] + W_pos[pos[r]] (W_pos may be null)
+hipError_t launch_embed(const int* tok, const int* pos, const float* W_E, const float* W_pos, float* out, int T, int d,
                         hipStream_t s);
 
+// Tiles have T rows, of which the first rp0 are built for instance 0 only; last_only groups: the last B rows of a tile.
 // shared_terms: the largest number of terms without instance stride in any of the groups (0: none)
-hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term* terms, int n_inst, int T, int B,
-                               int S, int d, int ldq, int norm_kind, float eps, int shared_terms, hipStream_t s);
+hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term* terms, int n_inst, int T, int rp0, int B,
+                               int d, int ldq, int norm_kind, float eps, int shared_terms, hipStream_t s);
 
 // Edge-batched patch: instance i reads x_i = xv - delta[send[i]] (mode 1) or
 // x_i = x_{i-1} - delta[send[i]] with x_{-1} = xv (mode 2), then norm and
 // fp32 / e4m3 output as in GroupDesc (base/run/terms of g are ignored).
 hipError_t launch_patch_build(const GroupDesc* g, const float* xv, const float* delta0, long long delta_stride,
-                              const int* send, int n_inst, int mode, int T, int B, int S, int d, int ldq,
+                              const int* send, int n_inst, int mode, int T, int rp0, int B, int d, int ldq,
                               int norm_kind, float eps, hipStream_t s);
 // xv -= delta[send[0]]; xv -= delta[send[1]]; ... (k terms, same order as mode 2 above)
 hipError_t launch_xv_advance(float* xv, const float* delta0, long long delta_stride, const int* send, int k,
@@ -151,25 +155,31 @@ hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int ma
 hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const HeadAux* auxs, int M, int N, int H, int dh,
                               int exact, int b16, hipStream_t s);
 
-// Causal attention per (instance, sequence, head).  q, k, v: fp32 rows [inst][T][..]; head hl of the
-// launch reads columns hl * head_cols .. + dh of each and writes output head h0 + hl (of H).
-// Heads whose bit is clear in f32_mask: z rows quantised per head -> zcodes [inst][T][H][ldz], zscale [inst][T][H].
-// Heads whose bit is set: z written unquantised to zf32 [inst][T][nf][dh], nf = number of set bits, a head's place
+// Causal attention per (instance, sequence, head).  q, k, v: fp32 rows; head hl of the launch reads columns
+// hl * head_cols .. + dh of each and writes output head h0 + hl (of H).
+// Position s of sequence b is row r = row_of[b * S + s] of a tile (null: b * S + s).  Rows below rp0 exist once, in
+// instance 0: they are read from there and written by the wave of instance 0.  Output row: r + (inst0 + instance) *
+// (B * S - rp0), with the instance taken as 0 below rp0.
+// Heads whose bit is clear in f32_mask: z rows quantised per head -> zcodes [row][H][ldz], zscale [row][H].
+// Heads whose bit is set: z written unquantised to zf32 [row][nf][dh], nf = number of set bits, a head's place
 // = number of set bits below its own.
 struct AttnSrc {
   const float* q; long long q_is; int q_ld; int form;     // form: 1 = the query-tile kernel also where the whole-sequence kernel applies (0: the launcher chooses)
-  const float* k; long long k_is; int k_ld; int pad1_;
-  const float* v; long long v_is; int v_ld; int pad2_;
+  const float* k; long long k_is; int k_ld; int rp0;      // rp0: rows that exist in instance 0 only
+  const float* v; long long v_is; int v_ld; int inst0;    // inst0: instance the launch's first one is in the outputs
   int n_heads, h0, head_cols, qbits;    // qbits: grid of the output codes (device_util.h, q_encode)
+  const int* row_of;                    // row of (sequence, position) in a tile, or null
+  int last_only, pad_;                  // 1: only the last position's output is needed (and written)
 };
-hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, long long zc_is, float* zscale,
-                            long long zs_is, float* zf32, long long zf_is, unsigned long long f32_mask, unsigned long long dead_mask, int n_inst, int B, int S,
-                            int H, int dh, int ldz, int rope, const float* rope_tab, hipStream_t s);
+hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, float* zscale, float* zf32, unsigned long long f32_mask,
+                            unsigned long long dead_mask, int n_inst, int B, int S, int H, int dh, int ldz, int rope,
+                            const float* rope_tab, hipStream_t s);
 // rope_tab: [n_pos][dh / 2] pairs (cos, sin), filled by launch_rope_table; read only when rope != 0, n_pos >= S
 hipError_t launch_rope_table(float* tab, int n_pos, int dh, float theta, hipStream_t s);
 
+// the first n_once elements are computed for instance 0 only
 hipError_t launch_combine(const CombineDesc* descs, int desc_index, const CombineSrc* srcs, int n_inst,
-                          long long n_elem, int d, hipStream_t s);
+                          long long n_elem, long long n_once, int d, hipStream_t s);
 
 // hidden rows [inst][T][m]: h = up (act 0), tanh-GELU(up) (act 1) or silu(gate) * up (act 2); row-quantise.
 hipError_t launch_hidden_quant(const float* up, const float* gate, long long h_is, uint8_t* codes, long long c_is,

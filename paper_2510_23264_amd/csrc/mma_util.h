@@ -55,6 +55,18 @@ __device__ __forceinline__ int xcd_tile(int wg, int total) {
   return (wg & 7) * chunk + (wg >> 3);
 }
 
+// Row numbering of a problem (GemmProb): instance 0 has rp0 + rpi rows, every other one rpi.  Split of row m0:
+__device__ __forceinline__ void row_origin(int m0, int rpi, int rp0, int& i0, int& r0) {
+  i0 = m0 < rp0 ? 0 : (m0 - rp0) / rpi;
+  r0 = m0 - i0 * rpi;
+}
+// Row m0 + r from the split (i0, r0) of m0: (instance, row in the instance).  One wrap covers tiles that are not
+// taller than an instance; shorter instances take the loop.
+__device__ __forceinline__ void split_row(int i0, int r0, int r, int rpi, int rp0, int& inst, int& row) {
+  inst = i0; row = r0 + r;
+  while (row >= rpi + rp0) { row -= rpi; inst++; }
+}
+
 // The slab loads, the waits for them and the workgroup barriers are written as volatile assembly
 // with a memory clobber.  The compiler's own wait insertion treats a load into LDS as something
 // every later LDS read may depend on wherever control flow merges, and waits for all of them

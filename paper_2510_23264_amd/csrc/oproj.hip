@@ -39,7 +39,8 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
 #pragma unroll
   for (int c = 0; c < 4; c++) {
     int m = m0 + (tid >> 3) + 32 * c;
-    pa[c] = (m < D.M) ? D.zc + (long long)(m / D.rpi) * D.zc_is + (long long)(m % D.rpi) * D.H * D.Kh + kc * 16 : nullptr;
+    int inst, row; row_origin(m, D.rpi, D.rp0, inst, row);
+    pa[c] = (m < D.M) ? D.zc + (long long)inst * D.zc_is + (long long)row * D.H * D.Kh + kc * 16 : nullptr;
   }
 #pragma unroll
   for (int c = 0; c < 2; c++) {
@@ -69,7 +70,8 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
     int m = m0 + wave * 32 + i * 16 + li;
     row_m[i] = m;
     int mm = m < D.M ? m : D.M - 1;
-    zs_p[i] = D.zs + (long long)(mm / D.rpi) * D.zs_is + (long long)(mm % D.rpi) * D.H;
+    int inst, row; row_origin(mm, D.rpi, D.rp0, inst, row);
+    zs_p[i] = D.zs + (long long)inst * D.zs_is + (long long)row * D.H;
   }
 
   v4f tot[TM][TN];
@@ -147,9 +149,10 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
         if (ax.dst) {
           int nb = n0 + j * 16 + lg * 4;
           if (m < D.M && nb < D.N) {
-            long long off = (long long)(m % D.rpi) * D.N + nb;
+            int inst, row; row_origin(m, D.rpi, D.rp0, inst, row);
+            long long off = (long long)row * D.N + nb;
             if (ax.sub) { float4 u = *(const float4*)(ax.sub + off); val.x -= u.x; val.y -= u.y; val.z -= u.z; val.w -= u.w; }
-            *(float4*)(ax.dst + (long long)(m / D.rpi) * ax.dst_is + off) = val;
+            *(float4*)(ax.dst + (long long)inst * ax.dst_is + off) = val;
           }
         }
       }
@@ -160,8 +163,8 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
   for (int i = 0; i < TM; i++) {
     int m = row_m[i];
     if (m >= D.M) continue;
-    int inst = m / D.rpi;
-    long long roff = (long long)(m % D.rpi) * D.N;
+    int inst, row; row_origin(m, D.rpi, D.rp0, inst, row);
+    long long roff = (long long)row * D.N;
 #pragma unroll
     for (int j = 0; j < TN; j++) {
       int nb = n0 + j * 16 + lg * 4;
@@ -230,9 +233,9 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
   for (int t = 0; t < NI; t++) {
     int r = 8 * (wave * NI + t) + (lane >> 3);
     if (r < BM) {
-      int m = min(m0 + r, D.M - 1);
-      src[t] = D.zc + (long long)(m / D.rpi) * D.zc_is + (long long)(m % D.rpi) * D.H * D.Kh +
-               (long long)(c / CPH) * D.Kh + (c % CPH) * 16;
+      int m = min(m0 + r, D.M - 1), inst, row;
+      row_origin(m, D.rpi, D.rp0, inst, row);
+      src[t] = D.zc + (long long)inst * D.zc_is + (long long)row * D.H * D.Kh + (long long)(c / CPH) * D.Kh + (c % CPH) * 16;
       stride[t] = (long long)HPS * D.Kh;
     } else {
       int n = min(n0 + r - BM, D.N - 1);
@@ -246,8 +249,8 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
   const float* zsrc;
   {
     const int q = (HPS == 2) ? ((wave & 3) >> 1) : 0;
-    const int m = min(m0 + (wave & 1) * 64 + lane, D.M - 1);
-    zsrc = D.zs + (long long)(m / D.rpi) * D.zs_is + (long long)(m % D.rpi) * D.H + q;
+    int inst, row; row_origin(min(m0 + (wave & 1) * 64 + lane, D.M - 1), D.rpi, D.rp0, inst, row);
+    zsrc = D.zs + (long long)inst * D.zs_is + (long long)row * D.H + q;
   }
   int si = 0;                              // stage of the next request
   auto issue = [&]() {                     // fetches the next slab and advances
@@ -292,9 +295,10 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
         if constexpr (AUX) if (ax.dst) {
           int m = mbase + i * 16 + li, nb = nbase + j * 16 + lg * 4;
           if (m < D.M && nb < D.N) {
-            long long off = (long long)(m % D.rpi) * D.N + nb;
+            int inst, row; row_origin(m, D.rpi, D.rp0, inst, row);
+            long long off = (long long)row * D.N + nb;
             if (ax.sub) { float4 u = gload4(ax.sub + off); val.x -= u.x; val.y -= u.y; val.z -= u.z; val.w -= u.w; }
-            gstore4(ax.dst + (long long)(m / D.rpi) * ax.dst_is + off, val);
+            gstore4(ax.dst + (long long)inst * ax.dst_is + off, val);
           }
         }
       }
@@ -388,8 +392,8 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
   for (int i = 0; i < TM; i++) {
     const int m = mbase + i * 16 + li;
     if (m >= D.M) continue;
-    const int inst_i = m / D.rpi;
-    const long long roff = (long long)(m - inst_i * D.rpi) * D.N;
+    int inst_i, row_i; row_origin(m, D.rpi, D.rp0, inst_i, row_i);
+    const long long roff = (long long)row_i * D.N;
 #pragma unroll
     for (int j = 0; j < TN; j++) {
       int nb = nbase + j * 16 + lg * 4;

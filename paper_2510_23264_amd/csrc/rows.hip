@@ -82,18 +82,18 @@ hipError_t launch_quant_transpose(const float* w, int K, int N, const unsigned* 
 }
 
 // ------------------------------------------------------------------ embedding
-__global__ void embed_k(const int* tok, const float* W_E, const float* W_pos, float* out, int T, int S, int d) {
+__global__ void embed_k(const int* tok, const int* pos, const float* W_E, const float* W_pos, float* out, int T, int d) {
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)T * d) return;
   int t = (int)(i / d), e = (int)(i % d);
   float v = W_E[(long long)tok[t] * d + e];
-  if (W_pos) v += W_pos[(long long)(t % S) * d + e];
+  if (W_pos) v += W_pos[(long long)pos[t] * d + e];
   out[i] = v;
 }
-hipError_t launch_embed(const int* tok, const float* W_E, const float* W_pos, float* out, int T, int S, int d,
+hipError_t launch_embed(const int* tok, const int* pos, const float* W_E, const float* W_pos, float* out, int T, int d,
                         hipStream_t s) {
   long long n = (long long)T * d;
-  hipLaunchKernelGGL(embed_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tok, W_E, W_pos, out, T, S, d);
+  hipLaunchKernelGGL(embed_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tok, pos, W_E, W_pos, out, T, d);
   return hipGetLastError();
 }
 
@@ -250,15 +250,16 @@ __device__ __forceinline__ void emit_row(const float (&y)[MAXE], int E, int d, i
 // chunk; with most edges removed that is the larger part of what a receiver's input is gathered from.  The
 // arithmetic of an instance does not depend on the chunk size or on its place in the chunk.
 template <int MAXE, bool VEC>
-__global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, const Term* terms, int T, int B,
-                                                       int S, int d, int ldq, int norm_kind, float eps) {
+__global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, const Term* terms, int T, int rp0, int B,
+                                                       int d, int ldq, int norm_kind, float eps) {
   GroupDesc g = groups[blockIdx.y];
   int inst = blockIdx.z;
   int lane = threadIdx.x & 63;
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (inst > 0 && !g.last_only) row += rp0;          // rows below rp0 exist in instance 0 only
   int rows = g.last_only ? B : T;
   if (row >= rows) return;
-  long long src = (long long)(g.last_only ? row * S + S - 1 : row) * d;
+  long long src = (long long)(g.last_only ? T - B + row : row) * d;
   // the vector forms with up to 16 values per lane are launched for exactly that width (PAHQ_DISPATCH_E): the width is
   // then a constant and every `j < E` below folds away
   const int E = (VEC && MAXE <= 16) ? MAXE : (d >> 6);
@@ -294,8 +295,8 @@ __global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, c
 // removed that is the larger part of what a receiver's input is gathered from.  The arithmetic of an instance
 // does not depend on the chunk size or on its place in the chunk, and is that of the kernel above.
 template <int MAXE, bool VEC>
-__global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* groups, const Term* terms, int T, int B,
-                                                              int S, int d, int ldq, int norm_kind, float eps,
+__global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* groups, const Term* terms, int T, int rp0,
+                                                              int B, int d, int ldq, int norm_kind, float eps,
                                                               int n_inst, int chunk, int n_groups) {
   // Workgroup -> (row quad, group): all groups of a row quad run back to back on one XCD (workgroup id mod 8), so
   // that a sender row several receivers of the layer gather is fetched into that XCD's L2 once.
@@ -306,7 +307,9 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
   int row = rq * 4 + (threadIdx.x >> 6);
   int rows = g.last_only ? B : T;
   if (row >= rows) return;
-  long long src = (long long)(g.last_only ? row * S + S - 1 : row) * d;
+  const bool once = !g.last_only && row < rp0;       // a row of instance 0 only
+  if (once && blockIdx.z > 0) return;
+  long long src = (long long)(g.last_only ? T - B + row : row) * d;
   // the vector forms with up to 16 values per lane are launched for exactly that width (PAHQ_DISPATCH_E): the width is
   // then a constant and every `j < E` below folds away
   const int E = (VEC && MAXE <= 16) ? MAXE : (d >> 6);
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
   }
   float gn[MAXE], of[MAXE];               // read once for the chunk, not once per instance
   norm_params_load<MAXE, VEC>(gn, of, E, lane, norm_kind, g.gain, g.offset);
-  const int i_end = min(n_inst, ((int)blockIdx.z + 1) * chunk);
+  const int i_end = once ? 1 : min(n_inst, ((int)blockIdx.z + 1) * chunk);
   for (int inst = blockIdx.z * chunk; inst < i_end; inst++) {
     float x[MAXE];
 #pragma unroll
@@ -344,14 +347,15 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
 template <int MAXE, bool VEC>
 __global__ __launch_bounds__(256) void patch_build_k(const GroupDesc* gp, const float* xv, const float* delta0,
                                                       long long delta_stride, const int* send, int n_inst, int mode,
-                                                      int T, int B, int S, int d, int ldq, int norm_kind,
+                                                      int T, int rp0, int B, int d, int ldq, int norm_kind,
                                                       float eps) {
   GroupDesc g = *gp;
   int lane = threadIdx.x & 63;
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   int rows = g.last_only ? B : T;
   if (row >= rows) return;
-  long long src = (long long)(g.last_only ? row * S + S - 1 : row) * d;
+  if (!g.last_only && row < rp0) n_inst = 1;         // a row of instance 0 only
+  long long src = (long long)(g.last_only ? T - B + row : row) * d;
   // the vector forms with up to 16 values per lane are launched for exactly that width (PAHQ_DISPATCH_E): the width is
   // then a constant and every `j < E` below folds away
   const int E = (VEC && MAXE <= 16) ? MAXE : (d >> 6);
@@ -375,15 +379,16 @@ __global__ __launch_bounds__(256) void patch_build_k(const GroupDesc* gp, const 
 // Independent candidates (x_i = xv - delta[send[i]]): one wavefront per (row, instance).
 template <int MAXE, bool VEC>
 __global__ __launch_bounds__(256) void patch_indep_k(const GroupDesc* gp, const float* xv, const float* delta0,
-                                                      long long delta_stride, const int* send, int T, int B, int S,
+                                                      long long delta_stride, const int* send, int T, int rp0, int B,
                                                       int d, int ldq, int norm_kind, float eps) {
   GroupDesc g = *gp;
   int lane = threadIdx.x & 63;
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   int inst = blockIdx.y;
+  if (inst > 0 && !g.last_only) row += rp0;          // rows below rp0 exist in instance 0 only
   int rows = g.last_only ? B : T;
   if (row >= rows) return;
-  long long src = (long long)(g.last_only ? row * S + S - 1 : row) * d;
+  long long src = (long long)(g.last_only ? T - B + row : row) * d;
   // the vector forms with up to 16 values per lane are launched for exactly that width (PAHQ_DISPATCH_E): the width is
   // then a constant and every `j < E` below folds away
   const int E = (VEC && MAXE <= 16) ? MAXE : (d >> 6);
@@ -415,8 +420,8 @@ __global__ __launch_bounds__(256) void patch_indep_k(const GroupDesc* gp, const 
     else { CALL(64, false); }                                       \
   } while (0)
 
-hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term* terms, int n_inst, int T, int B,
-                               int S, int d, int ldq, int norm_kind, float eps, int shared_terms, hipStream_t s) {
+hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term* terms, int n_inst, int T, int rp0, int B,
+                               int d, int ldq, int norm_kind, float eps, int shared_terms, hipStream_t s) {
   if (n_groups == 0 || n_inst == 0) return hipSuccess;
   // Groups with instance-independent terms go to the kernel that sums those once per chunk of instances (wide
   // rows, more than 16 values per lane, have no registers to spare for the shared sum and stay with the plain
@@ -426,31 +431,31 @@ hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term
     int chunk = (int)std::min<long long>(8, std::max<long long>(1, blocks / 16384));
     const int rq8 = ((T + 3) / 4 + 7) / 8 * 8;        // row quads, padded to the 8 XCDs (the padding exits at once)
     dim3 grid(rq8 * n_groups, 1, (n_inst + chunk - 1) / chunk);
-#define CALL(M, V) hipLaunchKernelGGL((build_inputs_shared_k<M, V>), grid, dim3(256), 0, s, groups, terms, T, B, S, d, ldq, norm_kind, eps, n_inst, chunk, n_groups)
+#define CALL(M, V) hipLaunchKernelGGL((build_inputs_shared_k<M, V>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps, n_inst, chunk, n_groups)
     PAHQ_DISPATCH_E(d / 64, CALL);
 #undef CALL
     return hipGetLastError();
   }
   dim3 grid((T + 3) / 4, n_groups, n_inst);
-#define CALL(M, V) hipLaunchKernelGGL((build_inputs_k<M, V>), grid, dim3(256), 0, s, groups, terms, T, B, S, d, ldq, norm_kind, eps)
+#define CALL(M, V) hipLaunchKernelGGL((build_inputs_k<M, V>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps)
   PAHQ_DISPATCH_E(d / 64, CALL);
 #undef CALL
   return hipGetLastError();
 }
 
 hipError_t launch_patch_build(const GroupDesc* g, const float* xv, const float* delta0, long long delta_stride,
-                              const int* send, int n_inst, int mode, int T, int B, int S, int d, int ldq,
+                              const int* send, int n_inst, int mode, int T, int rp0, int B, int d, int ldq,
                               int norm_kind, float eps, hipStream_t s) {
   if (n_inst == 0) return hipSuccess;
   if (mode == 1) {
     dim3 grid2((T + 3) / 4, n_inst);
-#define CALL(M, V) hipLaunchKernelGGL((patch_indep_k<M, V>), grid2, dim3(256), 0, s, g, xv, delta0, delta_stride, send, T, B, S, d, ldq, norm_kind, eps)
+#define CALL(M, V) hipLaunchKernelGGL((patch_indep_k<M, V>), grid2, dim3(256), 0, s, g, xv, delta0, delta_stride, send, T, rp0, B, d, ldq, norm_kind, eps)
     PAHQ_DISPATCH_E(d / 64, CALL);
 #undef CALL
     return hipGetLastError();
   }
   dim3 grid((T + 3) / 4);
-#define CALL(M, V) hipLaunchKernelGGL((patch_build_k<M, V>), grid, dim3(256), 0, s, g, xv, delta0, delta_stride, send, n_inst, mode, T, B, S, d, ldq, norm_kind, eps)
+#define CALL(M, V) hipLaunchKernelGGL((patch_build_k<M, V>), grid, dim3(256), 0, s, g, xv, delta0, delta_stride, send, n_inst, mode, T, rp0, B, d, ldq, norm_kind, eps)
   PAHQ_DISPATCH_E(d / 64, CALL);
 #undef CALL
   return hipGetLastError();
@@ -519,12 +524,17 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
 // A thread owns four values of up to four instances.  A dead layer's stand-ins arrive as tens of sources that are
 // the same tile for every instance: each is loaded once for the thread's instances, four sources' loads are in
 // flight together, and every instance's sum keeps the order of the sources.
-__global__ void combine_k(const CombineDesc* descs, int di, const CombineSrc* srcs, long long n4, int d, int n_inst) {
+__global__ void combine_k(const CombineDesc* descs, int di, const CombineSrc* srcs, long long n4, long long once4, int d, int n_inst) {
   constexpr int IPT = 4;
   CombineDesc D = descs[di];
-  const int inst0 = blockIdx.y * IPT, ni = min(IPT, n_inst - inst0);
+  const int inst0 = blockIdx.y * IPT;
+  int ni = min(IPT, n_inst - inst0);
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
+  if (i < once4) {                     // elements of instance 0 only
+    if (inst0 > 0) return;
+    ni = 1;
+  }
   long long e = i * 4;
   float4 acc[IPT];
   float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -577,10 +587,10 @@ __global__ void combine_k(const CombineDesc* descs, int di, const CombineSrc* sr
     if (q < ni) *(float4*)(D.run_out + (inst0 + q) * D.run_out_is + e) = acc[q];
 }
 hipError_t launch_combine(const CombineDesc* descs, int desc_index, const CombineSrc* srcs, int n_inst,
-                          long long n_elem, int d, hipStream_t s) {
+                          long long n_elem, long long n_once, int d, hipStream_t s) {
   long long n4 = n_elem / 4;
   hipLaunchKernelGGL(combine_k, dim3((unsigned)((n4 + 255) / 256), (n_inst + 3) / 4), dim3(256), 0, s, descs,
-                     desc_index, srcs, n4, d, n_inst);
+                     desc_index, srcs, n4, n_once / 4, d, n_inst);
   return hipGetLastError();
 }
 

@@ -1,0 +1,98 @@
+"""The rows a pass computes: the last layer at the last position only, and -- for the candidates of a batch -- the rows
+at which the two prompts cannot differ once for all of them.  Sizes at which that can go wrong: one layer (the first is
+the last), one position, one sequence, tiles of 16 positions that end or begin with a shared row; prompts that differ
+from the first position on, from the last but one, or nowhere."""
+import os
+import sys
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+import synth                                        # noqa: E402
+from synth import ModelShape                        # noqa: E402
+from oracle.acdc import Acdc, MODE_ALL_FP32         # noqa: E402
+from oracle.model import Model as OModel, ALL       # noqa: E402
+from test_gpu_modes import F32_ATOL, F32_RTOL, rnd_removed   # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+#       layers heads d_head d_mlp B  S  llama
+SIZES = [(1, 3, 16, 96, 4, 7, 0), (1, 2, 64, 0, 3, 16, 0), (2, 2, 64, 132, 3, 17, 0), (2, 3, 32, 64, 1, 33, 0),
+         (2, 2, 128, 96, 2, 5, 1), (2, 4, 64, 96, 5, 1, 0), (3, 2, 64, 68, 1, 70, 1)]
+FIRST = {"start": lambda S, b: 0, "late": lambda S, b: max(0, S - 2), "mixed": lambda S, b: (5 * b + 3) % max(1, S - 1), "never": None}
+
+
+def make(size, first, seed):
+    L, H, dh, m, B, S, llama = size
+    more = dict(norm=1, act=2, pos=1, norm_eps=1e-6) if llama else dict(act=1 if m else 0)
+    shape = ModelShape(n_layers=L, n_heads=H, d_head=dh, d_model=128, d_mlp=m, vocab=211, n_ctx=S, **more)
+    w = synth.make_weights(shape, seed, std=0.15, affine_std=0.1)
+    rng = np.random.default_rng(seed)
+    clean = rng.integers(0, shape.vocab, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    if FIRST[first]:
+        for b in range(B):
+            at = FIRST[first](S, b)
+            corrupt[b, at] = (clean[b, at] + 1 + rng.integers(0, shape.vocab - 1)) % shape.vocab
+            for s in range(at + 1, S - 1):
+                if rng.random() < 0.3:
+                    corrupt[b, s] = rng.integers(0, shape.vocab)
+    return shape, w, clean, corrupt
+
+
+@pytest.mark.parametrize("first", sorted(FIRST))
+@pytest.mark.parametrize("size", SIZES)
+def test_against_the_oracle(size, first):
+    """Nothing quantised: every edge of the graph, on the whole graph and on a pruned one, to rounding."""
+    import paper_2510_23264_amd as P
+    shape, w, clean, corrupt = make(size, first, 3)
+    gm = P.Model(shape, w, *clean.shape, precision=P.ALL_FP32, max_batch_edges=5)
+    try:
+        gm.clean_cache(clean, corrupt)
+        om = OModel(shape, w)
+        g, oa = om.g, Acdc(om, clean, corrupt, MODE_ALL_FP32)
+        for frac in (0.0, 0.5):
+            for r in range(g.n_receivers):
+                R = rnd_removed(g, frac, 100 + r, r)
+                gm.set_removed(g.removed_to_flat(R).astype(np.uint8))
+                got = gm.eval_edges(r, np.arange(g.n_upstream(r), dtype=np.int32))
+                want = np.array([oa.kl_edge(r, u, removed=R) for u in range(g.n_upstream(r))])
+                assert (np.abs(got - want) <= F32_ATOL + F32_RTOL * np.abs(want)).all(), (size, first, frac, r)
+        gm.set_removed(np.zeros(g.n_edges(), np.uint8))
+        s = g.n_senders - 1
+        a = gm.get_sender_output(1, s)
+        b = om.forward(corrupt, ALL)[0][s].reshape(a.shape)
+        assert np.abs(a - b).max() <= 1e-4 * np.abs(b).max()
+    finally:
+        gm.close()
+
+
+@pytest.mark.parametrize("size", SIZES)
+@pytest.mark.parametrize("options", [dict(), dict(precision=1), dict(low_bits=4), dict(nonattn_bf16=True), dict(split_qkv=False), dict(mma=0)])
+def test_a_score_does_not_depend_on_its_batch(size, options):
+    """Quantised modes: a candidate's bits are the same alone (where every row is its own) and at any place in a batch."""
+    import paper_2510_23264_amd as P
+    shape, w, clean, corrupt = make(size, "mixed", 4)
+    out = []
+    for batch in (1, 7):
+        gm = P.Model(shape, w, *clean.shape, max_batch_edges=batch, **options)
+        try:
+            gm.clean_cache(clean, corrupt)
+            res, rng = [], np.random.default_rng(1)
+            for r in range(P.n_receivers(gm.cfg)):
+                first = sum(P.n_upstream(gm.cfg, q) for q in range(r))
+                state = (rng.random(gm.n_edges) < (0.5 if r % 2 else 0.0)).astype(np.uint8)
+                state[:first] = 0
+                gm.set_removed(state)
+                n = P.n_upstream(gm.cfg, r)
+                got = np.empty(n, np.float32)
+                order = np.arange(n, dtype=np.int32) if batch == 1 else rng.permutation(n).astype(np.int32)
+                got[order] = gm.eval_edges(r, order)
+                res.append(got)
+                res.append(np.float32([gm.eval_current(r)]))
+                if batch == 1:
+                    rng.permutation(n)
+            out.append(np.concatenate(res))
+        finally:
+            gm.close()
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32)), (size, options)
