@@ -560,16 +560,26 @@ int pahq_clean_cache(pahq_model* M, const int32_t* clean_tok, const int32_t* cor
   if (!M || !clean_tok || !corrupt_tok) return PAHQ_EINVAL;
   for (int i = 0; i < M->T; i++)
     if (clean_tok[i] < 0 || clean_tok[i] >= M->V || corrupt_tok[i] < 0 || corrupt_tok[i] >= M->V) return PAHQ_EINVAL;
-  // The order of a tile's rows for this prompt pair ("Rows of a pass" in engine.hip): by position, then by sequence, so
-  // that the rows at the last position are the last B.
+  // The order of a tile's rows for this prompt pair ("Rows of a pass" in engine.hip): first the rows in front of the
+  // first position at which their sequence's prompts differ, then the others, each by position, then by sequence.  The
+  // last position always counts among the others, so that its rows are the last B.
   const int T = M->T, B = M->B, S = M->S;
   std::vector<int> table(4 * (size_t)T);                // row_of | row_pos | clean tokens | corrupt tokens
   int *row_of = table.data(), *row_pos = row_of + T, *tc = row_pos + T, *tx = tc + T;
-  for (int s = 0, row = 0; s < S; s++)
-    for (int b = 0; b < B; b++, row++) {
-      const int t = b * S + s;
-      row_of[t] = row; row_pos[row] = s; tc[row] = clean_tok[t]; tx[row] = corrupt_tok[t];
-    }
+  std::vector<int> first(B, S - 1);
+  for (int b = 0; b < B; b++)
+    for (int s = S - 2; s >= 0; s--) if (clean_tok[b * S + s] != corrupt_tok[b * S + s]) first[b] = s;
+  int row = 0;
+  for (int others = 0; others < 2; others++) {
+    for (int s = 0; s < S; s++)
+      for (int b = 0; b < B; b++) {
+        if ((s >= first[b]) != (others == 1)) continue;
+        const int t = b * S + s;
+        row_of[t] = row; row_pos[row] = s; tc[row] = clean_tok[t]; tx[row] = corrupt_tok[t];
+        row++;
+      }
+    if (!others) M->rp0 = row;
+  }
   M->has_cache = false;                                 // what is cached no longer matches the order of the rows
   M->row_of_host.assign(row_of, row_of + T);
   HIPCHK(hipMemcpyAsync(M->row_of, row_of, T * sizeof(int), hipMemcpyHostToDevice, M->stream));

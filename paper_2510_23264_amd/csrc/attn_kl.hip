@@ -53,7 +53,12 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
   auto at = [&](const float* base, long long is, int ld, int row) {
     return base + (row < src.rp0 ? 0 : inst) * is + (long long)row * ld;
   };
-  const int a0 = src.last_only ? ST - 1 : 0;                           // first query tile that is needed
+  const int inst_o = src.inst0 + inst;
+  // first query tile that is needed: a sequence's rows below rp0 are its first ones, and only instance 0 writes them
+  int a0 = src.last_only ? ST - 1 : 0;
+#pragma unroll
+  for (int a = 0; a < ST - 1; a++)
+    if (inst_o > 0 && a0 == a && !__ballot(rw[a] >= src.rp0)) a0 = a + 1;
 
   float q[ST][CH], k[ST][CH];
   // STG (one 16-position tile, d_head 64): the three 16 x 64 blocks go from global memory straight into this
@@ -200,7 +205,6 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
   const bool f32 = (f32_mask >> h) & 1ull;
   // place of this head among the fp32 heads, and their number
   const int f32_slot = __popcll(f32_mask & ((1ull << h) - 1ull)), f32_n = __popcll(f32_mask);
-  const int inst_o = src.inst0 + inst;
   // output row of tile row r, and whether this wave writes it
   auto out_row = [&](int r) { return (long long)r + (r < src.rp0 ? 0ll : (long long)inst_o * (B * S - src.rp0)); };
   auto writes = [&](int pos, int r) { return pos < S && (r >= src.rp0 || inst_o == 0) && (!src.last_only || pos == S - 1); };

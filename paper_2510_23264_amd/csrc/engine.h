@@ -76,6 +76,7 @@ struct pahq_model {
   int *tok_clean, *tok_corrupt, *send_dev;       // tokens in the order of a tile's rows
   int *row_of, *row_pos;                  // row of (sequence, position) in a tile [B * S]; position of a row [T]
   std::vector<int> row_of_host;           // host copy of row_of
+  int rp0 = 0;                            // rows of a tile at which no candidate differs from another ("Rows of a pass" in engine.hip)
   float *clean, *corrupt, *delta;         // [Ns] tiles each (delta has one more, all zero)
   float *rc, *rx;                         // [2L+1] residual prefixes (entry 0 unused: it is sender 0's tile)
   float *logits_clean, *logits_corrupt;   // [B][V]
