@@ -43,3 +43,27 @@ def test_noalloc_row_quantiser_matches_the_model_bound_one():
         assert lib.pahq_quantize_rows_noalloc(None, None, 4, 8, None, None) == -1
     finally:
         gm.close()
+
+
+@pytest.mark.parametrize("cols", [1, 2, 3, 5, 63, 257, 1023, 1024, 1025, 1027, 4093, 4096, 4097, 16381, 16384, 16385])
+@pytest.mark.parametrize("rows, shift", [(1, 0), (7, 1), (9, 3), (130, 2)])
+def test_noalloc_rows_at_the_edges_of_its_kernels(rows, cols, shift):
+    """Row lengths around what 64, 256 and 1024 threads hold, number of rows no multiple of four, codes that start at any
+    byte of a word and rows that start at any float: scale and codes of the oracle's quantiser, nothing written outside."""
+    import torch
+    import paper_2510_23264_amd as P
+    from oracle.e4m3 import quantize_rows
+    rng = np.random.default_rng(rows * 100003 + cols)
+    x = _rows(rng, rows, cols)
+    flat = torch.zeros(rows * cols + 4, dtype=torch.float32, device="cuda")
+    xd = flat[shift:shift + rows * cols].view(rows, cols)
+    xd.copy_(torch.from_numpy(x))
+    buf = torch.full((rows * cols + 8,), 0xAA, dtype=torch.uint8, device="cuda")
+    codes = buf[shift:shift + rows * cols].view(rows, cols)
+    scales = torch.full((rows + 2,), -1.0, dtype=torch.float32, device="cuda")
+    P.quantize_rows_noalloc(xd, codes, scales[:rows])
+    torch.cuda.synchronize()
+    want_c, want_s = quantize_rows(x)
+    assert (scales[:rows].cpu().numpy().view(np.uint32) == want_s.astype(np.float32).reshape(-1).view(np.uint32)).all()
+    assert (codes.cpu().numpy() == want_c).all()
+    assert (buf[:shift] == 0xAA).all() and (buf[shift + rows * cols:] == 0xAA).all() and (scales[rows:] == -1.0).all()
