@@ -20,8 +20,9 @@
 // differ by D_s alone, agree there: a candidate pass computes these rp0 rows for its first instance only, and the other
 // instances' keys and values of these positions are read from it.  (Reference runs of several heads differ everywhere:
 // their precision does; they compute all rows.)  What it gives is the share of those rows, a third to a half with two
-changed template positions in sixteen: candidates into layer 5 of 12 at the GPT-2-small shape 296 -> 149 ms, its pruned
-graph 73 -> 45 ms, 24 layers of 1024 (three positions in 24) 395 -> 355 ms.  The rows at the last position come last, in the order of the
+// changed template positions in sixteen: candidates into layer 5 of 12 at the GPT-2-small shape 296 -> 149 ms, its pruned
+// graph 73 -> 45 ms, 24 layers of 1024 (three positions in 24) 395 -> 355 ms.  The rows at the
+// last position come last, in the order of the
 // sequences.  What a pass computes last is read at that position
 // only: the output node takes the B last rows, so in the last layer the queries, the output projection and the MLP are
 // needed there alone, and keys and values everywhere.  Passes that end in a score compute just that (`last` below);
