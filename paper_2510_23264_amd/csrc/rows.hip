@@ -239,6 +239,9 @@ __device__ __forceinline__ void emit_row(const float (&y)[MAXE], int E, int d, i
     } else {
 #pragma unroll
       for (int j = 0; j < MAXE; j++) if (j < E) o[lane + 64 * j] = (uint8_t)q_encode(y[j] * inv, qb);
+      // Zero codes up to the row's stride (half a slab of the product where d is an odd multiple of 64): with bfloat16
+      // blocks the buffer held rows of another length, whose bytes can be the codes of NaN, which times zero is NaN.
+      if (4 * lane < ldq - d) *(uint32_t*)(o + d + 4 * lane) = 0u;
     }
     if (lane == 0) g.out_scale[inst * g.out_scale_is + row] = scale;
   }

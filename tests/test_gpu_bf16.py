@@ -214,3 +214,35 @@ def test_sixteen_bits_exact_zero_and_limits():
     with pytest.raises(P.PahqError) as e:
         P.Model(small, w1, c1.shape[0], c1.shape[1], low_bits=16)
     assert e.value.code == -6
+
+
+@pytest.mark.parametrize("d_model, n_heads", [(64, 1), (192, 3)])
+def test_rows_of_an_odd_number_of_half_slabs(d_model, n_heads):
+    """d_model an odd multiple of 64: the heads' rows of codes are padded to whole slabs, the bfloat16 rows that share
+    their buffer are not.  Per-edge values against the oracle, and the same bits from batches of one and of seven."""
+    import paper_2510_23264_amd as P
+    shape = synth.ModelShape(n_layers=3, n_heads=n_heads, d_head=64, d_model=d_model, d_mlp=320, vocab=300, n_ctx=12, act=1)
+    w = synth.make_weights(shape, 5, std=0.12, affine_std=0.1)
+    clean, corrupt = synth.make_tokens(shape.vocab, 4, 12, "uniform", 3, False, 5)
+    pr = Pair(shape, w, clean, corrupt, nonattn_bf16=True)
+    one = P.Model(shape, w, 4, 12, max_batch_edges=1, nonattn_bf16=True)
+    many = P.Model(shape, w, 4, 12, max_batch_edges=7, nonattn_bf16=True)
+    try:
+        g, cases, got = pr.g, [], []
+        one.clean_cache(clean, corrupt)
+        many.clean_cache(clean, corrupt)
+        for i, r in enumerate([g.OUT, g.headin(2, 0, 1), g.headin(1, n_heads - 1, 0), g.mlpin(1), g.headin(0, 0, 2)]):
+            R = g.empty_removed() if i % 2 == 0 else random_removed(g, 0.4, 31 + i, from_receiver=r)
+            senders = np.arange(g.n_upstream(r), dtype=np.int32)
+            flat = g.removed_to_flat(R).astype(np.uint8)
+            one.set_removed(flat); many.set_removed(flat); pr.gm.set_removed(flat)
+            a, b = one.eval_edges(r, senders), many.eval_edges(r, senders)
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), (d_model, r)
+            got.append(np.concatenate([[pr.gm.eval_current(r)], a]))
+            cases.append((r, R, senders))
+        res = kl_with_spread(pr.om, clean, corrupt, pr.mode, cases, seeds=6)
+        want = np.concatenate([[r["kl_current"]] + list(r["kl_new"]) for r in res])
+        sigma = np.concatenate([[r["sigma_current"]] + list(r["sigma_new"]) for r in res])
+        check_kl_cases(np.concatenate(got), want, sigma, what="d_model %d, bf16 non-attention" % d_model)
+    finally:
+        pr.close(); one.close(); many.close()
