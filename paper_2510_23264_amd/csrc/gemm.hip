@@ -26,6 +26,7 @@
 //
 // gemm_f32: plain fp32 C = A * W (+ bias) with V_MFMA_F32_16X16X4_F32 (true
 //   fp32 multiply-accumulate) for the investigated head.
+#include <algorithm>
 #include <atomic>
 #include "kernels.h"
 #include "device_util.h"
@@ -344,6 +345,107 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gemm_x_k(const GemmP
     slab0_here = true;       // the barrier at the top publishes slab 0
     j = jn; m0 = m0n; n0 = n0n;
   }
+}
+
+// ------------------------------------------------------------------ exact sums, problems of few tiles
+// A problem with fewer 128 x 128 tiles than the chip has room for leaves compute units idle and the others waiting for
+// their loads slab by slab.  Here tiles are smaller (their number fills the chip), a workgroup has one tile, and NS
+// stages of LDS keep NS - 1 slabs on their way.  Operand order, steps and epilogue are those of gemm_x_k: same bits.
+template <int WAVES_M, int WAVES_N, int TM, int TN, int NS, bool B16>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gemm_s_k(const GemmProb* probs) {
+  constexpr int NW = WAVES_M * WAVES_N;
+  constexpr int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16, ROWS = BM + BN;
+  constexpr int NI = ROWS / 8 / NW;            // load instructions per wave and slab (8 rows each)
+  constexpr int STAGE = ROWS * 128;
+  static_assert(ROWS % (8 * NW) == 0 && BM % 8 == 0, "rows must split evenly over the waves");
+  __shared__ __attribute__((aligned(1024))) uint8_t st[NS * STAGE];
+
+  const GemmProb P = probs[blockIdx.y];
+  const int mt = (P.M + BM - 1) / BM, nt = (P.N + BN - 1) / BN;
+  const int lin = xcd_tile(blockIdx.x, mt * nt);
+  if (blockIdx.x >= (unsigned)((mt * nt + 7) / 8 * 8) || lin >= mt * nt) return;
+  const bool col_first = P.N > P.M;            // as in gemm_x_k
+  const int m0 = (col_first ? lin % mt : lin / nt) * BM, n0 = (col_first ? lin / mt : lin % nt) * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int li = lane & 15, lg = lane >> 4;
+  const int mbase = m0 + wm * TM * 16, nbase = n0 + wn * TN * 16;
+  int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
+  EpiPre<TM, TN> E;                            // in front of the slabs, so that the counted waits cover it
+  epi_prefetch<TM, TN>(E, P, m0, i0, r0, mbase, nbase, li, lg);
+
+  const uint8_t* src[NI];
+  const int cg = ((lane & 7) ^ (lane >> 3)) * 16;
+#pragma unroll
+  for (int t = 0; t < NI; t++) {
+    const int r = 8 * (wave * NI + t) + (lane >> 3);
+    if (r < BM) {
+      int m = min(m0 + r, P.M - 1), inst, row;
+      split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
+      src[t] = (const uint8_t*)P.A + (long long)inst * P.a_is + (long long)row * P.lda + cg;
+    } else {
+      src[t] = (const uint8_t*)P.W + (long long)min(n0 + r - BM, P.N - 1) * P.ldw + cg;
+    }
+  }
+  const uint32_t lds0 = lds_addr_of(st);
+  auto issue = [&](int stage) {
+    const uint32_t base = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + wave * NI * 1024);
+#pragma unroll
+    for (int t = 0; t < NI; t++) { slab_load16(src[t], base + t * 1024); src[t] += 128; }
+  };
+  const int offA = (wm * TM * 16 + li) * 128, offB = (BM + wn * TN * 16 + li) * 128;
+  v4f acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const uint8_t* s) {
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const int sw = ((4 * q + lg) ^ (li & 7)) * 16;
+      uint4 wa[TM], wb[TN];
+#pragma unroll
+      for (int i = 0; i < TM; i++) wa[i] = *(const uint4*)(s + offA + i * 2048 + sw);
+#pragma unroll
+      for (int j = 0; j < TN; j++) wb[j] = *(const uint4*)(s + offB + j * 2048 + sw);
+      if constexpr (B16) {
+        union U { uint4 u; v8bf h; };
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          U hb; hb.u = wb[j];
+#pragma unroll
+          for (int i = 0; i < TM; i++) { U ha; ha.u = wa[i]; acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hb.h, ha.h, acc[i][j], 0, 0, 0); }
+        }
+      } else {
+        v8h ha[TM][2];
+#pragma unroll
+        for (int i = 0; i < TM; i++) { ha[i][0] = decode8(wa[i].x, wa[i].y); ha[i][1] = decode8(wa[i].z, wa[i].w); }
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          const v8h hb0 = decode8(wb[j].x, wb[j].y), hb1 = decode8(wb[j].z, wb[j].w);
+#pragma unroll
+          for (int i = 0; i < TM; i++) {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hb0, ha[i][0], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hb1, ha[i][1], acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+    }
+  };
+  const int nslab = P.K >> 7;
+#pragma unroll
+  for (int k = 0; k < NS - 1; k++) if (k < nslab) issue(k);
+  int sc = 0, sr = NS - 1;                     // stage of the slab to multiply, of the next request
+  for (int k = 0; k < nslab; k++) {
+    wait_slab_barrier<NS, NI>(nslab - 1 - k);  // the slab has landed for everyone, the previous one's stage is free
+    if (k + NS - 1 < nslab) issue(sr);
+    compute(st + sc * STAGE);
+    sr = sc;
+    sc = (sc == NS - 1) ? 0 : sc + 1;
+  }
+  if (P.kl_part) epi_kl<TM, TN>(E, P, acc, mbase, nbase, li, lg, (n0 / BN) * WAVES_N + wn);
+  else epi_store<TM, TN>(E, P, acc, mbase, nbase, li, lg);
 }
 
 // ------------------------------------------------------------------ exact sums, three-stage pipeline
@@ -673,36 +775,79 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_k(const GemmPr
   epi_store<TM, TN>(E, P, acc, mbase, nbase, li, lg);
 }
 
-// Problems with the log-softmax / KL epilogue: always the 128 x 128 kernel, whose column tiling the number
-// of parts per row (kl_parts_per_row) is derived from.
+// Which tile a launch of the exact-sum kernels takes.  With r = tiles per compute unit, rounded up, the time of a launch
+// is close to a + b r in units of a 128 x 128 tile of a full chip; a is what a tile's dependent steps take when nothing
+// else runs beside it.  (a, b) are fits to timings of M 128 .. 50000, N 64 .. 12288, K 128 .. 11008.  The choice is within
+// 5 % of the best of the six at most of these sizes.  Measured, us (128 x 128 or 256 x 128, which was the rule before,
+// against what is taken now): 1024 x 512 x 2048 23.8 -> 8.8, 1024 x 2048 x 512 12.4 -> 7.6, 3000 x 768 x 3072 35 -> 26,
+// 8192 x 512 x 2048 32 -> 25, 512 x 4096 x 11008 102 -> 61, 9000 x 2304 x 768 50 -> 45.  From five tiles of 256 x 128 per unit
+// on that kernel is the fastest whatever the remainder (50000 x 3072 x 768: 261 against 355 and more).
+enum ExactTile { TILE_256x128, TILE_128x128, TILE_64x128, TILE_128x64, TILE_64x64, TILE_32x64 };
+static ExactTile pick_tile(int n_probs, int M, int N, bool b16, bool kl) {
+  auto per_cu = [&](int bm, int bn) {
+    const long long t = (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * n_probs;
+    return (double)((t + 255) / 256);
+  };
+  ExactTile best; double cost;
+  auto consider = [&](ExactTile t, double c) { if (c < cost) { best = t; cost = c; } };
+  if (N <= 64 && !kl) { best = TILE_128x64; cost = 0.37 + 0.48 * per_cu(128, 64); }
+  else {
+    best = TILE_128x128; cost = 0.5 + 0.85 * per_cu(128, 128);
+    if (!b16 && !kl && M >= 8192 && N >= 128) {
+      const double r = per_cu(256, 128);
+      if (r >= 5 || 0.1 + 1.8 * r <= cost) { best = TILE_256x128; cost = 0.1 + 1.8 * r; }
+      if (r >= 5) return best;
+    }
+    consider(TILE_64x128, 0.37 + 0.48 * per_cu(64, 128));
+  }
+  if (!kl) {           // (the parts of a row of the KL epilogue are 64 columns of one wave)
+    consider(TILE_64x64, 0.3 + 0.26 * per_cu(64, 64));
+    consider(TILE_32x64, 0.27 + 0.17 * per_cu(32, 64));
+  }
+  return best;
+}
+// grid of the persistent kernel: at most `per` workgroups (limited by LDS) per compute unit
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool B16>
+static hipError_t launch_x(const GemmProb* probs, int n_probs, int M, int N, int per, hipStream_t s) {
+  constexpr int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16;
+  const long long tiles = (long long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+  const int gx = (int)std::min<long long>((tiles + 7) / 8 * 8, 256LL * per);
+  hipLaunchKernelGGL((gemm_x_k<WAVES_M, WAVES_N, TM, TN, B16>), dim3(gx, n_probs), dim3(256), 0, s, probs);
+  return hipGetLastError();
+}
+template <int TM, bool B16>
+static hipError_t launch_s(const GemmProb* probs, int n_probs, int M, int N, hipStream_t s) {
+  const long long tiles = (long long)((M + 32 * TM - 1) / (32 * TM)) * ((N + 63) / 64);
+  if (tiles > 0x7ffffff0LL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemm_s_k<2, 2, TM, 2, 3, B16>), dim3((unsigned)((tiles + 7) / 8 * 8), n_probs), dim3(256), 0, s, probs);
+  return hipGetLastError();
+}
+template <bool B16>
+static hipError_t launch_tile(ExactTile t, const GemmProb* probs, int n_probs, int M, int N, hipStream_t s) {
+  switch (t) {
+    case TILE_64x128: return launch_x<2, 2, 2, 4, B16>(probs, n_probs, M, N, 3, s);
+    case TILE_128x64: return launch_x<4, 1, 2, 4, B16>(probs, n_probs, M, N, 3, s);
+    case TILE_64x64: return launch_s<2, B16>(probs, n_probs, M, N, s);
+    case TILE_32x64: return launch_s<1, B16>(probs, n_probs, M, N, s);
+    default: return launch_x<2, 2, 4, 4, B16>(probs, n_probs, M, N, 2, s);
+  }
+}
+
+// Problems with the log-softmax / KL epilogue: the 128-column tilings that the number of parts per row
+// (kl_parts_per_row) is derived from.
 hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int b16, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  int tiles = ((max_M + 127) / 128) * ((max_N + 127) / 128);
-  int gx = (tiles + 7) / 8 * 8;
-  if (gx > 512) gx = 512;
-  if (b16) hipLaunchKernelGGL((gemm_x_k<2, 2, 4, 4, true>), dim3(gx, n_probs), dim3(256), 0, s, probs);
-  else hipLaunchKernelGGL((gemm_x_k<2, 2, 4, 4>), dim3(gx, n_probs), dim3(256), 0, s, probs);
-  return hipGetLastError();
+  const ExactTile t = pick_tile(n_probs, max_M, max_N, b16 != 0, true);
+  return b16 ? launch_tile<true>(t, probs, n_probs, max_M, max_N, s) : launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
 }
 
 hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int exact, int b16, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  if (b16) {
-    // bfloat16 operands: the two-stage kernel at every size (the three-stage kernel has no such form)
-    if (!exact) return hipErrorInvalidValue;
-    const bool wide = max_N > 64;
-    int tiles = ((max_M + 127) / 128) * (wide ? (max_N + 127) / 128 : (max_N + 63) / 64);
-    int gx = (tiles + 7) / 8 * 8;
-    if (gx > 512) gx = 512;
-    dim3 grid(gx, n_probs);
-    if (wide) hipLaunchKernelGGL((gemm_x_k<2, 2, 4, 4, true>), grid, dim3(256), 0, s, probs);
-    else hipLaunchKernelGGL((gemm_x_k<4, 1, 2, 4, true>), grid, dim3(256), 0, s, probs);
-    return hipGetLastError();
-  }
+  // bfloat16 operands: exact sums only (and no three-stage kernel)
+  if (b16) return exact ? launch_tile<true>(pick_tile(n_probs, max_M, max_N, true, false), probs, n_probs, max_M, max_N, s) : hipErrorInvalidValue;
   if (exact) {
-    // persistent: at most two workgroups per compute unit (64 KB of LDS each), 256 compute units
-    const bool wide = max_N > 64;
-    if (wide && max_M >= 8192 && max_N >= 128) {
+    const ExactTile t = pick_tile(n_probs, max_M, max_N, false, false);
+    if (t == TILE_256x128) {
       // one 512-thread workgroup per compute unit, three 48 KB stages + 2 KB of scales
       const int lds_bytes = 3 * 384 * 128 + 2048;
       // the attribute belongs to the kernel's code object on one device: set once per device (atomically, so that
@@ -721,12 +866,7 @@ hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int ma
       hipLaunchKernelGGL((gemm_p_k<0>), dim3(gx, n_probs), dim3(512), lds_bytes, s, probs);
       return hipGetLastError();
     }
-    int tiles = ((max_M + 127) / 128) * (wide ? (max_N + 127) / 128 : (max_N + 63) / 64);
-    int gx = (tiles + 7) / 8 * 8;
-    if (gx > 512) gx = 512;
-    dim3 grid(gx, n_probs);
-    if (wide) hipLaunchKernelGGL((gemm_x_k<2, 2, 4, 4>), grid, dim3(256), 0, s, probs);
-    else hipLaunchKernelGGL((gemm_x_k<4, 1, 2, 4>), grid, dim3(256), 0, s, probs);
+    return launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
   } else {
     int tiles = ((max_M + 127) / 128) * ((max_N + 63) / 64);
     dim3 grid((tiles + 7) / 8 * 8, n_probs);

@@ -90,6 +90,22 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
+// The two at one place of a slab loop: at most N loads outstanding, and none of this wave's LDS reads in flight when the
+// barrier lets another wave overwrite what they read.
+template <int N>
+__device__ __forceinline__ void wait_vm_barrier() {
+  static_assert(N < 64, "vmcnt has six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+// The wait in front of a slab with `after` more slabs behind it, of which a loop of NS stages has requested up to
+// NS - 2, each with L loads of this wave.
+template <int NS, int L>
+__device__ __forceinline__ void wait_slab_barrier(int after) {
+  static_assert(NS >= 2 && NS <= 4, "stages");
+  if (after >= NS - 2) wait_vm_barrier<(NS - 2) * L>();
+  else if (NS == 4 && after == 1) wait_vm_barrier<L>();
+  else wait_vm_barrier<0>();
+}
 // "Everything has arrived" is said with the builtin, so that the compiler also knows that its own
 // loads (scales, bias) are complete and does not wait for them again in the middle of a slab.
 // 0x0F70: vmcnt(0), expcnt and lgkmcnt left at their maxima.
