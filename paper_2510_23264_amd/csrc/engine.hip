@@ -30,6 +30,7 @@
 // sixth and a sixteenth of the rest at 16 positions: candidates into layer 5 of 12 at the GPT-2-small shape 330 -> 302
 // ms, into the last layer of a 7B-class model 82 -> 34 ms.)
 #include "engine.h"
+#include <algorithm>
 #include <map>
 #include <string.h>
 
@@ -1043,7 +1044,12 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
         HIPCHK(launch_ref_probs((const float*)o.p0, (const double*)(uintptr_t)o.u64, (double*)o.p1, n * B, M->V, M->Vp, st));
         break;
       }
-      case OP_GEMM32: HIPCHK(launch_gemm_f32(d_probs + o.i0, o.i1, o.i2, o.i3, st)); break;
+      case OP_GEMM32: {
+        int form = 2;
+        for (int q = 0; q < o.i1; q++) form = std::min(form, gemm32_form(b.probs[o.i0 + q]));
+        HIPCHK(launch_gemm_f32(d_probs + o.i0, o.i1, o.i2, o.i3, form, st));
+        break;
+      }
       case OP_ATTN: {
         // o.i2 instances (0: all of the pass)
         HIPCHK(launch_attention(b.asrcs[o.i0], M->zcodes, M->zscale, M->zf32, o.u64, o.u64b, o.i2 ? o.i2 : n, B, S, M->H,

@@ -878,8 +878,8 @@ hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int ma
 // ------------------------------------------------------------------ fp32
 // 64 x 64 tile, K slabs of 32, four waves as 2 x 2, each 32 x 32 (2 x 2 MFMA tiles).
 // MFMA 16x16x4 f32: A operand of lane (i, g) = A[i][g], B operand = B[g][i],
-// result lane (i, g) holds C[4g + r][i].  Requires K % 4 == 0 and 16-byte aligned rows
-// (true for d_model and d_head here); global loads are 16 bytes per lane.
+// result lane (i, g) holds C[4g + r][i].  Global loads are 16 bytes per lane where rows allow them.  For what the
+// kernel below does not take: K not a multiple of 32 (heads of 16, an MLP of such a width).
 __global__ __launch_bounds__(256) void gemm_f32_k(const GemmProb* probs) {
   __shared__ float sA[64][33];
   __shared__ float sB[32][65];
@@ -963,8 +963,158 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const GemmProb* probs) {
     }
 }
 
-hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, hipStream_t s) {
+// The fp32 product for K a multiple of 32 and 16-byte aligned rows of A.  Per element the same sum as gemm_f32_k: one
+// V_MFMA_F32_16X16X4_F32 per four k, ascending.  W is the first operand here, so that a lane owns one row and four
+// neighbouring columns (16-byte stores).  Slabs of 32 k go from global memory straight into LDS, two stages, one barrier
+// per slab; a lane reads its single k of a step (a wider read would hand it four k of one row and change the order of
+// the sum).  LDS rows have no padding: chunk c (16 bytes) of row r of A sits at chunk c ^ (r & 7), chunk c of row k of W
+// at c ^ swz(k), so that the 64 words a read of W takes lie in 64 banks and those of A in at least 32.
+// Bound by the fp32 matrix cores' issue once the chip is full (16384 x 2048 x 512: 390 -> 312 us, 110 of a nominal 157
+// TFLOP/s), by a wave's chain of reads and products before that: the tile is chosen for enough waves in flight (see
+// launch_gemm_f32; 2700 x 128 x 4096 165 -> 56 us, 1024 x 512 x 2048 89 -> 31 us, 16384 x 512 x 2048 376 -> 305 us).
+// Three or four stages instead of two gain nothing (the reads, not the loads, are waited for) and cost occupancy.
+// WV4: rows of W are 16-byte aligned too; otherwise (an unembedding with an odd vocabulary) W comes word by word.
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool WV4>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const GemmProb* probs, int n_probs, int mt, int nt, int col_first) {
+  constexpr int NW = WAVES_M * WAVES_N, NS = 2;
+  constexpr int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16;
+  constexpr int IA = BM / 8 / NW;                       // load instructions per wave and slab: A (8 rows each)
+  constexpr int IB = (WV4 ? BN / 8 : BN / 2) / NW;      // and W (256 or 64 words each)
+  constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && BN >= 32, "rows must split evenly over the waves");
+  __shared__ __attribute__((aligned(1024))) uint8_t st[NS * STAGE];
+  // all problems' tiles of a row tile are neighbours on one XCD (heads read the same rows); with more columns than
+  // rows the row tiles of one column tile are
+  const int lin = xcd_tile(blockIdx.x, mt * nt * n_probs);
+  if (lin >= mt * nt * n_probs) return;
+  const int pi = col_first ? lin / (mt * nt) : (lin / nt) % n_probs;
+  const int m0 = (col_first ? lin % mt : lin / (nt * n_probs)) * BM, n0 = (col_first ? (lin / mt) % nt : lin % nt) * BN;
+  const GemmProb P = probs[pi];
+  if (m0 >= P.M || n0 >= P.N) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int li = lane & 15, lg = lane >> 4;
+  auto swz = [](int k) { return BN == 32 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); };
+
+  const uint8_t* srcA[IA];
+  const uint8_t* srcB[IB];
+  int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
+#pragma unroll
+  for (int t = 0; t < IA; t++) {
+    const int m = min(m0 + 8 * (wave * IA + t) + (lane >> 3), P.M - 1);
+    int inst, row; split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
+    srcA[t] = (const uint8_t*)((const float*)P.A + (long long)inst * P.a_is + (long long)row * P.lda) + ((lane & 7) ^ (lane >> 3)) * 16;
+  }
+#pragma unroll
+  for (int t = 0; t < IB; t++) {
+    const int f = WV4 ? ((wave * IB + t) * 64 + lane) * 4 : (wave * IB + t) * 64 + lane;      // word of the W slab in LDS
+    const int k = f / BN, c = (f % BN) >> 2;
+    const int n = n0 + ((c ^ swz(k)) << 2) + (f & 3);
+    srcB[t] = (const uint8_t*)((const float*)P.W + (long long)k * P.ldw + min(n, P.N - (WV4 ? 4 : 1)));
+  }
+  const long long stepB = 32LL * P.ldw * 4;
+  const uint32_t lds0 = lds_addr_of(st);
+  auto issue = [&](int stage) {
+    const uint32_t ba = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + wave * IA * 1024);
+    const uint32_t bb = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + ABYTES + wave * IB * (WV4 ? 1024 : 256));
+#pragma unroll
+    for (int t = 0; t < IA; t++) { slab_load16(srcA[t], ba + t * 1024); srcA[t] += 128; }
+#pragma unroll
+    for (int t = 0; t < IB; t++) {
+      if (WV4) slab_load16(srcB[t], bb + t * 1024); else lds_load4(srcB[t], bb + t * 256);
+      srcB[t] += stepB;
+    }
+  };
+  v4f acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+  int offB[TN];
+#pragma unroll
+  for (int j = 0; j < TN; j++) offB[j] = ABYTES + (lg * BN + ((((wn * TN + j) * 4 + (li >> 2)) ^ swz(lg)) << 2) + (li & 3)) * 4;
+  const int offA = (wm * TM * 16 + li) * 128 + lg * 4;
+  auto compute = [&](const uint8_t* s) {
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      float fa[TM], fb[TN];
+      const int sw = (q ^ (li & 7)) * 16;
+#pragma unroll
+      for (int i = 0; i < TM; i++) fa[i] = *(const float*)(s + offA + i * 2048 + sw);
+#pragma unroll
+      for (int j = 0; j < TN; j++) fb[j] = *(const float*)(s + offB[j] + q * (16 * BN));
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
+    }
+  };
+  const int nslab = P.K >> 5;
+#pragma unroll
+  for (int k = 0; k < NS - 1; k++) if (k < nslab) issue(k);
+  int sc = 0, sr = NS - 1;                              // stage of the slab to multiply, of the next request
+  for (int k = 0; k < nslab; k++) {
+    wait_slab_barrier<NS, IA + IB>(nslab - 1 - k);      // the slab has landed for everyone, the previous one's stage is free
+    if (k + NS - 1 < nslab) issue(sr);
+    compute(st + sc * STAGE);
+    sr = sc;
+    sc = (sc == NS - 1) ? 0 : sc + 1;
+  }
+  // 16-byte accesses where rows, strides and pointers allow them
+  const bool al = ((P.ldc | P.c_is | (P.add ? P.add_is : 0) | (P.aux ? P.aux_is : 0)) & 3) == 0 &&
+                  (((uintptr_t)P.C | (uintptr_t)P.add | (uintptr_t)P.aux | (uintptr_t)P.aux_sub) & 15) == 0;
+#pragma unroll
+  for (int i = 0; i < TM; i++) {
+    const int m = m0 + wm * TM * 16 + i * 16 + li;
+    if (m >= P.M) continue;
+    int inst, row; split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      const int n = n0 + wn * TN * 16 + j * 16 + lg * 4;
+      if (al && n + 3 < P.N) {
+        const float4 val = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        float4 v = val;
+        if (P.bias) { v.x += GCF(P.bias)[n]; v.y += GCF(P.bias)[n + 1]; v.z += GCF(P.bias)[n + 2]; v.w += GCF(P.bias)[n + 3]; }
+        if (P.act == 1) { v.x = gelu_tanh(v.x); v.y = gelu_tanh(v.y); v.z = gelu_tanh(v.z); v.w = gelu_tanh(v.w); }
+        const long long off = (long long)row * P.ldc + n;
+        if (P.add) { const float4 a = gload4(P.add + inst * P.add_is + off); v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w; }
+        gstore4(P.C + inst * P.c_is + off, v);
+        if (P.aux) {
+          float4 x = val;
+          if (P.aux_sub) { const float4 u = gload4(P.aux_sub + off); x.x -= u.x; x.y -= u.y; x.z -= u.z; x.w -= u.w; }
+          gstore4(P.aux + inst * P.aux_is + off, x);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++) if (n + r < P.N) epilogue_store(P, n + r, acc[i][j][r], 1.0f, 1.0f, inst, row);
+      }
+    }
+  }
+}
+
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool WV4>
+static hipError_t launch_f32_x(const GemmProb* probs, int n_probs, int M, int N, hipStream_t s) {
+  const int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16, mt = (M + BM - 1) / BM, nt = (N + BN - 1) / BN;
+  const long long tiles = (long long)mt * nt * n_probs;
+  if (tiles > 0x7ffffff0LL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemm_f32_x_k<WAVES_M, WAVES_N, TM, TN, WV4>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, probs,
+                     n_probs, mt, nt, n_probs == 1 && N > M ? 1 : 0);
+  return hipGetLastError();
+}
+// form: the smallest gemm32_form of the problems.  Tiles of 64 x 64 from two per compute unit on; below that smaller ones,
+// so that every unit has waves to switch between (us, 64 x 64 / 32 x 64 / 32 x 32; t = tiles of 64 x 64): 16384 x 2048 x 512
+// 312 / 385 / 439, t = 512 26 / 26 / 28, t = 384 43 / 38 / 41, t = 128 50 / 31 / 31, t = 48 26 / 16 / 12, t = 16 6.9 / 5.2 / 5.0.
+hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
+  const long long t = (long long)((max_M + 63) / 64) * ((max_N + 63) / 64) * n_probs;
+  if (form == 2) {
+    if (t >= 512) return launch_f32_x<2, 2, 2, 2, true>(probs, n_probs, max_M, max_N, s);
+    if (t >= 96) return launch_f32_x<2, 2, 1, 2, true>(probs, n_probs, max_M, max_N, s);
+    return launch_f32_x<2, 2, 1, 1, true>(probs, n_probs, max_M, max_N, s);
+  }
+  if (form == 1) return t >= 256 ? launch_f32_x<2, 2, 2, 2, false>(probs, n_probs, max_M, max_N, s)
+                                 : launch_f32_x<2, 2, 1, 1, false>(probs, n_probs, max_M, max_N, s);
   dim3 grid((max_N + 63) / 64, (max_M + 63) / 64, n_probs);
   hipLaunchKernelGGL(gemm_f32_k, grid, dim3(256), 0, s, probs);
   return hipGetLastError();

@@ -76,6 +76,13 @@ inline bool gemm8_prob_ok(const GemmProb& p) {
 }
 // For the fp32 GEMM the same struct is used with A = float [..][lda], W = float
 // [K][ldw] (row-major, K rows), ascale / wscale unused (null).
+// Which fp32 kernel may take a problem: 0 only the general one; 1 the one that stages slabs of 32 k through LDS 16 bytes of A
+// and a word of W at a time; 2 with 16 bytes of both.
+inline int gemm32_form(const GemmProb& p) {
+  auto a16 = [](const void* q) { return (((uintptr_t)q) & 15) == 0; };
+  if (p.K < 32 || p.K % 32 || p.lda % 4 || p.a_is % 4 || !a16(p.A) || p.N < 1) return 0;
+  return p.N % 4 == 0 && p.ldw % 4 == 0 && a16(p.W) ? 2 : 1;
+}
 
 struct CombineSrc {
   const float* src;  long long src_is;
@@ -151,7 +158,7 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
 // products, fp32 sums).
 // b16: the problems' operands are bfloat16 patterns (exact products on the bf16 matrix cores, fp32 sums)
 hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int exact, int b16, hipStream_t s);
-hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, hipStream_t s);
+hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s);
 hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const HeadAux* auxs, int M, int N, int H, int dh,
                               int exact, int b16, hipStream_t s);
 

@@ -1,0 +1,58 @@
+"""The fp32 products choose their tile by the number of tiles, and the output projections of a layer's fp32 heads are one
+launch.  Whatever the tile, an element is the same sum in the same order: a candidate scores the same bits in batches that
+take the smallest, the middle and the largest tile, and the scores are the oracle's.  An odd vocabulary takes the form that
+loads single words of the unembedding, heads of 16 (four of them: K = 64 in, 16 out) the kernel for K not a multiple of 32."""
+import os
+import sys
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+import synth                                        # noqa: E402
+from synth import ModelShape                        # noqa: E402
+from oracle.acdc import Acdc, MODE_ALL_FP32         # noqa: E402
+from oracle.model import Model as OModel            # noqa: E402
+from test_gpu_modes import F32_ATOL, F32_RTOL       # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+#                          heads d_head d_model d_mlp vocab  removed
+@pytest.mark.parametrize("H,dh,d,m,V,frac", [(8, 64, 512, 1024, 1031, 0.0), (8, 64, 512, 1024, 1028, 0.4), (3, 128, 320, 480, 515, 0.4),
+                                             (4, 16, 64, 100, 67, 0.4), (5, 32, 192, 160, 300, 0.0)])
+def test_fp32_scores_by_batch_and_against_the_oracle(H, dh, d, m, V, frac):
+    import paper_2510_23264_amd as P
+    B, S = 8, 16
+    shape = ModelShape(n_layers=2, n_heads=H, d_head=dh, d_model=d, d_mlp=m, vocab=V, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 11, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(11)
+    clean = rng.integers(0, V, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:5] = rng.integers(0, V, (B, 4))
+    om = OModel(shape, w)
+    g, oa = om.g, Acdc(om, clean, corrupt, MODE_ALL_FP32)
+    r = g.headin(0, 1, 2)                            # a value input of the first layer: every later layer is recomputed
+    r2 = g.headin(1, 0, 0)
+    state = np.zeros(g.n_edges(), np.uint8)
+    first = sum(g.n_upstream(q) for q in range(r2))
+    state[first:] = rng.random(g.n_edges() - first) < frac
+    out = []
+    for batch in (40, 6, 1):
+        gm = P.Model(shape, w, B, S, precision=P.ALL_FP32, max_batch_edges=batch)
+        try:
+            gm.clean_cache(clean, corrupt)
+            a = gm.eval_edges(r, np.zeros(40, np.int32))
+            gm.set_removed(state)
+            n = g.n_upstream(r2)
+            out.append(np.concatenate([a, gm.eval_edges(r2, np.resize(np.arange(n, dtype=np.int32), 40))]))
+            n_up = n
+        finally:
+            gm.close()
+    for got in out[1:]:
+        assert np.array_equal(got.view(np.uint32), out[0].view(np.uint32))
+    want = oa.kl_edge(r, 0)
+    assert abs(out[0][0] - want) <= F32_ATOL + F32_RTOL * abs(want)
+    if frac == 0.0:
+        for u in range(n_up):
+            want = oa.kl_edge(r2, u)
+            assert abs(out[0][40 + u] - want) <= F32_ATOL + F32_RTOL * abs(want), u
