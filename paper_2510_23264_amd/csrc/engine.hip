@@ -92,7 +92,7 @@ int w32_prefetch(pahq_model* M, int l, unsigned long long mask) {
 
 namespace {
 
-enum OpType { OP_BUILD, OP_GEMM8, OP_GEMM32, OP_ATTN, OP_COMBINE, OP_HIDQ, OP_LOGZ, OP_KL, OP_PATCH, OP_OPROJ, OP_KLRED, OP_PREF, OP_SWIGLU32, OP_LD, OP_W32ACQ, OP_W32REL };
+enum OpType { OP_BUILD, OP_GEMM8, OP_GEMM32, OP_ATTN, OP_COMBINE, OP_HIDQ, OP_LOGZ, OP_KL, OP_PATCH, OP_OPROJ, OP_KLRED, OP_PREF, OP_SWIGLU32, OP_LD, OP_GEMM32H, OP_W32ACQ, OP_W32REL };
 struct Op { OpType t; int i0, i1, i2, i3; void* p0; void* p1; double flops, bytes; unsigned long long u64, u64b; };
 
 struct Stream { float* p; long long is; };
@@ -203,12 +203,12 @@ struct Builder {
   void w32_begin(int l, unsigned long long mask) { if (M->w32.on && mask) { add_op(OP_W32ACQ, l, -1); ops.back().u64 = mask; } }
   void w32_end(int l, unsigned long long mask) { if (M->w32.on && mask) { add_op(OP_W32REL, l); ops.back().u64 = mask; } }
   // algorithmic work of the op just added (all instances)
-  void work_gemm(int pb) {
+  void work_gemm(int pb, int n = 0) {          // n: problems of the op (0: all from pb on)
     // flops of the contraction; bytes that must move: operand codes once (A: M x K, W: N x K; for
     // the fp32 GEMM four bytes per element), row scales, the fp32 result, and the residual /
     // second-output tiles when the problem has them
     double f = 0, by = 0;
-    for (size_t i = pb; i < probs.size(); i++) {
+    for (size_t i = pb; i < (n ? (size_t)pb + n : probs.size()); i++) {
       const GemmProb& q = probs[i];
       const double M_ = q.M, N_ = q.N, K_ = q.k_real, eb = q.ascale ? (q.b16 ? 2.0 : 1.0) : 4.0;
       f += 2.0 * M_ * N_ * K_;
@@ -668,27 +668,44 @@ struct Builder {
       if (hx[h].dst) hx[h].dst += lo;
       if (hx[h].dst && !((fmask >> h) & 1ull)) any_aux = true;
     }
+    bool fused = false;                               // the fp32 heads' launch has updated the stream
     if (nf && !prefix) {
-      // the fp32 heads' projections, one fp32 GEMM each, summed in ascending head order into one tile (the
+      // the fp32 heads' projections, summed in ascending head order into one tile (the
       // fused kernel, or the plain stream update when every head is fp32, adds it); a head's own output goes,
       // where needed, to its cache tile / slot through the second output
-      int k = 0;
-      for (int h = 0; h < H; h++) {
+      const int pf = (int)probs.size();
+      bool one_launch = nf > 1 || off8 == all_heads;      // (a single head beside quantised ones is a plain product)
+      for (int h = 0, k = 0; h < H; h++) {
         if (!((fmask >> h) & 1ull)) continue;
-        int pf = (int)probs.size();
         GemmProb pp = prob8(M->zf32 + (long long)k * dh + last_off(last, (long long)nf * dh), inst_stride((long long)nf * dh), nf * dh, nullptr, 0, 0,
                             w32_ptr(M, 3, l, h), d, nullptr, 1, nullptr, M->headout + lo, inst_stride(d), d, 0, last, d, dh, dh);
         if (k > 0) { pp.add = M->headout + lo; pp.add_is = inst_stride(d); }
         else if (deadsum) { pp.add = deadsum + lo; pp.add_is = 0; }          // the chain starts from the dead heads' stand-ins
         pp.aux = hx[h].dst; pp.aux_is = hx[h].dst_is; pp.aux_sub = hx[h].sub;
+        one_launch = one_launch && gemm32_heads_ok(pp);
         probs.push_back(pp);
-        add_op(OP_GEMM32, pf, 1, rows(last), d); work_gemm(pf);
         k++;
       }
+      if (one_launch) {
+        // one launch for all of them, and where every head is fp32 the stream update with it
+        fused = off8 == all_heads;
+        for (int k = 0; k < nf; k++) {
+          GemmProb& pp = probs[pf + k];
+          pp.chained = 1;
+          if (k > 0) { pp.add = nullptr; pp.add_is = 0; }
+          if (fused) { pp.C = nxt.p + lo; pp.c_is = nxt.is; }
+        }
+        add_op(OP_GEMM32H, pf, nf, rows(last), d, fused ? (void*)(run.p + lo) : nullptr, fused ? (void*)(M->b_O + (long long)l * d) : nullptr);
+        ops.back().u64 = (unsigned long long)run.is;
+        work_gemm(pf);
+      } else
+        for (int k = 0; k < nf; k++) { add_op(OP_GEMM32, pf + k, 1, rows(last), d); work_gemm(pf + k, 1); }
       w32_end(l, fmask);
       od.extra = M->headout + lo; od.extra_is = inst_stride(d);
     }
-    if (off8 == all_heads && nf && !prefix) {
+    if (fused) {
+      // next = run + b_O + (sum of the fp32 heads): done
+    } else if (off8 == all_heads && nf && !prefix) {
       // nothing is quantised in this layer: next = run + b_O + (sum of the fp32 heads)
       CombineDesc cd; memset(&cd, 0, sizeof(cd));
       cd.run_in = run.p; cd.run_in_is = run.is; cd.run_out = nxt.p; cd.run_out_is = nxt.is;
@@ -905,7 +922,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // then find a tile's rows without walking over instances (a 256-row tile crosses five of them with 50 rows each).
 void join_instances(GemmProb& p) {
   auto joined = [&](long long is, long long ld) { return is == p.rpi * ld; };
-  if (p.aux || p.kl_part || !joined(p.a_is, p.lda) || (p.ascale && !joined(p.as_is, p.as_stride)) || !joined(p.c_is, p.ldc) ||
+  if (p.aux || p.kl_part || p.chained || !joined(p.a_is, p.lda) || (p.ascale && !joined(p.as_is, p.as_stride)) || !joined(p.c_is, p.ldc) ||
       (p.add && !joined(p.add_is, p.ldc)) || (long long)p.M * p.ldc >= (1ll << 31)) return;
   p.rpi = p.M; p.rp0 = 0;
 }
@@ -985,7 +1002,7 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
   // ---- launch
   const int n = a.n, T = M->T, B = M->B, S = M->S, d = M->d;
   hipStream_t st = M->stream;
-  static const int cls_of[] = {0, 2, 3, 4, 5, 6, 7, 8, 1, 9, 8, 7, 6, 8};   // OpType -> kernel class
+  static const int cls_of[] = {0, 2, 3, 4, 5, 6, 7, 8, 1, 9, 8, 7, 6, 8, 3};   // OpType -> kernel class
   const bool prof_pass = M->prof_on && (M->prof_pass++ % M->prof_every) == 0;
   for (const Op& o : b.ops) {
     int pair = -1;
@@ -1050,6 +1067,9 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
         HIPCHK(launch_gemm_f32(d_probs + o.i0, o.i1, o.i2, o.i3, form, st));
         break;
       }
+      case OP_GEMM32H:
+        HIPCHK(launch_gemm_f32_heads(d_probs + o.i0, o.i1, o.i2, o.i3, (const float*)o.p0, (long long)o.u64, (const float*)o.p1, st));
+        break;
       case OP_ATTN: {
         // o.i2 instances (0: all of the pass)
         HIPCHK(launch_attention(b.asrcs[o.i0], M->zcodes, M->zscale, M->zf32, o.u64, o.u64b, o.i2 ? o.i2 : n, B, S, M->H,

@@ -1093,6 +1093,148 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const Gemm
   }
 }
 
+// Output projections of the fp32 heads of a layer, summed:
+//   C[m] = (run_in[m] + bias) + (((add[m] + z_0 W_0) + z_1 W_1) + ...)        (run_in null: the bracket alone)
+// probs[h] is head h's projection (A = the head's columns of the rows of all heads, which lie side by side: probs[0].A and
+// 4 K bytes per head); rows, C and `add` are probs[0]'s, W and the second output (aux = z_h W_h - aux_sub) each head's own.
+// One launch per head moved the running sum through memory H times: with eight heads of 64 and 16384 rows of 512 the heads'
+// 25 us each were 20 us of traffic, and at 1024 rows 14 us each were latency.  Here the sum stays in registers.
+// Every head's product starts from zero and is then added, ascending: the bits of the launches one by one.
+// Slabs, operand layout and tiles as in gemm_f32_x_k; the slabs of all heads are one stream.
+template <int TM, int TN>
+__global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, int n_heads, int mt, int nt, const float* run_in,
+                                                         long long run_is, const float* bias) {
+  constexpr int BM = 32 * TM, BN = 32 * TN, IA = BM / 32, IB = BN / 32;
+  constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
+  static_assert(BN == 64 || BN == 32, "swz below");
+  __shared__ __attribute__((aligned(1024))) uint8_t st[2 * STAGE];
+  const int lin = xcd_tile(blockIdx.x, mt * nt);
+  if (lin >= mt * nt) return;
+  const int m0 = (lin / nt) * BM, n0 = (lin % nt) * BN;
+  const GemmProb P = probs[0];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int li = lane & 15, lg = lane >> 4;
+  auto swz = [](int k) { return BN == 32 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); };
+  int i0, r0; row_origin(m0, P.rpi, P.rp0, i0, r0);
+  const uint8_t* srcA[IA];
+  long long offW[IB];
+#pragma unroll
+  for (int t = 0; t < IA; t++) {
+    const int m = min(m0 + 8 * (wave * IA + t) + (lane >> 3), P.M - 1);
+    int inst, row; split_row(i0, r0, m - m0, P.rpi, P.rp0, inst, row);
+    srcA[t] = (const uint8_t*)((const float*)P.A + (long long)inst * P.a_is + (long long)row * P.lda) + ((lane & 7) ^ (lane >> 3)) * 16;
+  }
+#pragma unroll
+  for (int t = 0; t < IB; t++) {
+    const int f = ((wave * IB + t) * 64 + lane) * 4, k = f / BN, c = (f % BN) >> 2;
+    offW[t] = (long long)k * P.ldw + min(n0 + ((c ^ swz(k)) << 2), P.N - 4);
+  }
+  const int spk = P.K >> 5, nslab = spk * n_heads;      // slabs of a head, of all
+  const uint32_t lds0 = lds_addr_of(st);
+  int rh = 0, rk = 0;                                   // head and slab of the next request
+  const float* rw = (const float*)P.W;
+  auto issue = [&](int stage) {
+    const uint32_t ba = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + wave * IA * 1024);
+    const uint32_t bb = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + ABYTES + wave * IB * 1024);
+#pragma unroll
+    for (int t = 0; t < IA; t++) { slab_load16(srcA[t], ba + t * 1024); srcA[t] += 128; }
+#pragma unroll
+    for (int t = 0; t < IB; t++) slab_load16((const uint8_t*)(rw + offW[t]), bb + t * 1024);
+    rw += 32LL * P.ldw;
+    if (++rk == spk) { rk = 0; rh++; if (rh < n_heads) rw = (const float*)probs[rh].W; }
+  };
+  int offB[TN];
+#pragma unroll
+  for (int j = 0; j < TN; j++) offB[j] = ABYTES + (lg * BN + ((((wn * TN + j) * 4 + (li >> 2)) ^ swz(lg)) << 2) + (li & 3)) * 4;
+  const int offA = (wm * TM * 16 + li) * 128 + lg * 4;
+  v4f acc[TM][TN], tot[TM][TN];
+  // what a lane adds to: its row and the columns n .. n + 3 of every 16 x 16 block
+  int inst[TM], row[TM];
+  bool on[TM];
+#pragma unroll
+  for (int i = 0; i < TM; i++) {
+    const int m = m0 + wm * TM * 16 + i * 16 + li;
+    on[i] = m < P.M;
+    split_row(i0, r0, min(m, P.M - 1) - m0, P.rpi, P.rp0, inst[i], row[i]);
+  }
+  const int nb = n0 + wn * TN * 16 + lg * 4;
+  issue(0);
+  int slab = 0;
+  for (int h = 0; h < n_heads; h++) {
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < spk; k++, slab++) {
+      wait_vm_barrier<0>();                             // the slab has landed for everyone, the other stage is free
+      if (slab + 1 < nslab) issue((slab + 1) & 1);
+      const uint8_t* s = st + (slab & 1) * STAGE;
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        float fa[TM], fb[TN];
+        const int sw = (q ^ (li & 7)) * 16;
+#pragma unroll
+        for (int i = 0; i < TM; i++) fa[i] = *(const float*)(s + offA + i * 2048 + sw);
+#pragma unroll
+        for (int j = 0; j < TN; j++) fb[j] = *(const float*)(s + offB[j] + q * (16 * BN));
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
+      }
+    }
+    float* const aux = probs[h].aux;
+    const float* const sub = probs[h].aux_sub;
+    const long long aux_is = probs[h].aux_is;
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        const int n = nb + j * 16;
+        const bool st_on = on[i] && n < P.N;
+        const long long off = (long long)row[i] * P.ldc + n;
+        if (h == 0) {
+          tot[i][j] = acc[i][j];
+          if (P.add && st_on) { const float4 a = gload4(P.add + inst[i] * P.add_is + off); tot[i][j] += (v4f){a.x, a.y, a.z, a.w}; }
+        } else tot[i][j] += acc[i][j];
+        if (aux && st_on) {
+          float4 x = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+          if (sub) { const float4 u = gload4(sub + off); x.x -= u.x; x.y -= u.y; x.z -= u.z; x.w -= u.w; }
+          gstore4(aux + inst[i] * aux_is + off, x);
+        }
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      const int n = nb + j * 16;
+      if (!on[i] || n >= P.N) continue;
+      const long long off = (long long)row[i] * P.ldc + n;
+      float4 v = make_float4(tot[i][j][0], tot[i][j][1], tot[i][j][2], tot[i][j][3]);
+      if (run_in) {
+        float4 r = gload4(run_in + inst[i] * run_is + off);
+        if (bias) { const float4 b = gload4(bias + n); r.x += b.x; r.y += b.y; r.z += b.z; r.w += b.w; }
+        v.x = r.x + v.x; v.y = r.y + v.y; v.z = r.z + v.z; v.w = r.w + v.w;
+      }
+      gstore4(P.C + inst[i] * P.c_is + off, v);
+    }
+}
+hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int N, const float* run_in, long long run_is,
+                                 const float* bias, hipStream_t s) {
+  if (n_heads == 0 || M == 0 || N == 0) return hipSuccess;
+  auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  auto grid = [](long long t) { return dim3((unsigned)((t + 7) / 8 * 8)); };
+  if (tiles(32, 32) > 0x7ffffff0LL) return hipErrorInvalidValue;
+  // the tile by the same counts as in launch_gemm_f32
+  if (tiles(64, 64) >= 512) hipLaunchKernelGGL((gemm_f32_heads_k<2, 2>), grid(tiles(64, 64)), dim3(256), 0, s, probs, n_heads, (M + 63) / 64, (N + 63) / 64, run_in, run_is, bias);
+  else if (tiles(64, 64) >= 96) hipLaunchKernelGGL((gemm_f32_heads_k<1, 2>), grid(tiles(32, 64)), dim3(256), 0, s, probs, n_heads, (M + 31) / 32, (N + 63) / 64, run_in, run_is, bias);
+  else hipLaunchKernelGGL((gemm_f32_heads_k<1, 1>), grid(tiles(32, 32)), dim3(256), 0, s, probs, n_heads, (M + 31) / 32, (N + 31) / 32, run_in, run_is, bias);
+  return hipGetLastError();
+}
+
 template <int WAVES_M, int WAVES_N, int TM, int TN, bool WV4>
 static hipError_t launch_f32_x(const GemmProb* probs, int n_probs, int M, int N, hipStream_t s) {
   const int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16, mt = (M + BM - 1) / BM, nt = (N + BN - 1) / BN;

@@ -56,6 +56,7 @@ struct GemmProb {
   const float* kl_ref; const double* kl_ref_logz; float* kl_part; int kl_npart;
   int b16;             // operands are bfloat16 patterns, two bytes per element (lda, ldw, K stay in bytes), not e4m3 codes
   int rp0;             // rows of instance 0 in front of the rpi rows every instance has
+  int chained;         // a head of launch_gemm_f32_heads (which reads its rows' numbering from the first of them)
 };
 // Parts per row of the log-softmax / KL epilogue (128-column tiles, two wavefronts across).
 inline int kl_parts_per_row(int N) { return (N + 127) / 128 * 2; }
@@ -82,6 +83,13 @@ inline int gemm32_form(const GemmProb& p) {
   auto a16 = [](const void* q) { return (((uintptr_t)q) & 15) == 0; };
   if (p.K < 32 || p.K % 32 || p.lda % 4 || p.a_is % 4 || !a16(p.A) || p.N < 1) return 0;
   return p.N % 4 == 0 && p.ldw % 4 == 0 && a16(p.W) ? 2 : 1;
+}
+
+// What launch_gemm_f32_heads assumes of every head's problem; false: one launch per head.
+inline bool gemm32_heads_ok(const GemmProb& p) {
+  auto a16 = [](const void* q) { return (((uintptr_t)q) & 15) == 0; };
+  return gemm32_form(p) == 2 && p.ldc % 4 == 0 && p.c_is % 4 == 0 && p.add_is % 4 == 0 && p.aux_is % 4 == 0 &&
+         a16(p.C) && a16(p.add) && a16(p.aux) && a16(p.aux_sub) && !p.bias && p.act == 0;
 }
 
 struct CombineSrc {
@@ -159,6 +167,9 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
 // b16: the problems' operands are bfloat16 patterns (exact products on the bf16 matrix cores, fp32 sums)
 hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int exact, int b16, hipStream_t s);
 hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s);
+// C = (run_in + bias) + (add + sum over heads of A_h W_h), each head's own product to its aux (see gemm.hip); run_in may be null
+hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int N, const float* run_in, long long run_is,
+                                 const float* bias, hipStream_t s);
 hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const HeadAux* auxs, int M, int N, int H, int dh,
                               int exact, int b16, hipStream_t s);
 
