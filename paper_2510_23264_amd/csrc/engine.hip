@@ -163,18 +163,23 @@ struct Builder {
   // fills base / run / terms of a group from a receiver spec
   void fill_input(GroupDesc& gd, const RecvSpec* sp, int pw, Stream run) {
     gd.base = nullptr; gd.base_is = 0; gd.run = nullptr; gd.run_is = 0;
-    gd.term_begin = (int)terms.size(); gd.term_count = 0;
+    gd.term_begin = (int)terms.size(); gd.term_count = gd.term_shared = 0;
     int form = sp ? sp->form : 0;
     if (form == 2) { gd.base = corrupt_prefix_pi(pw); }
     else { gd.run = run.p; gd.run_is = run.is; }
     if (form != 0) {
       float sign = form == 1 ? -1.f : 1.f;
-      for (int s : sp->senders) {
-        Term t;
-        if (s < nstat) { t.p = M->delta + (long long)s * M->tile; t.inst_stride = 0; }
-        else { t.p = slot_ptr(s); t.inst_stride = slot_is(s); }
-        t.sign = sign; t.pad_ = 0;
-        terms.push_back(t);
+      // those every instance reads from the same tile first: the kernels add them in front of the others
+      for (int pass = 0; pass < 2; pass++) {
+        for (int s : sp->senders) {
+          Term t;
+          if (s < nstat) { t.p = M->delta + (long long)s * M->tile; t.inst_stride = 0; }
+          else { t.p = slot_ptr(s); t.inst_stride = slot_is(s); }
+          if ((t.inst_stride != 0) != (pass == 1)) continue;
+          t.sign = sign; t.pad_ = 0;
+          terms.push_back(t);
+        }
+        if (pass == 0) gd.term_shared = (int)terms.size() - gd.term_begin;
       }
       gd.term_count = (int)sp->senders.size();
     }
@@ -243,9 +248,7 @@ struct Builder {
       int shared_terms = 0;      // terms every instance reads from the same tile
       for (int i = g0; i < g0 + n_groups; i++) {
         if (i == patch_group) continue;
-        int c = 0;
-        for (int t = 0; t < groups[i].term_count; t++) c += terms[groups[i].term_begin + t].inst_stride == 0;
-        shared_terms = std::max(shared_terms, c);
+        shared_terms = std::max(shared_terms, groups[i].term_shared);
       }
       add_op(OP_BUILD, g0, n_groups, patch_group, shared_terms);
       work_build(g0, n_groups, patch_group);

@@ -20,13 +20,14 @@ struct Term {
 struct GroupDesc {
   const float* base;  long long base_is;
   const float* run;   long long run_is;
-  int term_begin, term_count;
+  int term_begin, term_count;                   // terms without instance stride first: term_shared of them
   const float* gain;  const float* offset;      // norm parameters [d]
   float* out_f32;     long long out_f32_is;     // normalised rows, stride d (may be null)
   uint8_t* out_codes; long long out_codes_is;   // e4m3 codes, row stride ldq (may be null)
   float* out_scale;   long long out_scale_is;   // one scale per row
   int last_only;      // 1: only the last position of each sequence (B rows per instance)
   int qbits;          // grid of the codes: 4 = 4-bit round-to-nearest, anything else E4M3 (device_util.h, q_encode)
+  int term_shared, pad_;
 };
 
 // One GEMM problem.  Rows are numbered 0 .. M-1 over all instances, so a launch needs no instance dimension and row

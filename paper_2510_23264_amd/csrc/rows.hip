@@ -131,6 +131,28 @@ __device__ __forceinline__ void row_axpy(float (&x)[MAXE], float sign, const flo
     for (int j = 0; j < MAXE; j++) if (j < E) x[j] += sign * p[lane + 64 * j];
   }
 }
+// x += sign * p for n terms in their order.  The rows of up to four are loaded before the first is added: one at a time, a
+// wave that gathers tens of them waits a memory latency for each (and, with shared and other terms mixed, for the
+// descriptors of those it skips: GPT-2-small graph with 90 % of the edges gone 43.1 -> 39.3 ms).
+template <int MAXE, bool VEC>
+__device__ __forceinline__ void row_add_terms(float (&x)[MAXE], const Term* tt, int n, int inst, long long src, int E, int lane) {
+  constexpr int U = MAXE <= 16 ? 4 : MAXE <= 32 ? 2 : 1;
+  int t = 0;
+  for (; t + U <= n; t += U) {
+    float v[U][MAXE];
+    float sign[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      sign[u] = tt[t + u].sign;
+      row_load<MAXE, VEC>(v[u], tt[t + u].p + inst * tt[t + u].inst_stride + src, E, lane);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int j = 0; j < MAXE; j++) if (j < E) x[j] += sign[u] * v[u][j];
+  }
+  for (; t < n; t++) row_axpy<MAXE, VEC>(x, tt[t].sign, tt[t].p + inst * tt[t].inst_stride + src, E, lane);
+}
 // y = a - p
 template <int MAXE, bool VEC>
 __device__ __forceinline__ void row_sub(float (&y)[MAXE], const float (&a)[MAXE], const float* p, int E, int lane) {
@@ -275,19 +297,10 @@ __global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, c
   const Term* tt = terms + g.term_begin;
   const bool base_shared = g.base && g.base_is == 0;
   if (base_shared) row_load<MAXE, VEC>(x, g.base + src, E, lane);
-  int n_dyn = 0;
-  for (int t = 0; t < g.term_count; t++) {
-    Term tm = tt[t];
-    if (tm.inst_stride == 0) row_axpy<MAXE, VEC>(x, tm.sign, tm.p + src, E, lane);
-    else n_dyn++;
-  }
+  row_add_terms<MAXE, VEC>(x, tt, g.term_shared, 0, src, E, lane);
   if (g.base && !base_shared) row_axpy<MAXE, VEC>(x, 1.0f, g.base + inst * g.base_is + src, E, lane);
   if (g.run) row_axpy<MAXE, VEC>(x, 1.0f, g.run + inst * g.run_is + src, E, lane);
-  if (n_dyn)
-    for (int t = 0; t < g.term_count; t++) {
-      Term tm = tt[t];
-      if (tm.inst_stride != 0) row_axpy<MAXE, VEC>(x, tm.sign, tm.p + inst * tm.inst_stride + src, E, lane);
-    }
+  row_add_terms<MAXE, VEC>(x, tt + g.term_shared, g.term_count - g.term_shared, inst, src, E, lane);
   norm_row<MAXE, VEC>(x, E, d, lane, norm_kind, eps, g.gain, g.offset);
   emit_row<MAXE, VEC>(x, E, d, lane, g, inst, row, ldq);
 }
@@ -322,12 +335,7 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
 #pragma unroll
   for (int j = 0; j < MAXE; j++) x0[j] = 0.f;
   if (base_shared) row_load<MAXE, VEC>(x0, g.base + src, E, lane);
-  int n_dyn = 0;
-  for (int t = 0; t < g.term_count; t++) {
-    Term tm = tt[t];
-    if (tm.inst_stride == 0) row_axpy<MAXE, VEC>(x0, tm.sign, tm.p + src, E, lane);
-    else n_dyn++;
-  }
+  row_add_terms<MAXE, VEC>(x0, tt, g.term_shared, 0, src, E, lane);
   float gn[MAXE], of[MAXE];               // read once for the chunk, not once per instance
   norm_params_load<MAXE, VEC>(gn, of, E, lane, norm_kind, g.gain, g.offset);
   const int i_end = once ? 1 : min(n_inst, ((int)blockIdx.z + 1) * chunk);
@@ -337,11 +345,7 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
     for (int j = 0; j < MAXE; j++) x[j] = x0[j];
     if (g.base && !base_shared) row_axpy<MAXE, VEC>(x, 1.0f, g.base + inst * g.base_is + src, E, lane);
     if (g.run) row_axpy<MAXE, VEC>(x, 1.0f, g.run + inst * g.run_is + src, E, lane);
-    if (n_dyn)
-      for (int t = 0; t < g.term_count; t++) {
-        Term tm = tt[t];
-        if (tm.inst_stride != 0) row_axpy<MAXE, VEC>(x, tm.sign, tm.p + inst * tm.inst_stride + src, E, lane);
-      }
+    row_add_terms<MAXE, VEC>(x, tt + g.term_shared, g.term_count - g.term_shared, inst, src, E, lane);
     norm_row<MAXE, VEC>(x, E, d, lane, norm_kind, eps, gn, of);
     emit_row<MAXE, VEC>(x, E, d, lane, g, inst, row, ldq);
   }
