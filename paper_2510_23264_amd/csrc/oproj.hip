@@ -200,13 +200,15 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
 // instead of counting.
 // DH: bytes of a head's row of codes (64 or 128).  B16: they are bfloat16 patterns (d_head = DH / 2), multiplied
 // without conversion by V_MFMA_F32_16X16X32_BF16, one step per 16-byte operand read; everything else is the same.
+// BM: rows of a tile, 128 or 32 (four wavefronts of 16 x 32; for problems of few tiles, see launch_oproj_fused).
 constexpr int OPX_STAGES = 3;
-constexpr int OPX_OPER = (128 + 64) * 128;                 // operand bytes of a stage
-constexpr int OPX_STAGE = OPX_OPER + 1024;                 // + row scales [heads of the slab][128]
-constexpr int OPX_LDS = OPX_STAGES * OPX_STAGE + 256;      // + weight scales [64]
-template <int DH, bool B16 = false>
-__global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int di, const HeadAux* auxs) {
-  constexpr int BM = 128, BN = 64, TM = 2, TN = 2, NI = 3, NS = OPX_STAGES, STAGE = OPX_STAGE;
+constexpr int opx_oper(int BM) { return (BM + 64) * 128; }                                     // operand bytes of a stage
+constexpr int opx_stage(int BM) { return opx_oper(BM) + 1024; }                                // + row scales [heads of the slab][BM]
+constexpr int opx_lds(int BM) { return OPX_STAGES * opx_stage(BM) + 256; }                     // + weight scales [64]
+template <int DH, bool B16, int BM>
+__global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const OprojDesc* descs, int di, const HeadAux* auxs) {
+  constexpr int BN = 64, TM = BM == 128 ? 2 : 1, TN = 2, NI = 3, NS = OPX_STAGES, STAGE = opx_stage(BM);
+  static_assert(BM == 128 || BM == 32, "waves: BM / (16 TM) x 2, three loads each");
   constexpr int HPS = 128 / DH;            // heads per slab
   constexpr int CPH = 8 / HPS;             // 16-byte chunks per head
   static_assert(NI + 1 == 4, "four loads per slab and wave: the wait counts below assume it");
@@ -244,12 +246,13 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
     }
   }
   // row scales of a slab: entry [q][r] (head q of the slab, tile row r) is lane's if 64 wave + lane = 128 q + r;
-  // waves 4 .. 7 repeat what waves 0 .. 3 fetch (so that all waves count alike), and with one head per slab waves 2
-  // and 3 repeat rows 0 .. 127 into the unused half
+  // waves past the last entry repeat what earlier ones fetch (so that all waves count alike), and with one head per slab
+  // the entries behind the first BM repeat the rows into the unused part
   const float* zsrc;
   {
-    const int q = (HPS == 2) ? ((wave & 3) >> 1) : 0;
-    int inst, row; row_origin(min(m0 + (wave & 1) * 64 + lane, D.M - 1), D.rpi, D.rp0, inst, row);
+    const int e = (wave & 3) * 64 + lane;
+    const int q = (HPS == 2) ? (e / BM) & 1 : 0;
+    int inst, row; row_origin(min(m0 + e % BM, D.M - 1), D.rpi, D.rp0, inst, row);
     zsrc = D.zs + (long long)inst * D.zs_is + (long long)row * D.H + q;
   }
   int si = 0;                              // stage of the next request
@@ -258,17 +261,17 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
     const uint32_t base = __builtin_amdgcn_readfirstlane(st + wave * NI * 1024);
 #pragma unroll
     for (int t = 0; t < NI; t++) { slab_load16(src[t], base + t * 1024); src[t] += stride[t]; }
-    lds_load4(zsrc, __builtin_amdgcn_readfirstlane(st + OPX_OPER + (wave & 3) * 256));
+    lds_load4(zsrc, __builtin_amdgcn_readfirstlane(st + opx_oper(BM) + (wave & 3) * 256));
     zsrc += HPS;
     si = (si == NS - 1) ? 0 : si + 1;
   };
-  const int mbase = m0 + wm * 32, nbase = n0 + wn * 32;
+  const int mbase = m0 + wm * TM * 16, nbase = n0 + wn * 32;
   // weight scales of all heads, the same 64 dwords from every wave (so that all waves count alike)
   lds_load4(D.ws + min(lane, D.H - 1), __builtin_amdgcn_readfirstlane(lds0 + NS * STAGE));
   issue();
   if (1 < nslab) issue();
 
-  const int offA = (wm * 32 + li) * 128, offB = (BM + wn * 32 + li) * 128;
+  const int offA = (wm * TM * 16 + li) * 128, offB = (BM + wn * 32 + li) * 128;
   const int sw0 = (lg ^ (li & 7)) * 16, sw1 = ((4 + lg) ^ (li & 7)) * 16;
   v4f tot[TM][TN], acc[TM][TN];
 #pragma unroll
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
   auto compute = [&](auto aux_tag, const uint8_t* st, int s) {
     const uint8_t* sA = st + offA;
     const uint8_t* sB = st + offB;
-    const float* zrow = (const float*)(st + OPX_OPER) + wm * 32 + li;
+    const float* zrow = (const float*)(st + opx_oper(BM)) + wm * TM * 16 + li;
     float zsc[HPS][TM];                      // requested now, used after the MFMAs of the half
 #pragma unroll
     for (int q = 0; q < HPS; q++)
@@ -410,18 +413,29 @@ __global__ __launch_bounds__(512, 4) void oproj_x_k(const OprojDesc* descs, int 
 
 // The kernel's 75 KB of dynamic LDS need the attribute, which belongs to the kernel's code object on one device:
 // set once per device and instantiation (atomically: models on several streams or host threads may launch at once).
-template <int DH, bool B16>
-static hipError_t launch_oproj_x(dim3 grid, hipStream_t s, const OprojDesc* descs, int desc_index, const HeadAux* auxs) {
-  static std::atomic<bool> attr_set[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (!attr_set[dev].load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)oproj_x_k<DH, B16>, hipFuncAttributeMaxDynamicSharedMemorySize, OPX_LDS);
-    if (e != hipSuccess) return e;
-    attr_set[dev].store(true, std::memory_order_release);
+template <int DH, bool B16, int BM>
+static hipError_t launch_oproj_bm(int M, int N, hipStream_t s, const OprojDesc* descs, int desc_index, const HeadAux* auxs) {
+  if (BM == 128) {
+    static std::atomic<bool> attr_set[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!attr_set[dev].load(std::memory_order_acquire)) {
+      hipError_t e = hipFuncSetAttribute((const void*)oproj_x_k<DH, B16, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, opx_lds(BM));
+      if (e != hipSuccess) return e;
+      attr_set[dev].store(true, std::memory_order_release);
+    }
   }
-  hipLaunchKernelGGL((oproj_x_k<DH, B16>), grid, dim3(512), OPX_LDS, s, descs, desc_index, auxs);
+  const int tiles = ((M + BM - 1) / BM) * ((N + 63) / 64);
+  hipLaunchKernelGGL((oproj_x_k<DH, B16, BM>), dim3((tiles + 7) / 8 * 8), dim3(BM == 128 ? 512 : 256), opx_lds(BM), s, descs, desc_index, auxs);
   return hipGetLastError();
+}
+// A tile is a chain of dependent steps whatever its height; with fewer 128-row tiles than compute units the chip waits for
+// that chain with units idle, and tiles of 32 rows make the chain's steps shorter (1024 rows of 512, 64 tiles against 256:
+// four-layer circuit 2.28 -> 2.16 ms, its sweep 21.8 -> 21.2 ms, both with four such layers a pass).
+template <int DH, bool B16>
+static hipError_t launch_oproj_x(int M, int N, hipStream_t s, const OprojDesc* descs, int desc_index, const HeadAux* auxs) {
+  if (((M + 127) / 128) * ((N + 63) / 64) < 256) return launch_oproj_bm<DH, B16, 32>(M, N, s, descs, desc_index, auxs);
+  return launch_oproj_bm<DH, B16, 128>(M, N, s, descs, desc_index, auxs);
 }
 
 hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const HeadAux* auxs, int M, int N, int H, int dh,
@@ -433,12 +447,12 @@ hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const Head
     // bfloat16 attention outputs: heads of 32 or 64 values (64 or 128 bytes)
     if (!exact || (dh != 32 && dh != 64) || N % 4 != 0 || H % (64 / dh) != 0) return hipErrorInvalidValue;
     if (H > 64) return hipErrorInvalidValue;
-    if (dh == 32) return launch_oproj_x<64, true>(grid, s, descs, desc_index, auxs);
-    return launch_oproj_x<128, true>(grid, s, descs, desc_index, auxs);
+    if (dh == 32) return launch_oproj_x<64, true>(M, N, s, descs, desc_index, auxs);
+    return launch_oproj_x<128, true>(M, N, s, descs, desc_index, auxs);
   }
   if (exact && (dh == 64 || dh == 128) && N % 4 == 0 && H % (128 / dh) == 0 && H <= 64) {
-    if (dh == 64) return launch_oproj_x<64, false>(grid, s, descs, desc_index, auxs);
-    return launch_oproj_x<128, false>(grid, s, descs, desc_index, auxs);
+    if (dh == 64) return launch_oproj_x<64, false>(M, N, s, descs, desc_index, auxs);
+    return launch_oproj_x<128, false>(M, N, s, descs, desc_index, auxs);
   } else if (exact) hipLaunchKernelGGL(oproj_fused_k<true>, grid, dim3(256), 0, s, descs, desc_index, auxs);
   else hipLaunchKernelGGL(oproj_fused_k<false>, grid, dim3(256), 0, s, descs, desc_index, auxs);
   return hipGetLastError();
