@@ -310,7 +310,11 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
   const int qrow = row_at(16 * a + i);                                 // tile row of query i of the tile
   auto writes = [&](int pos, int r) { return pos < S && (r >= src.rp0 || inst_o == 0) && (!src.last_only || pos == S - 1); };
   if (!__ballot(writes(16 * a + i, qrow))) return;                     // every row of the tile is instance 0's
-  // row `pos` of a matrix: this lane's CH consecutive columns, rotated when the model has rotary positions
+  // tile row of position 16 bk + i of every key tile: looked up once and together, not in front of each tile's loads
+  int rw[STM];
+#pragma unroll
+  for (int bk = 0; bk < STM; bk++) rw[bk] = bk < a ? row_at(16 * bk + i) : qrow;
+  // row `pos` of a matrix: this lane's CH consecutive columns
   auto load_rows = [&](float (&x)[CH], const float* base, long long is, int ld, int pos, int trow) {
     const float* row = at(base, is, ld, trow) + CH * g;
 #pragma unroll
@@ -319,6 +323,9 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
       if (pos < S) v = *(const float4*)(row + c);
       x[c] = v.x; x[c + 1] = v.y; x[c + 2] = v.z; x[c + 3] = v.w;
     }
+  };
+  // rotated when the model has rotary positions
+  auto rotate = [&](float (&x)[CH], int pos) {
     if (ROPE) {
 #pragma unroll
       for (int c = 0; c < CH; c++) {
@@ -330,20 +337,37 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
       }
     }
   };
-  float q[CH];
+  // values of key tile bk: vv[r][t] = V[key 16 bk + 4 g + r][16 t + i]
+  auto load_values = [&](float (&vv)[4][NT], int bk, int rows) {
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int kpos = 16 * bk + 4 * g + r;
+      const float* row = at(v0, src.v_is, src.v_ld, __shfl(rows, 4 * g + r, 64)) + i;
+#pragma unroll
+      for (int t = 0; t < NT; t++) vv[r][t] = (kpos < S) ? row[16 * t] : 0.f;
+    }
+  };
+  // Key tiles, then value tiles, one after the other; the next one's loads are issued in front of this one's products
+  // (edges of a four-layer model with prompts of 100 positions, where this kernel was a fifth of the time: 4.40 -> 3.70 ms), the first value tile's in
+  // front of the softmax.
+  float q[CH], kk[2][CH];
   load_rows(q, q0, src.q_is, src.q_ld, 16 * a + i, qrow);
+  load_rows(kk[0], k0, src.k_is, src.k_ld, i, rw[0]);
+  rotate(q, 16 * a + i);
   v4f_a sc[STM];
   const float scl = 1.0f / sqrtf((float)DH);
 #pragma unroll
   for (int bk = 0; bk < STM; bk++) {
     if (bk > a) continue;                                              // (wave-uniform)
-    float kk[CH];
-    load_rows(kk, k0, src.k_is, src.k_ld, 16 * bk + i, row_at(16 * bk + i));
+    if (bk + 1 < STM && bk + 1 <= a) load_rows(kk[(bk + 1) & 1], k0, src.k_is, src.k_ld, 16 * (bk + 1) + i, rw[bk + 1]);
+    rotate(kk[bk & 1], 16 * bk + i);
     v4f_a acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < CH; c++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[c], q[c], acc, 0, 0, 0);
+    for (int c = 0; c < CH; c++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[bk & 1][c], q[c], acc, 0, 0, 0);
     sc[bk] = acc;
   }
+  float vv[2][4][NT];
+  load_values(vv[0], 0, rw[0]);
   {
     const int qpos = 16 * a + i;
     float mx = -3.0e38f;
@@ -388,16 +412,11 @@ __global__ __launch_bounds__(256) void attention_qtile_k(AttnSrc src, uint8_t* z
 #pragma unroll
   for (int bk = 0; bk < STM; bk++) {
     if (bk > a) continue;
+    if (bk + 1 < STM && bk + 1 <= a) load_values(vv[(bk + 1) & 1], bk + 1, rw[bk + 1]);
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int kpos = 16 * bk + 4 * g + r;
-      const float* row = at(v0, src.v_is, src.v_ld, row_at(kpos)) + i;
+    for (int r = 0; r < 4; r++)
 #pragma unroll
-      for (int t = 0; t < NT; t++) {
-        const float vv = (kpos < S) ? row[16 * t] : 0.f;
-        z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sc[bk][r], vv, z[t], 0, 0, 0);
-      }
-    }
+      for (int t = 0; t < NT; t++) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sc[bk][r], vv[bk & 1][r][t], z[t], 0, 0, 0);
   }
   const bool f32 = (f32_mask >> h) & 1ull;
   const int f32_slot = __popcll(f32_mask & ((1ull << h) - 1ull)), f32_n = __popcll(f32_mask);
