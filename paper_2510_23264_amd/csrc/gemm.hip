@@ -3,21 +3,23 @@
 // gemm_fp8: val = (A_codes * W_codes^T) * row_scale * col_scale, then the
 //   epilogue of GemmProb (bias, GELU, residual add, second output).  Both
 //   operands are FP8 E4M3 codes with K contiguous, K padded with zero codes to
-//   a multiple of 128.  Two kernels:
+//   a multiple of 128.  The kernels:
 //
 //   gemm_x_k (exact sums, the default): codes are decoded to fp16 in registers
 //   (V_CVT_SCALEF32_PK_F16_FP8, exact) and multiplied by V_MFMA_F32_16X16X32_F16:
 //   exact products, fp32 sums.  Slabs of 128 K-bytes go from global memory
 //   straight into LDS (GLOBAL_LOAD_LDS_DWORDX4), two stages, one barrier per
 //   slab.  128 x 128 tile, four wavefronts of 64 x 64 (two decodes per MFMA; a
-//   smaller wave tile is bound by instruction issue, not by the matrix cores).
+//   smaller wave tile is bound by instruction issue, not by the matrix cores), or
+//   smaller ones where those would leave compute units idle (pick_tile).
+//   gemm_s_k: the smallest tiles, one per workgroup; gemm_p_k: the large problems.
 //
 //   gemm_fp8_k (PAHQ_MMA_FP8): V_MFMA_SCALE_F32_16X16X128_F8F6F4 with unit block
 //   scales; its adder keeps a fixed-point window below the largest product of
 //   an instruction (about 2^-13 of sum |a w| in the worst case).  128 x 64 tile,
 //   slabs staged through registers into LDS rows padded to 144 bytes.
 //
-//   In both, W is the first MFMA operand, so a lane owns one output row of a
+//   In these (not in gemm_p_k), W is the first MFMA operand, so a lane owns one output row of a
 //   16 x 16 tile and four consecutive columns (16-byte stores); row scales,
 //   column scales and the instance / row split are fetched before the K loop so
 //   that the epilogue does not wait on them.  The workgroup -> tile map gives
@@ -25,7 +27,7 @@
 //   innermost, so the A rows of a tile are fetched into one L2 only.
 //
 // gemm_f32: plain fp32 C = A * W (+ bias) with V_MFMA_F32_16X16X4_F32 (true
-//   fp32 multiply-accumulate) for the investigated head.
+//   fp32 multiply-accumulate) for the heads in fp32 and the all-fp32 mode.
 #include <algorithm>
 #include <atomic>
 #include "kernels.h"
