@@ -53,6 +53,8 @@ struct W32Cache {
 
 }  // namespace pahq
 
+constexpr long long SMALL_TILE = 1 << 16;      // elements of a tile pahq_get_sender_output puts in order on the host
+
 struct pahq_model {
   pahq_config cfg;
   pahq::GraphDims g;
@@ -76,6 +78,7 @@ struct pahq_model {
   int *tok_clean, *tok_corrupt, *send_dev;       // tokens in the order of a tile's rows
   int *row_of, *row_pos;                  // row of (sequence, position) in a tile [B * S]; position of a row [T]
   std::vector<int> row_of_host;           // host copy of row_of
+  std::vector<float> tile_host;           // a tile of up to SMALL_TILE elements on its way to the caller (otherwise empty)
   int rp0 = 0;                            // rows of a tile at which no candidate differs from another ("Rows of a pass" in engine.hip)
   float *clean, *corrupt, *delta;         // [Ns] tiles each (delta has one more, all zero)
   float *rc, *rx;                         // [2L+1] residual prefixes (entry 0 unused: it is sender 0's tile)

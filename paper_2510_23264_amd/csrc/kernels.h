@@ -161,6 +161,8 @@ hipError_t launch_ref_probs(const float* logits, const double* logz, double* psu
                             hipStream_t s);
 hipError_t launch_tile_lincomb(float* out, const float* base, const Term* terms, int n_terms, long long n_elem,
                                int base_last, hipStream_t s);
+// out[t] = row row_of[t] of the tile, t = 0 .. T-1 (d a multiple of 4)
+hipError_t launch_tile_rows(float* out, const float* tile, const int* row_of, int T, int d, hipStream_t s);
 hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long n_elem, hipStream_t s);
 
 // exact = 0: FP8 matrix-core instruction; exact = 1: codes decoded to fp16, fp16 matrix cores (exact

@@ -527,6 +527,18 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
   return hipGetLastError();
 }
 
+__global__ void tile_rows_k(float4* out, const float4* tile, const int* row_of, long long n4, int d4) {
+  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  out[i] = tile[(long long)row_of[i / d4] * d4 + i % d4];
+}
+hipError_t launch_tile_rows(float* out, const float* tile, const int* row_of, int T, int d, hipStream_t s) {
+  const long long n4 = (long long)T * d / 4;
+  hipLaunchKernelGGL(tile_rows_k, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, (float4*)out, (const float4*)tile,
+                     row_of, n4, d / 4);
+  return hipGetLastError();
+}
+
 // run_out = run_in + bias + sum_k src_k ; slot_k = src_k - sub_k
 // A thread owns four values of up to four instances.  A dead layer's stand-ins arrive as tens of sources that are
 // the same tile for every instance: each is loaded once for the thread's instances, four sources' loads are in
