@@ -1048,10 +1048,10 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
         for (int q = 0; q < o.i1; q++)
           if (!gemm8_prob_ok(b.probs[o.i0 + q]))      // the problem does not meet what the kernels assume
             return PAHQ_EINVAL;
-        if (o.p0) HIPCHK(launch_gemm_fp8_kl(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].b16, st));      // log-softmax / KL epilogue
+        if (o.p0) HIPCHK(launch_gemm_fp8_kl(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, b.probs[o.i0].b16, st));      // log-softmax / KL epilogue
         else {
           for (int q = 0; q < o.i1; q++) if (b.probs[o.i0 + q].kl_part || !b.probs[o.i0 + q].C) return PAHQ_EINVAL;
-          HIPCHK(launch_gemm_fp8(d_probs + o.i0, o.i1, o.i2, o.i3, M->cfg.mma == PAHQ_MMA_F16_EXACT, b.probs[o.i0].b16, st));
+          HIPCHK(launch_gemm_fp8(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, M->cfg.mma == PAHQ_MMA_F16_EXACT, b.probs[o.i0].b16, st));
         }
         break;
       case OP_KLRED:

@@ -784,24 +784,28 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_k(const GemmPr
 // against what is taken now): 1024 x 512 x 2048 23.8 -> 8.8, 1024 x 2048 x 512 12.4 -> 7.6, 3000 x 768 x 3072 35 -> 26,
 // 8192 x 512 x 2048 32 -> 25, 512 x 4096 x 11008 102 -> 61, 9000 x 2304 x 768 50 -> 45.  From five tiles of 256 x 128 per unit
 // on that kernel is the fastest whatever the remainder (50000 x 3072 x 768: 261 against 355 and more).
+// A smaller tile reads more per product, which the fit does not know: where the larger one's tiles fill the chip already
+// (r > 1) and rows of K are longer than 1024 bytes, it is taken only if it promises 6 %.  Of 38 such sizes that promise less
+// 26 took 4 % longer or more with it and 4 that much less (2178 x 3264 x 1408 in bfloat16 33 -> 44, 7143 x 2880 x 3840 177 ->
+// 192); with shorter rows it is the other way round (59 sizes: 4 and 33, 860 x 7104 x 128 0.95 of the larger tile's time).
 enum ExactTile { TILE_256x128, TILE_128x128, TILE_64x128, TILE_128x64, TILE_64x64, TILE_32x64 };
-static ExactTile pick_tile(int n_probs, int M, int N, bool b16, bool kl) {
+static ExactTile pick_tile(int n_probs, int M, int N, int K, bool b16, bool kl) {
   auto per_cu = [&](int bm, int bn) {
     const long long t = (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * n_probs;
     return (double)((t + 255) / 256);
   };
-  ExactTile best; double cost;
-  auto consider = [&](ExactTile t, double c) { if (c < cost) { best = t; cost = c; } };
-  if (N <= 64 && !kl) { best = TILE_128x64; cost = 0.37 + 0.48 * per_cu(128, 64); }
-  else {
-    best = TILE_128x128; cost = 0.5 + 0.85 * per_cu(128, 128);
-    if (!b16 && !kl && M >= 8192 && N >= 128) {
-      const double r = per_cu(256, 128);
-      if (r >= 5 || 0.1 + 1.8 * r <= cost) { best = TILE_256x128; cost = 0.1 + 1.8 * r; }
-      if (r >= 5) return best;
-    }
-    consider(TILE_64x128, 0.37 + 0.48 * per_cu(64, 128));
+  const bool narrow = N <= 64 && !kl;
+  ExactTile best = narrow ? TILE_128x64 : TILE_128x128;
+  double r = narrow ? per_cu(128, 64) : per_cu(128, 128);
+  double cost = narrow ? 0.37 + 0.48 * r : 0.5 + 0.85 * r;
+  if (!narrow && !b16 && !kl && M >= 8192 && N >= 128) {
+    const double rp = per_cu(256, 128);
+    if (rp >= 5) return TILE_256x128;
+    if (0.1 + 1.8 * rp <= cost) { best = TILE_256x128; r = rp; cost = 0.1 + 1.8 * rp; }
   }
+  if (r > 1 && K > 1024) cost *= 0.94;
+  auto consider = [&](ExactTile t, double c) { if (c < cost) { best = t; cost = c; } };
+  if (!narrow) consider(TILE_64x128, 0.37 + 0.48 * per_cu(64, 128));
   if (!kl) {           // (the parts of a row of the KL epilogue are 64 columns of one wave)
     consider(TILE_64x64, 0.3 + 0.26 * per_cu(64, 64));
     consider(TILE_32x64, 0.27 + 0.17 * per_cu(32, 64));
@@ -837,18 +841,18 @@ static hipError_t launch_tile(ExactTile t, const GemmProb* probs, int n_probs, i
 
 // Problems with the log-softmax / KL epilogue: the 128-column tilings that the number of parts per row
 // (kl_parts_per_row) is derived from.
-hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int b16, hipStream_t s) {
+hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int b16, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  const ExactTile t = pick_tile(n_probs, max_M, max_N, b16 != 0, true);
+  const ExactTile t = pick_tile(n_probs, max_M, max_N, K, b16 != 0, true);
   return b16 ? launch_tile<true>(t, probs, n_probs, max_M, max_N, s) : launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
 }
 
-hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int exact, int b16, hipStream_t s) {
+hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
   // bfloat16 operands: exact sums only (and no three-stage kernel)
-  if (b16) return exact ? launch_tile<true>(pick_tile(n_probs, max_M, max_N, true, false), probs, n_probs, max_M, max_N, s) : hipErrorInvalidValue;
+  if (b16) return exact ? launch_tile<true>(pick_tile(n_probs, max_M, max_N, K, true, false), probs, n_probs, max_M, max_N, s) : hipErrorInvalidValue;
   if (exact) {
-    const ExactTile t = pick_tile(n_probs, max_M, max_N, false, false);
+    const ExactTile t = pick_tile(n_probs, max_M, max_N, K, false, false);
     if (t == TILE_256x128) {
       // one 512-thread workgroup per compute unit, three 48 KB stages + 2 KB of scales
       const int lds_bytes = 3 * 384 * 128 + 2048;

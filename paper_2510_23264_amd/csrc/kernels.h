@@ -150,7 +150,7 @@ hipError_t launch_patch_build(const GroupDesc* g, const float* xv, const float* 
 hipError_t launch_xv_advance(float* xv, const float* delta0, long long delta_stride, const int* send, int k,
                              long long n_elem, hipStream_t s);
 // out = base + sum(terms) over n_elem elements (instance 0 of every term)
-hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int b16, hipStream_t s);
+hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int b16, hipStream_t s);
 // One wavefront per row of kl_part: logz[row] = log sum exp of the row from its parts (if logz != null);
 // row_kl[row] = a - (ref_logz[row % B] - logz) * ref_psum[row % B] with a = the sum of the parts' third values
 // (if row_kl != null); then kl[i] = mean over the B rows of instance i (if kl != null).
@@ -167,8 +167,9 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
 
 // exact = 0: FP8 matrix-core instruction; exact = 1: codes decoded to fp16, fp16 matrix cores (exact
 // products, fp32 sums).
-// b16: the problems' operands are bfloat16 patterns (exact products on the bf16 matrix cores, fp32 sums)
-hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int exact, int b16, hipStream_t s);
+// K: bytes of an operand row (for the choice of the tile).  b16: the problems' operands are bfloat16 patterns (exact products
+// on the bf16 matrix cores, fp32 sums)
+hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, hipStream_t s);
 hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s);
 // C = (run_in + bias) + (add + sum over heads of A_h W_h), each head's own product to its aux (see gemm.hip); run_in may be null
 hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int N, const float* run_in, long long run_is,

@@ -24,7 +24,8 @@ def model():
     (500, 384, (24500, 16300, 8150, 2040, 33, 1)),      # 128 x 128, 256 x 128, 64 x 128, 64 x 64, 32 x 64 twice
     (60, 256, (65500, 8200, 4000, 1)),                  # 128 x 64, 64 x 64, 32 x 64 twice
     (257, 128, (24500, 2000, 70)),
-    (130, 896, (3000, 300))])
+    (130, 896, (3000, 300)),
+    (960, 1536, (7500, 5100, 40))])                     # 128 x 128 (at K <= 1024 it would be 64 x 64), 64 x 128, 32 x 64
 def test_every_tile_gives_the_same_bits(model, n, k, rows):
     rng = np.random.default_rng(n + k)
     a, w = random_codes(rng, rows[0], k), random_codes(rng, n, k)
