@@ -431,10 +431,15 @@ static hipError_t launch_oproj_bm(int M, int N, hipStream_t s, const OprojDesc* 
 }
 // A tile is a chain of dependent steps whatever its height; with fewer 128-row tiles than compute units the chip waits for
 // that chain with units idle, and tiles of 32 rows make the chain's steps shorter (1024 rows of 512, 64 tiles against 256:
-// four-layer circuit 2.28 -> 2.16 ms, its sweep 21.8 -> 21.2 ms, both with four such layers a pass).
+// four-layer circuit 2.28 -> 2.16 ms, its sweep 21.8 -> 21.2 ms, both with four such layers a pass).  They also read the
+// weights four times as often, so near a full chip it depends on the slabs (128 bytes of codes) a chain has.  Time with 32
+// rows over that with 128, means over 1300 random sizes: up to 7 slabs 0.78 at 96 .. 127 tiles, 0.94 at 192 .. 255; from 8 on
+// 0.73 at 96 .. 127, 0.89 at 160 .. 191, 1.04 at 192 .. 255 (1.10 at the worst).  With bfloat16 rows, up to 3 slabs 0.84 and
+// 0.97; from 4 on 0.81, 0.93 and 1.07 (1.47), and from 12 on 1.00 at 128 .. 191 already (1.14).
 template <int DH, bool B16>
-static hipError_t launch_oproj_x(int M, int N, hipStream_t s, const OprojDesc* descs, int desc_index, const HeadAux* auxs) {
-  if (((M + 127) / 128) * ((N + 63) / 64) < 256) return launch_oproj_bm<DH, B16, 32>(M, N, s, descs, desc_index, auxs);
+static hipError_t launch_oproj_x(int M, int N, int H, hipStream_t s, const OprojDesc* descs, int desc_index, const HeadAux* auxs) {
+  const int slabs = H * DH / 128, few = slabs < (B16 ? 4 : 8) ? 256 : (!B16 || slabs < 12 ? 192 : 128);
+  if (((M + 127) / 128) * ((N + 63) / 64) < few) return launch_oproj_bm<DH, B16, 32>(M, N, s, descs, desc_index, auxs);
   return launch_oproj_bm<DH, B16, 128>(M, N, s, descs, desc_index, auxs);
 }
 
@@ -447,12 +452,12 @@ hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const Head
     // bfloat16 attention outputs: heads of 32 or 64 values (64 or 128 bytes)
     if (!exact || (dh != 32 && dh != 64) || N % 4 != 0 || H % (64 / dh) != 0) return hipErrorInvalidValue;
     if (H > 64) return hipErrorInvalidValue;
-    if (dh == 32) return launch_oproj_x<64, true>(M, N, s, descs, desc_index, auxs);
-    return launch_oproj_x<128, true>(M, N, s, descs, desc_index, auxs);
+    if (dh == 32) return launch_oproj_x<64, true>(M, N, H, s, descs, desc_index, auxs);
+    return launch_oproj_x<128, true>(M, N, H, s, descs, desc_index, auxs);
   }
   if (exact && (dh == 64 || dh == 128) && N % 4 == 0 && H % (128 / dh) == 0 && H <= 64) {
-    if (dh == 64) return launch_oproj_x<64, false>(M, N, s, descs, desc_index, auxs);
-    return launch_oproj_x<128, false>(M, N, s, descs, desc_index, auxs);
+    if (dh == 64) return launch_oproj_x<64, false>(M, N, H, s, descs, desc_index, auxs);
+    return launch_oproj_x<128, false>(M, N, H, s, descs, desc_index, auxs);
   } else if (exact) hipLaunchKernelGGL(oproj_fused_k<true>, grid, dim3(256), 0, s, descs, desc_index, auxs);
   else hipLaunchKernelGGL(oproj_fused_k<false>, grid, dim3(256), 0, s, descs, desc_index, auxs);
   return hipGetLastError();
