@@ -245,12 +245,14 @@ struct Builder {
   }
   void add_build(int g0, int n_groups, int patch_group) {
     if (n_groups - (patch_group >= 0 ? 1 : 0) > 0) {
-      int shared_terms = 0;      // terms every instance reads from the same tile
+      int shared_terms = 0, many = 0;      // terms every instance reads from the same tile; terms of one kind
       for (int i = g0; i < g0 + n_groups; i++) {
         if (i == patch_group) continue;
         shared_terms = std::max(shared_terms, groups[i].term_shared);
+        many = std::max(many, std::max(groups[i].term_shared, groups[i].term_count - groups[i].term_shared));
       }
       add_op(OP_BUILD, g0, n_groups, patch_group, shared_terms);
+      ops.back().u64b = (unsigned long long)many;
       work_build(g0, n_groups, patch_group);
     }
     if (patch_group >= 0) add_patch(patch_group);
@@ -1031,12 +1033,12 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
         // the patched receiver's group (if any) is built by the edge-batched patch kernel
         int pg = o.i2;
         if (pg < 0) {
-          HIPCHK(launch_build_inputs(d_groups + o.i0, o.i1, d_terms, o.u64 ? 1 : n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
+          HIPCHK(launch_build_inputs(d_groups + o.i0, o.i1, d_terms, o.u64 ? 1 : n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, (int)o.u64b, st));
         } else {
           if (pg > o.i0)
-            HIPCHK(launch_build_inputs(d_groups + o.i0, pg - o.i0, d_terms, n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
+            HIPCHK(launch_build_inputs(d_groups + o.i0, pg - o.i0, d_terms, n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, (int)o.u64b, st));
           if (o.i0 + o.i1 > pg + 1)
-            HIPCHK(launch_build_inputs(d_groups + pg + 1, o.i0 + o.i1 - pg - 1, d_terms, n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, st));
+            HIPCHK(launch_build_inputs(d_groups + pg + 1, o.i0 + o.i1 - pg - 1, d_terms, n, T, b.rp0, B, d, M->Kd, M->cfg.norm, M->cfg.norm_eps, o.i3, (int)o.u64b, st));
         }
         break;
       }

@@ -136,9 +136,10 @@ hipError_t launch_embed(const int* tok, const int* pos, const float* W_E, const 
                         hipStream_t s);
 
 // Tiles have T rows, of which the first rp0 are built for instance 0 only; last_only groups: the last B rows of a tile.
-// shared_terms: the largest number of terms without instance stride in any of the groups (0: none)
+// shared_terms: the largest number of terms without instance stride in any of the groups (0: none); many_terms: the largest
+// number of terms of one kind, with or without, in any of them
 hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term* terms, int n_inst, int T, int rp0, int B,
-                               int d, int ldq, int norm_kind, float eps, int shared_terms, hipStream_t s);
+                               int d, int ldq, int norm_kind, float eps, int shared_terms, int many_terms, hipStream_t s);
 
 // Edge-batched patch: instance i reads x_i = xv - delta[send[i]] (mode 1) or
 // x_i = x_{i-1} - delta[send[i]] with x_{-1} = xv (mode 2), then norm and

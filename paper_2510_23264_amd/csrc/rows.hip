@@ -131,26 +131,25 @@ __device__ __forceinline__ void row_axpy(float (&x)[MAXE], float sign, const flo
     for (int j = 0; j < MAXE; j++) if (j < E) x[j] += sign * p[lane + 64 * j];
   }
 }
-// x += sign * p for n terms in their order.  The rows of up to four are loaded before the first is added: one at a time, a
-// wave that gathers tens of them waits a memory latency for each (and, with shared and other terms mixed, for the
-// descriptors of those it skips: GPT-2-small graph with 90 % of the edges gone 43.1 -> 39.3 ms).
-template <int MAXE, bool VEC>
+// x += sign * p for n terms in their order, the rows of U of them loaded before the first is added: piece by piece (U = 0), a
+// wave that gathers tens of them waits a memory latency for each.
+template <int MAXE, bool VEC, int U>
 __device__ __forceinline__ void row_add_terms(float (&x)[MAXE], const Term* tt, int n, int inst, long long src, int E, int lane) {
-  constexpr int U = MAXE <= 16 ? 4 : MAXE <= 32 ? 2 : 1;
   int t = 0;
-  for (; t + U <= n; t += U) {
-    float v[U][MAXE];
-    float sign[U];
+  if (U > 0)
+    for (; t + U <= n; t += U) {
+      float v[U ? U : 1][MAXE];
+      float sign[U ? U : 1];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      sign[u] = tt[t + u].sign;
-      row_load<MAXE, VEC>(v[u], tt[t + u].p + inst * tt[t + u].inst_stride + src, E, lane);
+      for (int u = 0; u < U; u++) {
+        sign[u] = tt[t + u].sign;
+        row_load<MAXE, VEC>(v[u], tt[t + u].p + inst * tt[t + u].inst_stride + src, E, lane);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int j = 0; j < MAXE; j++) if (j < E) x[j] += sign[u] * v[u][j];
     }
-#pragma unroll
-    for (int u = 0; u < U; u++)
-#pragma unroll
-      for (int j = 0; j < MAXE; j++) if (j < E) x[j] += sign[u] * v[u][j];
-  }
   for (; t < n; t++) row_axpy<MAXE, VEC>(x, tt[t].sign, tt[t].p + inst * tt[t].inst_stride + src, E, lane);
 }
 // y = a - p
@@ -274,7 +273,7 @@ __device__ __forceinline__ void emit_row(const float (&y)[MAXE], int E, int d, i
 // recomputed once for all candidates) -- is summed once per row into x0 and reused for the instances of the
 // chunk; with most edges removed that is the larger part of what a receiver's input is gathered from.  The
 // arithmetic of an instance does not depend on the chunk size or on its place in the chunk.
-template <int MAXE, bool VEC>
+template <int MAXE, bool VEC, int U>
 __global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, const Term* terms, int T, int rp0, int B,
                                                        int d, int ldq, int norm_kind, float eps) {
   GroupDesc g = groups[blockIdx.y];
@@ -297,10 +296,10 @@ __global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, c
   const Term* tt = terms + g.term_begin;
   const bool base_shared = g.base && g.base_is == 0;
   if (base_shared) row_load<MAXE, VEC>(x, g.base + src, E, lane);
-  row_add_terms<MAXE, VEC>(x, tt, g.term_shared, 0, src, E, lane);
+  row_add_terms<MAXE, VEC, U>(x, tt, g.term_shared, 0, src, E, lane);
   if (g.base && !base_shared) row_axpy<MAXE, VEC>(x, 1.0f, g.base + inst * g.base_is + src, E, lane);
   if (g.run) row_axpy<MAXE, VEC>(x, 1.0f, g.run + inst * g.run_is + src, E, lane);
-  row_add_terms<MAXE, VEC>(x, tt + g.term_shared, g.term_count - g.term_shared, inst, src, E, lane);
+  row_add_terms<MAXE, VEC, U>(x, tt + g.term_shared, g.term_count - g.term_shared, inst, src, E, lane);
   norm_row<MAXE, VEC>(x, E, d, lane, norm_kind, eps, g.gain, g.offset);
   emit_row<MAXE, VEC>(x, E, d, lane, g, inst, row, ldq);
 }
@@ -310,7 +309,7 @@ __global__ __launch_bounds__(256) void build_inputs_k(const GroupDesc* groups, c
 // instance stride are summed once per row into x0 and reused for the instances of the chunk.  With most edges
 // removed that is the larger part of what a receiver's input is gathered from.  The arithmetic of an instance
 // does not depend on the chunk size or on its place in the chunk, and is that of the kernel above.
-template <int MAXE, bool VEC>
+template <int MAXE, bool VEC, int U>
 __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* groups, const Term* terms, int T, int rp0,
                                                               int B, int d, int ldq, int norm_kind, float eps,
                                                               int n_inst, int chunk, int n_groups) {
@@ -335,7 +334,7 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
 #pragma unroll
   for (int j = 0; j < MAXE; j++) x0[j] = 0.f;
   if (base_shared) row_load<MAXE, VEC>(x0, g.base + src, E, lane);
-  row_add_terms<MAXE, VEC>(x0, tt, g.term_shared, 0, src, E, lane);
+  row_add_terms<MAXE, VEC, U>(x0, tt, g.term_shared, 0, src, E, lane);
   float gn[MAXE], of[MAXE];               // read once for the chunk, not once per instance
   norm_params_load<MAXE, VEC>(gn, of, E, lane, norm_kind, g.gain, g.offset);
   const int i_end = once ? 1 : min(n_inst, ((int)blockIdx.z + 1) * chunk);
@@ -345,7 +344,7 @@ __global__ __launch_bounds__(256) void build_inputs_shared_k(const GroupDesc* gr
     for (int j = 0; j < MAXE; j++) x[j] = x0[j];
     if (g.base && !base_shared) row_axpy<MAXE, VEC>(x, 1.0f, g.base + inst * g.base_is + src, E, lane);
     if (g.run) row_axpy<MAXE, VEC>(x, 1.0f, g.run + inst * g.run_is + src, E, lane);
-    row_add_terms<MAXE, VEC>(x, tt + g.term_shared, g.term_count - g.term_shared, inst, src, E, lane);
+    row_add_terms<MAXE, VEC, U>(x, tt + g.term_shared, g.term_count - g.term_shared, inst, src, E, lane);
     norm_row<MAXE, VEC>(x, E, d, lane, norm_kind, eps, gn, of);
     emit_row<MAXE, VEC>(x, E, d, lane, g, inst, row, ldq);
   }
@@ -427,9 +426,16 @@ __global__ __launch_bounds__(256) void patch_indep_k(const GroupDesc* gp, const 
     else { CALL(64, false); }                                       \
   } while (0)
 
+// Rows of terms in flight: as many as the registers of rows of 64 M values leave room for.  They pay where a group has as
+// many terms (GPT-2-small with 90 % of the edges gone, candidates of four receivers 43.1 -> 39.3 ms; d_model 960, 30 % gone,
+// gather 4.17 -> 3.35 ms); with fewer the registers only cost waves, and a launch takes the form without (no edge gone, us a
+// launch with and without: d_model 4096 19.2 and 17.6, 960 18.9 and 16.5, 768 24.6 and 24.1).
+#define TERMS_AHEAD(M) ((M) <= 16 ? 4 : (M) <= 32 ? 2 : 1)
+
 hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term* terms, int n_inst, int T, int rp0, int B,
-                               int d, int ldq, int norm_kind, float eps, int shared_terms, hipStream_t s) {
+                               int d, int ldq, int norm_kind, float eps, int shared_terms, int many_terms, hipStream_t s) {
   if (n_groups == 0 || n_inst == 0) return hipSuccess;
+  const bool ahead = many_terms >= std::max(2, TERMS_AHEAD(d / 64));
   // Groups with instance-independent terms go to the kernel that sums those once per chunk of instances (wide
   // rows, more than 16 values per lane, have no registers to spare for the shared sum and stay with the plain
   // kernel).  Both kernels give a group the same bits.
@@ -438,13 +444,15 @@ hipError_t launch_build_inputs(const GroupDesc* groups, int n_groups, const Term
     int chunk = (int)std::min<long long>(8, std::max<long long>(1, blocks / 16384));
     const int rq8 = ((T + 3) / 4 + 7) / 8 * 8;        // row quads, padded to the 8 XCDs (the padding exits at once)
     dim3 grid(rq8 * n_groups, 1, (n_inst + chunk - 1) / chunk);
-#define CALL(M, V) hipLaunchKernelGGL((build_inputs_shared_k<M, V>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps, n_inst, chunk, n_groups)
+#define CALL(M, V) if (ahead) hipLaunchKernelGGL((build_inputs_shared_k<M, V, TERMS_AHEAD(M)>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps, n_inst, chunk, n_groups); \
+                   else hipLaunchKernelGGL((build_inputs_shared_k<M, V, 0>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps, n_inst, chunk, n_groups)
     PAHQ_DISPATCH_E(d / 64, CALL);
 #undef CALL
     return hipGetLastError();
   }
   dim3 grid((T + 3) / 4, n_groups, n_inst);
-#define CALL(M, V) hipLaunchKernelGGL((build_inputs_k<M, V>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps)
+#define CALL(M, V) if (ahead) hipLaunchKernelGGL((build_inputs_k<M, V, TERMS_AHEAD(M)>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps); \
+                   else hipLaunchKernelGGL((build_inputs_k<M, V, 0>), grid, dim3(256), 0, s, groups, terms, T, rp0, B, d, ldq, norm_kind, eps)
   PAHQ_DISPATCH_E(d / 64, CALL);
 #undef CALL
   return hipGetLastError();

@@ -96,3 +96,34 @@ def test_a_score_does_not_depend_on_its_batch(size, options):
         finally:
             gm.close()
     assert np.isfinite(out[0]).all() and np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32)), (size, options)
+
+
+@pytest.mark.parametrize("d", [64, 256, 320, 768, 960, 1024, 1088, 1280, 2112, 2304])
+def test_gathered_inputs_by_width_and_number_of_terms(d):
+    """A receiver's input is the stream and a sum of terms, of which as many as a row's registers allow are loaded ahead once
+    a group has that many: rows of every width the kernels distinguish, with the first 0 to 7 of the edges into every receiver
+    from the third layer's second head on gone, against the oracle."""
+    import paper_2510_23264_amd as P
+    shape = ModelShape(n_layers=4, n_heads=3, d_head=16, d_model=d, d_mlp=0, vocab=61, n_ctx=6, act=0)
+    w = synth.make_weights(shape, 9, std=1.2 / d ** 0.5, affine_std=0.1)
+    rng = np.random.default_rng(d)
+    clean = rng.integers(0, 61, (3, 6)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:4] = (clean[:, 1:4] + 1 + rng.integers(0, 60, (3, 3))) % 61
+    gm = P.Model(shape, w, 3, 6, precision=P.ALL_FP32, max_batch_edges=4)
+    try:
+        gm.clean_cache(clean, corrupt)
+        om = OModel(shape, w)
+        g, oa = om.g, Acdc(om, clean, corrupt, MODE_ALL_FP32)
+        for gone in (0, 1, 2, 3, 4, 5, 7):
+            r = g.headin(2, 1, 0)
+            R = g.empty_removed()
+            for q in range(r, g.n_receivers):
+                R[q, :min(gone, g.n_upstream(q))] = True
+            gm.set_removed(g.removed_to_flat(R).astype(np.uint8))
+            senders = np.array([0, 3, 6], np.int32)
+            got = gm.eval_edges(r, senders)
+            want = np.array([oa.kl_edge(r, int(u), removed=R) for u in senders])
+            assert (np.abs(got - want) <= F32_ATOL + F32_RTOL * np.abs(want)).all(), (d, gone)
+    finally:
+        gm.close()
