@@ -35,3 +35,33 @@ def test_every_tile_gives_the_same_bits(model, n, k, rows):
     ends = np.r_[0:40, rows[0] - 40:rows[0]]
     exact, mag = exact_and_scale(a[ends], w)
     assert (np.abs(out[0][ends] - exact) <= k * 2.0 ** -24 * mag).all()      # k additions of binary32
+
+
+@pytest.mark.parametrize("options", [dict(), dict(nonattn_bf16=True), dict(low_bits=16)])
+def test_scores_across_the_tiles_of_one_and_two_bytes(options):
+    """Scores by batch where the same layer's products take other tiles, in one-byte codes and in bfloat16: with 48, 24 and 1
+    candidates the first MLP's input product has 5768, 2888 and 128 rows of 1280 columns (128 x 128, 64 x 128, 32 x 64; its output
+    product 64 x 64 and 32 x 64), and the unembedding with the KL epilogue 384, 192 and 8 rows of 20001 (128 x 128, then
+    64 x 128)."""
+    import paper_2510_23264_amd as P
+    B, S, V = 8, 16, 20001
+    shape = synth.ModelShape(n_layers=2, n_heads=4, d_head=64, d_model=512, d_mlp=1280, vocab=V, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 5, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(5)
+    clean = rng.integers(0, V, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, V - 1, (B, 5))) % V      # position 0 is shared
+    out = []
+    for batch in (48, 24, 1):
+        gm = P.Model(shape, w, B, S, max_batch_edges=batch, **options)
+        try:
+            gm.clean_cache(clean, corrupt)
+            r = 3 * 4                                   # the first layer's MLP input: every row of it is a candidate's own
+            senders = np.resize(np.arange(P.n_upstream(gm.cfg, r), dtype=np.int32), 48)[:batch]
+            before = gm.counters()[1]
+            out.append(gm.eval_edges(r, senders))
+            assert gm.counters()[1] == before + 1
+        finally:
+            gm.close()
+    for got in out:
+        assert np.isfinite(got).all() and np.array_equal(got.view(np.uint32), out[0][:got.size].view(np.uint32))

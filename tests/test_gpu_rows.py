@@ -127,3 +127,36 @@ def test_gathered_inputs_by_width_and_number_of_terms(d):
             assert (np.abs(got - want) <= F32_ATOL + F32_RTOL * np.abs(want)).all(), (d, gone)
     finally:
         gm.close()
+
+
+@pytest.mark.parametrize("size", [(2, 2, 64, 132, 3, 17, 0), (3, 2, 64, 68, 2, 70, 1), (2, 3, 32, 64, 1, 33, 0)])
+@pytest.mark.parametrize("options", [dict(), dict(precision=0), dict(nonattn_bf16=True)])
+def test_one_handle_with_one_prompt_pair_after_another(size, options):
+    """The order of a tile's rows belongs to the prompt pair: a handle that has seen other pairs, with other first changes, gives
+    the bits of a fresh one -- scores, a circuit's logits and the cached outputs."""
+    import paper_2510_23264_amd as P
+
+    def everything(gm, clean, corrupt):
+        gm.clean_cache(clean, corrupt)
+        res, rng = [gm.get_sender_output(0, 1).ravel(), gm.get_sender_output(1, P.n_senders(gm.cfg) - 1).ravel(), gm.get_logits(1).ravel()], np.random.default_rng(2)
+        for r in (P.n_receivers(gm.cfg) - 1, P.n_receivers(gm.cfg) // 2, 0):
+            state = (rng.random(gm.n_edges) < 0.4).astype(np.uint8)
+            state[:sum(P.n_upstream(gm.cfg, q) for q in range(r))] = 0
+            gm.set_removed(state)
+            res.append(gm.eval_edges(r, np.arange(P.n_upstream(gm.cfg, r), dtype=np.int32)))
+        kl, logits = gm.eval_circuit(kept=(rng.random(gm.n_edges) < 0.5).astype(np.uint8), want_logits=True)
+        return np.concatenate(res + [np.float32([kl]), np.asarray(logits, np.float32).ravel()])
+
+    pairs = [make(size, first, seed)[2:] for first, seed in (("late", 5), ("start", 6), ("mixed", 7), ("never", 8), ("mixed", 9), ("late", 5))]
+    shape, w = make(size, "late", 5)[:2]
+    used = P.Model(shape, w, *pairs[0][0].shape, max_batch_edges=5, **options)
+    try:
+        for clean, corrupt in pairs:
+            fresh = P.Model(shape, w, *clean.shape, max_batch_edges=5, **options)
+            try:
+                want, got = everything(fresh, clean, corrupt), everything(used, clean, corrupt)
+            finally:
+                fresh.close()
+            assert np.isfinite(want).all() and np.array_equal(got.view(np.uint32), want.view(np.uint32))
+    finally:
+        used.close()
