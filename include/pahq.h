@@ -420,17 +420,17 @@ int pahq_measure_ceilings(void* hip_stream, void* scratch, size_t scratch_bytes,
  * pahq_quantize_rows for code that may not allocate device or pinned memory and has no model
  * or workspace at hand: kernels recorded into a HIP graph, serving loops, harnesses that forbid
  * hipMalloc.  Same arithmetic, bit for bit (scale = amax / 448, 1 if amax = 0; inv = 1 / scale;
- * code = rne_e4m3(x * inv)), for rows of ANY length: a row is split over workgroups, and the per-row
- * maxima they combine live in a static device array of PAHQ_NOALLOC_MAX_ROWS words (128 KiB) that
- * every GPU the library runs on holds until the process ends.
+ * code = rne_e4m3(x * inv)), for rows of ANY length.  Rows of up to 16384 elements are held in registers: such calls are one
+ * launch each and share nothing.  A longer row is split over workgroups, and the per-row maxima they combine live in a static
+ * device array of PAHQ_NOALLOC_MAX_ROWS words (128 KiB) that every GPU the library runs on holds until the process ends.
  *   hip_stream  hipStream_t (NULL = default stream); the work is enqueued there, nothing is waited for
  *   x           DEVICE, rows x cols floats, row-major          (caller-owned, read)
  *   codes       DEVICE, rows x cols bytes                      (caller-owned, written)
  *   scales      DEVICE, rows floats                            (caller-owned, written)
  * The device that owns the pointers and the stream must be the current one.  rows = 0 does nothing;
  * rows > PAHQ_NOALLOC_MAX_ROWS gives PAHQ_ETOOBIG (split the call), rows < 0, cols < 1 or a null
- * pointer PAHQ_EINVAL.  No allocation, no memset node, no synchronisation.  All calls on one GPU
- * share that GPU's array: calls that overlap there (different streams or host threads) race. */
+ * pointer PAHQ_EINVAL.  No allocation, no memset node, no synchronisation.  Calls with rows of more than 16384 elements
+ * share their GPU's array: such calls that overlap there (different streams or host threads) race; all others may overlap. */
 enum { PAHQ_NOALLOC_MAX_ROWS = 32768 };
 int pahq_quantize_rows_noalloc(void* hip_stream, const float* x, int32_t rows, int32_t cols, uint8_t* codes,
                                float* scales);

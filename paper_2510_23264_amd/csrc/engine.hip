@@ -19,16 +19,16 @@
 // is causal, so both runs have the same bits there, every D_s is zero there, and so the candidates of a batch, which
 // differ by D_s alone, agree there: a candidate pass computes these rp0 rows for its first instance only, and the other
 // instances' keys and values of these positions are read from it.  (Reference runs of several heads differ everywhere:
-// their precision does; they compute all rows.)  What it gives is the share of those rows, a third to a half with two
-// changed template positions in sixteen: candidates into layer 5 of 12 at the GPT-2-small shape 296 -> 149 ms, its pruned
-// graph 73 -> 45 ms, 24 layers of 1024 (three positions in 24) 395 -> 355 ms.  The rows at the
-// last position come last, in the order of the
-// sequences.  What a pass computes last is read at that position
-// only: the output node takes the B last rows, so in the last layer the queries, the output projection and the MLP are
-// needed there alone, and keys and values everywhere.  Passes that end in a score compute just that (`last` below);
+// their precision does; they compute all rows.)  What it gives is the share of those rows, which the prompts set: candidates
+// into the sixth of 8 layers of the GPT-2-small shape (50 prompts of 16) take 32.7 ms when the first token already differs and
+// 21.6 when the ninth is the first that does, those into the fifteenth of 17 layers of 1024 (64 prompts of 24) 98 and, from
+// the thirteenth on, 70 ms.
+// The rows at the last position come last, in the order of the sequences.  What a pass computes last is read at that
+// position only: the output node takes the B last rows, so in the last layer the queries, the output projection and the MLP
+// are needed there alone, and keys and values everywhere.  Passes that end in a score compute just that (`last` below);
 // the cache passes, whose sender outputs are kept, compute every row.  (Of a layer's matrix products that leaves a
-// sixth and a sixteenth of the rest at 16 positions: candidates into layer 5 of 12 at the GPT-2-small shape 330 -> 302
-// ms, into the last layer of a 7B-class model 82 -> 34 ms.)
+// sixth and a sixteenth of the rest at 16 positions.  By itself, with no rows shared: candidates into layer 5 of 12 at the
+// GPT-2-small shape 330 -> 302 ms, into the last layer of a 7B-class model 82 -> 34 ms.)
 #include "engine.h"
 #include <algorithm>
 #include <map>

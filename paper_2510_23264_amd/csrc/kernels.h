@@ -36,7 +36,7 @@ struct GroupDesc {
 // first; see "Rows of a pass" in engine.hip).
 //   val[m][n] = (sum_k A[m][k] * W[n][k]) * ascale[m] * wscale[n / wscale_block]
 //   C[m][n]   = act(val + bias[n]) + add[m][n]
-//   aux[m][n] = val - aux_sub[m % rpi][n]            (optional second output)
+//   aux[m][n] = val - aux_sub[row of m in its instance][n]      (optional second output)
 // A, W: e4m3 codes, K contiguous, K a multiple of 128 (zero padded).
 struct GemmProb {
   const void* A;       long long a_is;  int lda;  int rpi;          // rows per instance
@@ -150,7 +150,7 @@ hipError_t launch_patch_build(const GroupDesc* g, const float* xv, const float* 
 // xv -= delta[send[0]]; xv -= delta[send[1]]; ... (k terms, same order as mode 2 above)
 hipError_t launch_xv_advance(float* xv, const float* delta0, long long delta_stride, const int* send, int k,
                              long long n_elem, hipStream_t s);
-// out = base + sum(terms) over n_elem elements (instance 0 of every term)
+// Products with the log-softmax / KL epilogue (exact sums; arguments as for launch_gemm_fp8)
 hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int b16, hipStream_t s);
 // One wavefront per row of kl_part: logz[row] = log sum exp of the row from its parts (if logz != null);
 // row_kl[row] = a - (ref_logz[row % B] - logz) * ref_psum[row % B] with a = the sum of the parts' third values
@@ -160,6 +160,7 @@ hipError_t launch_kl_reduce(const float* kl_part, int npart, int rows, int B, co
 // psum[b] = sum over v < V of exp(logits[b][v] - logz[b])
 hipError_t launch_ref_probs(const float* logits, const double* logz, double* psum, int B, int V, int ldv,
                             hipStream_t s);
+// out = base + sum(terms) over n_elem elements (instance 0 of every term)
 hipError_t launch_tile_lincomb(float* out, const float* base, const Term* terms, int n_terms, long long n_elem,
                                int base_last, hipStream_t s);
 // out[t] = row row_of[t] of the tile, t = 0 .. T-1 (d a multiple of 4)

@@ -97,13 +97,12 @@ __device__ __forceinline__ void wait_vm_barrier() {
   static_assert(N < 64, "vmcnt has six bits");
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
-// The wait in front of a slab with `after` more slabs behind it, of which a loop of NS stages has requested up to
-// NS - 2, each with L loads of this wave.
+// The wait in front of a slab with `after` more slabs behind it, in a loop of two or three stages that has requested one slab
+// less than it has stages, each with L loads of this wave.
 template <int NS, int L>
 __device__ __forceinline__ void wait_slab_barrier(int after) {
-  static_assert(NS >= 2 && NS <= 4, "stages");
-  if (after >= NS - 2) wait_vm_barrier<(NS - 2) * L>();
-  else if (NS == 4 && after == 1) wait_vm_barrier<L>();
+  static_assert(NS == 2 || NS == 3, "stages");
+  if (NS == 3 && after >= 1) wait_vm_barrier<L>();
   else wait_vm_barrier<0>();
 }
 // "Everything has arrived" is said with the builtin, so that the compiler also knows that its own

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
       stride[t] = (long long)HPS * D.N * D.Kh;
     }
   }
-  // row scales of a slab: entry [q][r] (head q of the slab, tile row r) is lane's if 64 wave + lane = 128 q + r;
+  // row scales of a slab: entry [q][r] (head q of the slab, tile row r) is lane's if 64 wave + lane = BM q + r;
   // waves past the last entry repeat what earlier ones fetch (so that all waves count alike), and with one head per slab
   // the entries behind the first BM repeat the rows into the unused part
   const float* zsrc;
