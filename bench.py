@@ -43,38 +43,49 @@ HBM_PEAK = 8000.0      # GB/s
 
 # Which kernels the library launches for a kernel class (rocprofv3 names them; the library reports classes).
 KERNELS_OF_CLASS = {
-    "gemm_fp8": ("pahq::gemm_p_k", "pahq::gemm_x_k"),
+    "gemm_fp8": ("pahq::gemm_p_k", "pahq::gemm_x_k", "pahq::gemm_s_k", "pahq::gemm_fp8_k"),
     "gather_norm_quant": ("pahq::build_inputs_k", "pahq::build_inputs_shared_k"),
-    "hidden_quant": ("pahq::hidden_quant_vec_k",), "attention": ("pahq::attention_mfma_k",),
-    "oproj_fused": ("pahq::oproj_x_k",), "gemm_f32": ("pahq::gemm_f32_k",), "edge_patch": ("pahq::patch_indep_k", "pahq::patch_build_k"),
+    "hidden_quant": ("pahq::hidden_quant_vec_k", "pahq::hidden_quant_k"),
+    "attention": ("pahq::attention_mfma_k", "pahq::attention_qtile_k"),
+    "oproj_fused": ("pahq::oproj_x_k", "pahq::oproj_fused_k"),
+    "gemm_f32": ("pahq::gemm_f32_x_k", "pahq::gemm_f32_heads_k", "pahq::gemm_f32_k"),
+    "edge_patch": ("pahq::patch_indep_k", "pahq::patch_build_k"),
     "kl": ("pahq::kl_reduce_k", "pahq::kl_mean_k"),
 }
 PROFILE_FILES = {"all_edges": "hbm_traffic_per_kernel_cfg3_all_edges_pmc.txt",
                  "gather_regime": "hbm_traffic_per_kernel_cfg3_gather_regime_pmc.txt"}
 
 
-def traffic_from_profile(regime, kernel_class, workload_key):
+def traffic_from_profile(regime, kernel_class, workload_key, now):
     """HBM bytes per launch of a kernel class, read from the committed rocprofv3 PMC summary of the same
     workload (profiles/): counters cannot be read from inside this process.  The summary states the
-    workload it was taken on and, per kernel, launches and calibrated read / write MB per launch.  Returns
-    None when the summary is of another workload; raises when the summary does not list the kernels this
-    class launches (then it predates a kernel change and must be re-measured)."""
+    workload it was taken on, per kernel class the launches and algorithmic bytes of one pass, and per kernel
+    its launches and calibrated read / write MB per launch.  None when the summary is of another workload, or
+    stale: `now` (this run's profile of the class) has other launches or bytes than the summary's run, or the
+    kernels known for the class do not make up its launches (that run went through the workload twice).  Then
+    it must be measured again."""
     path = os.path.join(ROOT, "profiles", PROFILE_FILES[regime])
     if not os.path.exists(path):
         return None
-    rows, workload = {}, None
+    rows, workload, classes = {}, None, {}
     for line in open(path):
         if line.startswith("# workload:"):
             workload = line.split(":", 1)[1].strip()
+        if line.startswith("# classes of one pass"):
+            classes = json.loads(line.split(":", 1)[1])
         m = re.match(r"^(\S.*?)\s+(\d+)\s+([0-9.]+)\s+([0-9.]+)\s*$", line)
         if m and not line.startswith("#"):
             rows[m.group(1).strip()] = (int(m.group(2)), float(m.group(3)), float(m.group(4)))
     if workload != workload_key:
         return None
     mine = {k: v for k, v in rows.items() if any(k.startswith(p) for p in KERNELS_OF_CLASS.get(kernel_class, ()))}
-    if not mine:
-        raise RuntimeError(f"{path} lists no kernel of class {kernel_class}: the summary is stale, re-measure it")
     n = sum(v[0] for v in mine.values())
+    launches, per_launch = classes.get(kernel_class, (0, 0))
+    same = lambda x, y, tol: abs(x - y) <= tol * max(x, y)        # noqa: E731
+    if not (same(launches, now["launches"], 0.01) and same(per_launch, now["bytes"] / now["launches"], 0.01) and same(n, 2 * launches, 0.1)):
+        print(f"bench.py: {path} is stale: class {kernel_class} has {now['launches']} launches of {now['bytes'] / now['launches']:.0f} bytes, "
+              f"the summary's run had {launches} of {per_launch}, {n} of them in known kernels over two passes", file=sys.stderr, flush=True)
+        return None
     return round(sum(v[0] * (v[1] + v[2]) for v in mine.values()) / n * 1e6)
 
 
@@ -175,7 +186,7 @@ def gather_regime(gm, P, cfg, receivers, torch, workload_key, mma):
     dom = "gather_norm_quant"
     return {"edges_per_s": round(n / dt, 1), "edges": int(n), "receivers": int(done), "removed_fraction": 0.9, "seed": 12345,
             "roofline": roofline_of(dom, prof[dom], prof[dom]["ms"] / total, mma,
-                                    traffic_from_profile("gather_regime", dom, workload_key),
+                                    traffic_from_profile("gather_regime", dom, workload_key, prof[dom]),
                                     "HIP events on the library's stream around every launch, second run of the sample"),
             "kernels": kernel_table(prof)}
 
@@ -325,7 +336,7 @@ def main():
                          "B": spec["B"], "S": spec["S"], "batch_edges": args.batch, "recv_stride": args.recv_stride,
                          "edges_per_step": n_evals // args.steps, "seed": spec["seed"]}
         out["roofline"] = roofline_of(dom, timed, prof[dom]["ms"] / sum(v["ms"] for v in prof.values()), args.mma,
-                                      traffic_from_profile("all_edges", dom, workload_key) if args.recv_stride == 1 else None,
+                                      traffic_from_profile("all_edges", dom, workload_key, prof[dom]) if args.recv_stride == 1 else None,
                                       "HIP events on the library's stream around every launch of this class in every third "
                                       "executor pass of the timed steps")
         out["kernels"] = kernel_table(prof)
