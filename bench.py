@@ -43,7 +43,7 @@ HBM_PEAK = 8000.0      # GB/s
 
 # Which kernels the library launches for a kernel class (rocprofv3 names them; the library reports classes).
 KERNELS_OF_CLASS = {
-    "gemm_fp8": ("pahq::gemm_p_k", "pahq::gemm_x_k", "pahq::gemm_s_k", "pahq::gemm_fp8_k"),
+    "gemm_fp8": ("pahq::gemm_w_k", "pahq::gemm_p_k", "pahq::gemm_x_k", "pahq::gemm_s_k", "pahq::gemm_fp8_k"),
     "gather_norm_quant": ("pahq::build_inputs_k", "pahq::build_inputs_shared_k"),
     "hidden_quant": ("pahq::hidden_quant_vec_k", "pahq::hidden_quant_k"),
     "attention": ("pahq::attention_mfma_k", "pahq::attention_qtile_k"),

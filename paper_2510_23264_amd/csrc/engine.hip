@@ -1052,8 +1052,12 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
             return PAHQ_EINVAL;
         if (o.p0) HIPCHK(launch_gemm_fp8_kl(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, b.probs[o.i0].b16, st));      // log-softmax / KL epilogue
         else {
-          for (int q = 0; q < o.i1; q++) if (b.probs[o.i0 + q].kl_part || !b.probs[o.i0 + q].C) return PAHQ_EINVAL;
-          HIPCHK(launch_gemm_fp8(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, M->cfg.mma == PAHQ_MMA_F16_EXACT, b.probs[o.i0].b16, st));
+          bool wide = true;
+          for (int q = 0; q < o.i1; q++) {
+            if (b.probs[o.i0 + q].kl_part || !b.probs[o.i0 + q].C) return PAHQ_EINVAL;
+            wide = wide && gemm8_wide_ok(b.probs[o.i0 + q]);
+          }
+          HIPCHK(launch_gemm_fp8(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, M->cfg.mma == PAHQ_MMA_F16_EXACT, b.probs[o.i0].b16, wide, st));
         }
         break;
       case OP_KLRED:

@@ -30,6 +30,7 @@
 //   fp32 multiply-accumulate) for the heads in fp32 and the all-fp32 mode.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include "kernels.h"
 #include "device_util.h"
 #include "mma_util.h"
@@ -681,6 +682,238 @@ __global__ __launch_bounds__(512, 1) void gemm_p_k(const GemmProb* probs) {
   }
 }
 
+// ------------------------------------------------------------------ exact sums, the large plain problems
+// gemm_w_k: one instance, no second output (gemm8_wide_ok).  256 x 256 tile, eight wavefronts (4 x 2) of 64 x 128, one persistent
+// workgroup per compute unit, slabs of 128 bytes of K in two stages of 64 KB.  gemm_p_k, which these problems took before,
+// spent its time on four things that this shape and schedule remove:
+//   - all waves read their operands behind the slab's barrier and multiplied afterwards, so that the matrix cores idled
+//     while LDS worked and the other way round.  Here the next half slab's reads, its conversions and the requests for the slab after
+//     it stand between the matrix instructions of the present one (step below);
+//   - two conversions per matrix instruction (a wave of 64 x 64); one and a half here, and half the LDS reads per product;
+//   - 24 bytes per clock and unit from L2; 16 here.  (Slabs of 64 bytes in more stages ask L2 for half lines: 15 % slower.)
+//   - an epilogue that placed every row by itself, 5 k clocks a tile: rows are equidistant here, one offset per lane.
+// Tiles at the right and lower edge are moved inwards until they end there and overlap their neighbours: no guard anywhere, and
+// the overlap is written twice with the same bits (so C may not be `add`).
+// Elements are the sums of the other kernels in the same order: same bits.  us, before and now (one MI355X): 102400 x 2304 x 768
+// 498 -> 353, 102400 x 3072 x 768 582 -> 431, 102400 x 768 x 3072 521 -> 423, 24576 x 4096 x 1024 224 -> 169, 4096 x 12288 x 4096
+// 354 -> 292 (1.4 PFLOP/s).  What bounds it now: at K = 768 the stores (1.26 GB of them; a slab requested behind the stores of
+// a tile is not seen to have landed before they have), at long K the chip's power: the shader clock falls to 1.75 GHz.
+// Measured and not kept: two workgroups of 256 x 128 per unit with slabs of 64 bytes (530 us where this takes 431), one wave of
+// 64 x 128 per SIMD whose finished tile leaves during the next one (747), V_MFMA_F32_32X32X16_F16 (the same bits, 15 % slower: the
+// clock falls further).
+template <bool B16>
+__global__ __launch_bounds__(512, 2) void gemm_w_k(const GemmProb* probs) {
+  constexpr int BM = 256, BN = 256, NI = 8, STAGE = (BM + BN) * 128;
+  static_assert(STAGE == 65536, "the stages differ in one address bit");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  float* const e_base = (float*)(smem + 2 * STAGE);      // per tile parity: row scales, column scales, bias [256 each]
+  const GemmProb P = probs[blockIdx.y];
+  const int mt = (P.M + BM - 1) / BM, nt = (P.N + BN - 1) / BN, total = mt * nt;
+  const int chunk = (total + 7) >> 3, xcd = blockIdx.x & 7, per = gridDim.x >> 3;
+  const int jend = min(chunk, total - xcd * chunk);
+  int j = blockIdx.x >> 3;
+  if (j >= jend) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int li = lane & 15, lg = lane >> 4;
+  const int nslab = P.K >> 7;
+  auto tile_origin = [&](int jj, int& m0, int& n0) {
+    const int lin = xcd * chunk + jj, tm = lin / nt;
+    m0 = min(tm * BM, P.M - BM); n0 = min((lin - tm * nt) * BN, P.N - BN);
+  };
+
+  // ---- request side: waves 0-3 load 64 rows of A each, waves 4-7 of W.  LDS row 16 q + i of a 64-row block of W holds row 4 i + q
+  // of the block, so that a lane's accumulators of four 16-column tiles are neighbouring columns (see the epilogue).
+  const bool is_a = wave < 4;
+  const int ldo = is_a ? P.lda : P.ldw;
+  const uint32_t lane_off = (uint32_t)((lane >> 3) * (is_a ? 1 : 4) * ldo + ((lane & 7) ^ (lane >> 3)) * 16);
+  const uint8_t* src;
+  auto set_src = [&](int m0, int n0) {
+    src = is_a ? (const uint8_t*)P.A + (long long)(m0 + wave * 64) * P.lda : (const uint8_t*)P.W + (long long)(n0 + (wave - 4) * 64) * P.ldw;
+  };
+  int ji = j, ki = 0;                    // tile and slab of the next request
+  uint32_t to = __builtin_amdgcn_readfirstlane(lds_addr_of(smem) + wave * NI * 1024);      // and where it goes
+  auto request_one = [&](int t) {
+    slab_load16s(src + (long long)(is_a ? 8 * t : 32 * (t & 1) + (t >> 1)) * ldo, lane_off, to + t * 1024);
+  };
+  auto request_end = [&]() {
+    src += 128;
+    to ^= STAGE;
+    if (++ki == nslab) {
+      ki = 0; ji += per;
+      if (ji < jend) { int a, b; tile_origin(ji, a, b); set_src(a, b); }
+      else { src -= 128; ki = nslab - 1; ji -= per; }      // behind the last tile its last slab again (nobody reads it): no branch in the loop
+    }
+  };
+  auto request_scales = [&](int m0, int n0, float* e) {
+    const uint32_t o = (uint32_t)((wave & 3) * 64 + lane) * 4;
+    if (is_a) {
+      lds_load4s(P.ascale + m0, o, __builtin_amdgcn_readfirstlane(lds_addr_of(e + wave * 64)));
+      lds_load4(P.wscale + wscale_index(P, n0 + wave * 64 + lane), __builtin_amdgcn_readfirstlane(lds_addr_of(e + 256 + wave * 64)));
+    } else if (P.bias) {
+      lds_load4s(P.bias + n0, o, __builtin_amdgcn_readfirstlane(lds_addr_of(e + 512 + (wave & 3) * 64)));
+    }
+  };
+
+  // ---- compute side.  LDS offsets of the operands' first tiles in the first half (64 bytes of K) of the stage at hand; the
+  // other half is at ^ 64, the other stage at ^ STAGE.
+  uint32_t at_a = (wm * 64 + li) * 128 + (lg ^ (li & 7)) * 16, at_b = (BM + wn * 128 + li) * 128 + (lg ^ (li & 7)) * 16;
+  v4f acc[4][8];
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+  union U { uint4 u; v8bf h; };
+  U ra[2][4], rb[8];                     // a half slab's operands as they lie in LDS ([1] with B16 only)
+  v8h ha[4], hb[2];                      // decoded: all of A and two of W, of one step
+  auto dec = [&](const U& w, int s) -> v8h { return s ? decode8(w.u.z, w.u.w) : decode8(w.u.x, w.u.y); };
+  auto read_a = [&](int h, int i, uint32_t a) { ra[h][i].u = *(const uint4*)(smem + a + i * 2048); };
+  auto read_b = [&](int jj, uint32_t b) { rb[jj].u = *(const uint4*)(smem + b + jj * 2048); };
+  // One step, 32 k, of the half slab in ra, rb: the decoded operands for it are there, those of the next step are made on the
+  // way.  rd: the other half (at a, b) is read into the registers that this step sets free; rq: a slab is requested.
+  auto step = [&](int s, bool first, bool rd, bool rq, uint32_t a, uint32_t b) {
+#pragma unroll
+    for (int jj = 0; jj < 8; jj++) {
+      if (jj < 7) hb[(jj + 1) & 1] = dec(rb[jj + 1], s);
+      if (rd) { if (jj < 4) read_a(0, jj, a); read_b(jj, b); }
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha[i], hb[jj & 1], first ? zero : acc[i][jj], 0, 0, 0);
+        if (jj == 7) { ha[i] = dec(ra[0][i], s ^ 1); __builtin_amdgcn_sched_barrier(0); }
+      }
+      if (jj == 7) hb[0] = dec(rb[0], s ^ 1);
+      if (rq) request_one(jj);
+      if (jj < 7) {                      // a conversion behind every matrix instruction
+#pragma unroll
+        for (int q = 0; q < 4; q++) { __builtin_amdgcn_sched_group_barrier(0x8, 1, 0); __builtin_amdgcn_sched_group_barrier(0x2, 1, 0); }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // bfloat16: a half slab is one step, its operands need no conversion
+  auto step16 = [&](int h, bool first, bool rq, uint32_t a, uint32_t b) {
+#pragma unroll
+    for (int jj = 0; jj < 8; jj++) {
+      if (jj < 4) read_a(h ^ 1, jj, a);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra[h][i].h, rb[jj].h, first ? zero : acc[i][jj], 0, 0, 0);
+      read_b(jj, b);
+      if (rq) request_one(jj);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto read_first = [&]() {              // the operands of a tile's first step, from the slab at hand
+#pragma unroll
+    for (int i = 0; i < 4; i++) read_a(0, i, at_a);
+#pragma unroll
+    for (int jj = 0; jj < 8; jj++) read_b(jj, at_b);
+    if constexpr (!B16) {
+#pragma unroll
+      for (int i = 0; i < 4; i++) ha[i] = dec(ra[0][i], 0);
+      hb[0] = dec(rb[0], 0);
+    }
+  };
+
+  int m0, n0;
+  tile_origin(j, m0, n0);
+  set_src(m0, n0);
+#pragma unroll
+  for (int q = 0; q < 2; q++) {
+#pragma unroll
+    for (int t = 0; t < NI; t++) request_one(t);
+    request_end();
+  }
+  wait_vm<NI>();
+  wg_barrier();
+  read_first();
+  int par = 0;
+  bool stored = false;                   // has this wave stored a tile since the next slab was requested?
+  const bool has_bias = P.bias != nullptr, has_add = P.add != nullptr;
+
+  for (;;) {
+    float* const e = e_base + par * 768; // (the other parity's may still be read by a wave that is behind)
+    request_scales(m0, n0, e);
+    for (int k = 0; k < nslab; k++) {
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (B16) {
+        if (k == 0) step16(0, true, false, at_a ^ 64, at_b ^ 64);
+        else step16(0, false, false, at_a ^ 64, at_b ^ 64);
+      } else {
+        if (k == 0) step(0, true, false, false, 0, 0);
+        else step(0, false, false, false, 0, 0);
+        step(1, false, true, false, at_a ^ 64, at_b ^ 64);
+        step(0, false, false, false, 0, 0);
+      }
+      // The next slab has landed for this wave: only a tile's 32 stores (and scales) were issued after it.  All of this slab's
+      // operands are in registers, so behind the barrier its stage is free.
+      if (stored) wait_vm_barrier<32>(); else wait_vm_barrier<0>();
+      stored = false;
+      at_a ^= STAGE; at_b ^= STAGE;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (B16) step16(1, false, true, at_a, at_b);
+      else step(1, false, true, true, at_a, at_b);
+      request_end();
+    }
+    if (nslab == 1) { wait_vm<0>(); wg_barrier(); }        // the scales were requested in this very slab
+
+    // ---- epilogue.  Accumulator acc[i][4 b + q][r] of lane (li, lg) is tile row 64 wm + 16 i + 4 lg + r and column
+    // 128 wn + 64 b + 4 li + q: a lane stores 16 bytes of a row, the 16 lanes of a group 256 contiguous ones.
+    const long long row = (long long)P.ldc * 4, origin = (long long)(m0 + wm * 64) * P.ldc + n0 + wn * 128;
+    uint8_t* const out = (uint8_t*)(P.C + origin);
+    const uint8_t* const res = (const uint8_t*)(P.add + origin);
+    const uint32_t vo = (uint32_t)(lg * 4 * P.ldc + li * 4) * 4;
+    float4 bias[2], sa[4];
+    float cs[2];
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      cs[b] = e[256 + wn * 128 + b * 64 + li * 4];
+      bias[b] = has_bias ? *(const float4*)(e + 512 + wn * 128 + b * 64 + li * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) sa[i] = *(const float4*)(e + wm * 64 + i * 16 + lg * 4);
+    auto store4 = [&](int g, const float4 (&addv)[4], bool add) {          // group g = 4 b + i: four rows
+      const int b = g >> 2, i = g & 3;
+      const float sar[4] = {sa[i].x, sa[i].y, sa[i].z, sa[i].w};
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const float s2 = sar[r] * cs[b];
+        float4 v = make_float4(acc[i][4 * b][r] * s2, acc[i][4 * b + 1][r] * s2, acc[i][4 * b + 2][r] * s2, acc[i][4 * b + 3][r] * s2);
+        if (has_bias) { v.x += bias[b].x; v.y += bias[b].y; v.z += bias[b].z; v.w += bias[b].w; }
+        if (add) { v.x += addv[r].x; v.y += addv[r].y; v.z += addv[r].z; v.w += addv[r].w; }
+        gstore4_nt((float*)(out + (16 * i + r) * row + b * 256 + vo), v);
+      }
+    };
+    if (!has_add) {
+      const float4 none[4] = {};
+#pragma unroll
+      for (int g = 0; g < 8; g++) { store4(g, none, false); __builtin_amdgcn_sched_barrier(0); }
+    } else {
+      // The residual tile comes four groups ahead of the one that is stored: loads and stores complete in order, and one
+      // group at a time each would wait for the stores in front of it (102400 x 768 x 3072 542 -> 423 us).
+      constexpr int D = 4;
+      float4 addv[D][4];
+      auto load4 = [&](int g) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) addv[g % D][r] = gload4_nt((const float*)(res + (16 * (g & 3) + r) * row + (g >> 2) * 256 + vo));
+      };
+#pragma unroll
+      for (int g = 0; g < D; g++) load4(g);
+#pragma unroll
+      for (int g = 0; g < 8; g++) {
+        store4(g, addv[g % D], true);
+        if (g + D < 8) load4(g + D);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    read_first();                        // once more: what the last slab read ahead has left its registers to the epilogue
+    stored = true;
+    j += per;
+    if (j >= jend) break;
+    tile_origin(j, m0, n0);
+    par ^= 1;
+  }
+  wait_vm<0>();                          // no load may still be on its way into LDS that is another workgroup's by then
+}
+
 // ------------------------------------------------------------------ FP8 matrix-core instruction
 // Lane layout of the instruction (lane = 16*g + i): the operand of lane (i, g) is row i, bytes
 // [32g, 32g+32) of the slab.  WAVES_M x WAVES_N wavefronts; each owns a (BM / WAVES_M) x
@@ -788,8 +1021,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_k(const GemmPr
 // (r > 1) and rows of K are longer than 1024 bytes, it is taken only if it promises 6 %.  Of 38 such sizes that promise less
 // 26 took 4 % longer or more with it and 4 that much less (2178 x 3264 x 1408 in bfloat16 33 -> 44, 7143 x 2880 x 3840 177 ->
 // 192); with shorter rows it is the other way round (59 sizes: 4 and 33, 860 x 7104 x 128 0.95 of the larger tile's time).
-enum ExactTile { TILE_256x128, TILE_128x128, TILE_64x128, TILE_128x64, TILE_64x64, TILE_32x64 };
-static ExactTile pick_tile(int n_probs, int M, int N, int K, bool b16, bool kl) {
+// 256 x 256 (plain problems with rows of whole cache lines): one workgroup per unit; because the clock rises where units run out of
+// tiles, a last round costs between its share and a whole one, and an epilogue counts for more the fewer slabs a tile has.  It is taken
+// where it promises 6 %.  Of 277 random plain sizes (60 to 5000 such tiles) in codes 129 take it: 0.75 to 1.07 of the others' time, mean
+// 0.89, four of them more than 1.03 (short rows with a residual); without the 6 % nine of 162 would.  In bfloat16 153 of 223, 0.51 to
+// 1.09, mean 0.77, three above 1.03.  One-slab rows (K = 128: 0.88 to 1.15) never do.
+enum ExactTile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_64x128, TILE_128x64, TILE_64x64, TILE_32x64 };
+static ExactTile pick_tile(int n_probs, int M, int N, int K, bool b16, bool kl, bool wide) {
   auto per_cu = [&](int bm, int bn) {
     const long long t = (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * n_probs;
     return (double)((t + 255) / 256);
@@ -798,17 +1036,23 @@ static ExactTile pick_tile(int n_probs, int M, int N, int K, bool b16, bool kl) 
   ExactTile best = narrow ? TILE_128x64 : TILE_128x128;
   double r = narrow ? per_cu(128, 64) : per_cu(128, 128);
   double cost = narrow ? 0.37 + 0.48 * r : 0.5 + 0.85 * r;
+  bool large = false;
   if (!narrow && !b16 && !kl && M >= 8192 && N >= 128) {
     const double rp = per_cu(256, 128);
-    if (rp >= 5) return TILE_256x128;
-    if (0.1 + 1.8 * rp <= cost) { best = TILE_256x128; r = rp; cost = 0.1 + 1.8 * rp; }
+    if (rp >= 5 || 0.1 + 1.8 * rp <= cost) { best = TILE_256x128; r = rp; cost = 0.1 + 1.8 * rp; large = rp >= 5; }
   }
-  if (r > 1 && K > 1024) cost *= 0.94;
-  auto consider = [&](ExactTile t, double c) { if (c < cost) { best = t; cost = c; } };
-  if (!narrow) consider(TILE_64x128, 0.37 + 0.48 * per_cu(64, 128));
-  if (!kl) {           // (the parts of a row of the KL epilogue are 64 columns of one wave)
-    consider(TILE_64x64, 0.3 + 0.26 * per_cu(64, 64));
-    consider(TILE_32x64, 0.27 + 0.17 * per_cu(32, 64));
+  if (!large) {
+    if (r > 1 && K > 1024) cost *= 0.94;
+    auto consider = [&](ExactTile t, double c) { if (c < cost) { best = t; cost = c; } };
+    if (!narrow) consider(TILE_64x128, 0.37 + 0.48 * per_cu(64, 128));
+    if (!kl) {         // (the parts of a row of the KL epilogue are 64 columns of one wave)
+      consider(TILE_64x64, 0.3 + 0.26 * per_cu(64, 64));
+      consider(TILE_32x64, 0.27 + 0.17 * per_cu(32, 64));
+    }
+  }
+  if (wide && K >= 256) {
+    const double t = (double)((M + 255) / 256) * ((N + 255) / 256) * n_probs / 256;
+    if (0.6 + (b16 ? 1.2 + 40.0 / K : 1.25 + 120.0 / K) * (std::ceil(t) + t) <= 0.94 * cost) best = TILE_256x256;
   }
   return best;
 }
@@ -843,36 +1087,43 @@ static hipError_t launch_tile(ExactTile t, const GemmProb* probs, int n_probs, i
 // (kl_parts_per_row) is derived from.
 hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int b16, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  const ExactTile t = pick_tile(n_probs, max_M, max_N, K, b16 != 0, true);
+  const ExactTile t = pick_tile(n_probs, max_M, max_N, K, b16 != 0, true, false);
   return b16 ? launch_tile<true>(t, probs, n_probs, max_M, max_N, s) : launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
 }
 
-hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, hipStream_t s) {
+// The kernels of one workgroup per compute unit use more LDS than a launch gets by default.  The attribute belongs to the
+// kernel's code object on one device: set once per device (atomically, so that models on several streams or host threads may
+// launch concurrently).
+static hipError_t launch_one_per_cu(const void* kernel, std::atomic<bool>* set, int lds_bytes, int tiles, int n_probs,
+                                    const GemmProb* probs, hipStream_t s) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!set[dev].load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+    set[dev].store(true, std::memory_order_release);
+  }
+  void* args[] = {(void*)&probs};
+  return hipLaunchKernel(kernel, dim3(std::min((tiles + 7) / 8 * 8, 256), n_probs), dim3(512), args, lds_bytes, s);
+}
+template <bool B16>
+static hipError_t launch_w(const GemmProb* probs, int n_probs, int M, int N, hipStream_t s) {
+  static std::atomic<bool> set[64];
+  return launch_one_per_cu((const void*)gemm_w_k<B16>, set, 2 * 512 * 128 + 2 * 768 * 4, ((M + 255) / 256) * ((N + 255) / 256), n_probs, probs, s);
+}
+
+hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, bool wide, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  // bfloat16 operands: exact sums only (and no three-stage kernel)
-  if (b16) return exact ? launch_tile<true>(pick_tile(n_probs, max_M, max_N, K, true, false), probs, n_probs, max_M, max_N, s) : hipErrorInvalidValue;
+  if (b16 && !exact) return hipErrorInvalidValue;        // bfloat16 operands: exact sums only
   if (exact) {
-    const ExactTile t = pick_tile(n_probs, max_M, max_N, K, false, false);
+    const ExactTile t = pick_tile(n_probs, max_M, max_N, K, b16 != 0, false, wide);
+    if (t == TILE_256x256) return b16 ? launch_w<true>(probs, n_probs, max_M, max_N, s) : launch_w<false>(probs, n_probs, max_M, max_N, s);
     if (t == TILE_256x128) {
-      // one 512-thread workgroup per compute unit, three 48 KB stages + 2 KB of scales
-      const int lds_bytes = 3 * 384 * 128 + 2048;
-      // the attribute belongs to the kernel's code object on one device: set once per device (atomically, so that
-      // models on several streams or host threads may launch concurrently)
-      static std::atomic<bool> attr_set[64];
-      int dev = 0;
-      if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-      if (!attr_set[dev].load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_p_k<0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        if (e != hipSuccess) return e;
-        attr_set[dev].store(true, std::memory_order_release);
-      }
-      int tiles = ((max_M + 255) / 256) * ((max_N + 127) / 128);
-      int gx = (tiles + 7) / 8 * 8;
-      if (gx > 256) gx = 256;
-      hipLaunchKernelGGL((gemm_p_k<0>), dim3(gx, n_probs), dim3(512), lds_bytes, s, probs);
-      return hipGetLastError();
+      // three 48 KB stages + 2 KB of scales
+      static std::atomic<bool> set[64];
+      return launch_one_per_cu((const void*)gemm_p_k<0>, set, 3 * 384 * 128 + 2048, ((max_M + 255) / 256) * ((max_N + 127) / 128), n_probs, probs, s);
     }
-    return launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
+    return b16 ? launch_tile<true>(t, probs, n_probs, max_M, max_N, s) : launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
   } else {
     int tiles = ((max_M + 127) / 128) * ((max_N + 63) / 64);
     dim3 grid((tiles + 7) / 8 * 8, n_probs);

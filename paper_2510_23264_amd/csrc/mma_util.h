@@ -84,6 +84,15 @@ __device__ __forceinline__ void slab_load16(const uint8_t* g, uint32_t lds_addr)
 __device__ __forceinline__ void lds_load4(const void* g, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(lds_addr) : "memory");
 }
+// The same with a wave-uniform address and a 32-bit offset per lane.  The address may have been written by the vector ALU (a
+// lane of a spilled register read back) just in front of the block, and a load may read such a register five wait states later
+// at the earliest; the compiler does not count them for assembly.
+__device__ __forceinline__ void slab_load16s(const uint8_t* g, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(g), "s"(lds_addr) : "memory");
+}
+__device__ __forceinline__ void lds_load4s(const float* g, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(g), "s"(lds_addr) : "memory");
+}
 // at most N vector-memory operations of this wave still outstanding (they retire in issue order)
 template <int N>
 __device__ __forceinline__ void wait_vm() {

@@ -37,6 +37,38 @@ def test_every_tile_gives_the_same_bits(model, n, k, rows):
     assert (np.abs(out[0][ends] - exact) <= k * 2.0 ** -24 * mag).all()      # k additions of binary32
 
 
+# Plain problems of enough tiles take 256 x 256, whose tiles at the edges overlap their neighbours: by all rows but one (32513 = 127 * 256
+# + 1), by one row and 32 columns, by one row and half the columns.  Smaller numbers of rows take other tiles.
+@pytest.mark.parametrize("n,k,rows", [(512, 768, (32513, 8193, 300)), (480, 896, (30207, 2000, 1)), (640, 768, (21759, 9000, 77))])
+def test_overlapping_tiles_give_the_same_bits(model, n, k, rows):
+    test_every_tile_gives_the_same_bits(model, n, k, rows)
+
+
+@pytest.mark.parametrize("options", [dict(), dict(nonattn_bf16=True)])
+def test_scores_do_not_depend_on_the_tile_of_a_batch(options):
+    """224 candidates have 26888 rows: the MLP's products of 1280 and 512 columns (the second with a residual) are 256 x 256 tiles
+    then, others with 24 and with one."""
+    import paper_2510_23264_amd as P
+    B, S, V = 8, 16, 600
+    shape = synth.ModelShape(n_layers=2, n_heads=4, d_head=64, d_model=512, d_mlp=1280, vocab=V, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 6, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(6)
+    clean = rng.integers(0, V, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, V - 1, (B, 5))) % V
+    out = []
+    for batch in (224, 24, 1):
+        gm = P.Model(shape, w, B, S, max_batch_edges=batch, **options)
+        try:
+            gm.clean_cache(clean, corrupt)
+            r = 3 * 4
+            out.append(gm.eval_edges(r, np.resize(np.arange(P.n_upstream(gm.cfg, r), dtype=np.int32), 224)[:batch]))
+        finally:
+            gm.close()
+    for got in out:
+        assert np.isfinite(got).all() and np.array_equal(got.view(np.uint32), out[0][:got.size].view(np.uint32))
+
+
 @pytest.mark.parametrize("options", [dict(), dict(nonattn_bf16=True), dict(low_bits=16)])
 def test_scores_across_the_tiles_of_one_and_two_bytes(options):
     """Scores by batch where the same layer's products take other tiles, in one-byte codes and in bfloat16: with 48, 24 and 1
