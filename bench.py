@@ -47,7 +47,7 @@ KERNELS_OF_CLASS = {
     "gather_norm_quant": ("pahq::build_inputs_k", "pahq::build_inputs_shared_k"),
     "hidden_quant": ("pahq::hidden_quant_vec_k", "pahq::hidden_quant_k"),
     "attention": ("pahq::attention_mfma_k", "pahq::attention_qtile_k"),
-    "oproj_fused": ("pahq::oproj_x_k", "pahq::oproj_fused_k"),
+    "oproj_fused": ("pahq::oproj_w_k", "pahq::oproj_x_k", "pahq::oproj_fused_k"),
     "gemm_f32": ("pahq::gemm_f32_x_k", "pahq::gemm_f32_heads_k", "pahq::gemm_f32_k"),
     "edge_patch": ("pahq::patch_indep_k", "pahq::patch_build_k"),
     "kl": ("pahq::kl_reduce_k", "pahq::kl_mean_k"),

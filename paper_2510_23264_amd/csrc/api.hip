@@ -72,6 +72,9 @@ void set_dims(pahq_model* M, const pahq_config* c, int B, int S) {
   if (M->qbits == 16) {        // bfloat16 operands for the heads too: their rows take two bytes per element
     M->Kd = pad128(2 * M->d); M->Kh = pad128(2 * M->dh);
   }
+  const int hb = M->dh * (M->qbits == 16 ? 2 : 1);
+  M->side_by_side = oproj_side_by_side(M->H, hb, M->d, c->mma == PAHQ_MMA_F16_EXACT);
+  M->Kz = M->side_by_side ? hb : M->Kh;
   M->Kd_o = M->nb16 ? pad128(2 * M->d) : M->Kd;
   M->Km_o = M->nb16 ? pad128(2 * (M->m > 0 ? M->m : 1)) : M->Km;
   M->deadsum_tag.assign(M->L, -1);
@@ -125,7 +128,7 @@ size_t layout(pahq_model* M, char* base) {
   M->rope_tab = M->cfg.pos == PAHQ_POS_ROPE ? b.take<float>((size_t)128 * dh) : nullptr;   // the attention kernels' (up to eight) 16-position tiles
   M->bqkv = b.take<float>(L * 3 * H * dh);
   M->qkv_codes = b.take<uint8_t>(L * 3 * H * dh * Kd); M->qkv_scale = b.take<float>(L * 3 * H);
-  M->o_codes = b.take<uint8_t>(L * H * d * Kh); M->o_scale = b.take<float>(L * H);
+  M->o_codes = b.take<uint8_t>(L * H * d * M->Kz); M->o_scale = b.take<float>(L * H);
   M->in_codes = mlp ? b.take<uint8_t>(L * m * Kdo) : nullptr; M->in_scale = mlp ? b.take<float>(L) : nullptr;
   M->gate_codes = (mlp && swi) ? b.take<uint8_t>(L * m * Kdo) : nullptr;
   M->gate_scale = (mlp && swi) ? b.take<float>(L) : nullptr;
@@ -145,7 +148,7 @@ size_t layout(pahq_model* M, char* base) {
   M->run_a = b.take<float>(n * tile); M->run_b = b.take<float>(n * tile);
   M->xcodes = b.take<uint8_t>(n * G * T * Kd); M->xscale = b.take<float>(n * G * T); M->xf32 = b.take<float>(std::max<size_t>(n * (size_t)M->f32_groups, 3 * H) * tile);
   M->qkv = b.take<float>(n * T * 3 * H * dh);
-  M->zcodes = b.take<uint8_t>(n * T * H * Kh); M->zscale = b.take<float>(n * T * H); M->zf32 = b.take<float>(std::max<size_t>(n * (size_t)M->f32_heads_max, H) * T * dh);
+  M->zcodes = b.take<uint8_t>(n * T * H * M->Kz); M->zscale = b.take<float>(n * T * H); M->zf32 = b.take<float>(std::max<size_t>(n * (size_t)M->f32_heads_max, H) * T * dh);
   M->headout = b.take<float>(n * H * tile);
   M->mlpout = mlp ? b.take<float>(n * tile) : nullptr;
   M->hid = mlp ? b.take<float>(n * T * m) : nullptr; M->hid2 = (mlp && swi) ? b.take<float>(n * T * m) : nullptr;
@@ -473,7 +476,7 @@ int pahq_init_model(const pahq_config* c, const pahq_weights* w, int32_t B, int3
     if (rc == PAHQ_OK) {
       const float* src = staged(on_host ? nullptr : M->W_O + l * H * dh * d, w->W_O + l * H * dh * d, H * dh * d);
       if (rc == PAHQ_OK)
-        rc = quantise_class(M, src, (int)H, (int)dh, (int)d, M->o_codes + l * H * d * M->Kh, (long long)d * M->Kh, M->Kh, M->o_scale + l * H, 1, M->qbits);
+        rc = quantise_class(M, src, (int)H, (int)dh, (int)d, M->o_codes + o_codes_at(M, (int)l, 0), o_codes_at(M, 0, 1), o_codes_ld(M), M->o_scale + l * H, 1, M->qbits);
     }
     if (mlp && rc == PAHQ_OK) {
       const float* src = staged(on_host ? nullptr : M->W_in + l * d * m, w->W_in + l * d * m, d * m);
@@ -992,7 +995,7 @@ int pahq_get_weight_q(pahq_model* M, int32_t which, int32_t layer, int32_t head,
       K = d; N = dh; ldq = M->Kd;
       src = M->qkv_codes + ((long long)layer * 3 * H * dh + ((long long)cc * H + head) * dh) * M->Kd;
       ssrc = M->qkv_scale + (long long)layer * 3 * H + cc * H + head; break; }
-    case PAHQ_W_O: K = dh; N = d; ldq = M->Kh; src = M->o_codes + ((long long)layer * H + head) * d * M->Kh; ssrc = M->o_scale + layer * H + head; break;
+    case PAHQ_W_O: K = dh; N = d; ldq = o_codes_ld(M); src = M->o_codes + o_codes_at(M, layer, head); ssrc = M->o_scale + layer * H + head; break;
     case PAHQ_W_IN: K = d; N = m; ldq = M->Kd; src = M->in_codes + (long long)layer * m * M->Kd; ssrc = M->in_scale + layer; break;
     case PAHQ_W_GATE: if (!M->gate_codes) return PAHQ_EINVAL;
       K = d; N = m; ldq = M->Kd; src = M->gate_codes + (long long)layer * m * M->Kd; ssrc = M->gate_scale + layer; break;
@@ -1000,7 +1003,7 @@ int pahq_get_weight_q(pahq_model* M, int32_t which, int32_t layer, int32_t head,
     case PAHQ_W_U: K = d; N = V; ldq = M->Kd; src = M->u_codes; ssrc = M->u_scale; break;
     default: return PAHQ_EINVAL;
   }
-  std::vector<uint8_t> tmp((size_t)N * ldq);
+  std::vector<uint8_t> tmp((size_t)(N - 1) * ldq + K);
   HIPCHK(hipMemcpyAsync(tmp.data(), src, tmp.size(), hipMemcpyDeviceToHost, M->stream));
   HIPCHK(hipMemcpyAsync(scale, ssrc, sizeof(float), hipMemcpyDeviceToHost, M->stream));
   HIPCHK(hipStreamSynchronize(M->stream));
@@ -1024,7 +1027,7 @@ int pahq_get_weight_bf16(pahq_model* M, int32_t which, int32_t layer, int32_t he
       const int cc = which - PAHQ_W_Q;
       K = d; N = dh; ldq = M->Kd;
       src = M->qkv_codes + ((long long)layer * 3 * H * dh + ((long long)cc * H + head) * dh) * M->Kd; break; }
-    case PAHQ_W_O: K = dh; N = d; ldq = M->Kh; src = M->o_codes + ((long long)layer * H + head) * d * M->Kh; break;
+    case PAHQ_W_O: K = dh; N = d; ldq = o_codes_ld(M); src = M->o_codes + o_codes_at(M, layer, head); break;
     case PAHQ_W_IN: K = d; N = m; ldq = M->Kd_o; src = M->in_codes + (long long)layer * m * ldq; break;
     case PAHQ_W_GATE: if (!M->gate_codes) return PAHQ_EINVAL;
       K = d; N = m; ldq = M->Kd_o; src = M->gate_codes + (long long)layer * m * ldq; break;
@@ -1032,7 +1035,7 @@ int pahq_get_weight_bf16(pahq_model* M, int32_t which, int32_t layer, int32_t he
     case PAHQ_W_U: K = d; N = V; ldq = M->Kd_o; src = M->u_codes; break;
     default: return PAHQ_EINVAL;
   }
-  std::vector<uint8_t> tmp((size_t)N * ldq);
+  std::vector<uint8_t> tmp((size_t)(N - 1) * ldq + 2 * (size_t)K);
   HIPCHK(hipMemcpyAsync(tmp.data(), src, tmp.size(), hipMemcpyDeviceToHost, M->stream));
   HIPCHK(hipStreamSynchronize(M->stream));
   for (int k = 0; k < K; k++)

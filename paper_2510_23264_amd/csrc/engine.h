@@ -60,6 +60,8 @@ struct pahq_model {
   pahq::GraphDims g;
   int B, S, T, L, H, dh, d, m, V;
   int Kd, Kh, Km;        // K extents padded to multiples of 128
+  int Kz;                // bytes of a head in a row of attention outputs: those of its codes where oproj_x_k takes them (heads side by side), else Kh
+  bool side_by_side;     // W_O's codes lie like those rows: [d][H * Kz] instead of [H][d][Kh]
   int Vp;                // row stride of logits buffers (vocab rounded up to 4 floats)
   int nmax, G;           // max instances; max groups per layer (3H + 1)
   long long tile;        // T * d
@@ -165,4 +167,10 @@ int w32_acquire(pahq_model* M, int l, unsigned long long mask);     // before th
 int w32_release(pahq_model* M, int l, unsigned long long mask);     // behind the last
 int w32_prefetch(pahq_model* M, int l, unsigned long long mask);    // expected next: starts the transfers, waits for nothing
 int prof_harvest(pahq_model* M);     // synchronises the stream and folds recorded event pairs into M->prof
+// W_O's codes: bytes from one output column to the next, and where head h of layer l begins
+inline int o_codes_ld(const pahq_model* M) { return M->side_by_side ? M->H * M->Kz : M->Kh; }
+inline long long o_codes_at(const pahq_model* M, int l, int h) {
+  return (long long)l * M->H * M->d * M->Kz + (long long)h * (M->side_by_side ? M->Kz : (long long)M->d * M->Kh);
+}
+
 }  // namespace pahq

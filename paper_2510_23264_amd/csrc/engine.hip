@@ -436,7 +436,7 @@ struct Builder {
   // launch for launch what the single-head reference pass (attention_block with that one head in fp32) does, with the
   // same kernels on the same operands, so the two give the same bits.
   void ref_layer_block(int l, Stream& run) {
-    const int H = M->H, dh = M->dh, d = M->d, T = M->T, Kd = M->Kd, Kh = M->Kh;
+    const int H = M->H, dh = M->dh, d = M->d, T = M->T, Kd = M->Kd;
     const unsigned long long all_heads = H >= 64 ? ~0ull : ((1ull << H) - 1ull);
     const long long qkv_ld = 3LL * H * dh;
     const bool last = last_rows(l);
@@ -491,12 +491,12 @@ struct Builder {
     Stream nxt = next_run(2 * l + 1, run.p == M->run_a ? M->run_b : M->run_a);
     for (int h = 0; h < H; h++) {
       OprojDesc od; memset(&od, 0, sizeof(od));
-      od.zc = M->zcodes + last_off(last, (long long)H * Kh); od.zc_is = (long long)T * H * Kh;
+      od.zc = M->zcodes + last_off(last, (long long)H * M->Kz); od.zc_is = (long long)T * H * M->Kz;
       od.zs = M->zscale + last_off(last, H); od.zs_is = (long long)T * H;
-      od.W = M->o_codes + (long long)l * H * d * Kh; od.ws = M->o_scale + (long long)l * H;
+      od.W = M->o_codes + o_codes_at(M, l, 0); od.w_ld = o_codes_ld(M); od.w_hs = o_codes_at(M, 0, 1); od.ws = M->o_scale + (long long)l * H;
       od.run_in = run.p + lo; od.run_in_is = run.is; od.run_out = nxt.p + (long long)h * nxt.is + lo; od.run_out_is = nxt.is;
       od.bias = M->b_O + (long long)l * d;
-      od.H = H; od.Kh = Kh; od.skip_mask = 1ull << h; od.rpi = od.M = last ? M->B : T; od.N = d;
+      od.H = H; od.Kz = M->Kz; od.skip_mask = 1ull << h; od.rpi = od.M = last ? M->B : T; od.N = d;
       od.aux_begin = -1; od.dh = M->dh;
       od.extra = M->headout + (long long)h * M->tile + lo; od.extra_is = M->tile;
       odescs.push_back(od);
@@ -508,7 +508,7 @@ struct Builder {
 
   void attention_block(int l, Stream& run) {
     const GraphDims& g = M->g;
-    const int H = M->H, dh = M->dh, d = M->d, T = M->T, Kd = M->Kd, Kh = M->Kh;
+    const int H = M->H, dh = M->dh, d = M->d, T = M->T, Kd = M->Kd;
     const unsigned long long all_heads = H >= 64 ? ~0ull : ((1ull << H) - 1ull);
     const unsigned long long dead = dead_heads(l);             // heads of this layer that are not computed at all
     const unsigned long long fmask = mask_of(l) & ~dead;       // live heads of this layer computed in fp32
@@ -652,12 +652,12 @@ struct Builder {
     if (prefix) { nxt.p = M->oth; nxt.is = 0; }       // stream + bias + every head but the investigated one
     const bool store_raw = (a.kind == BASE_CLEAN || a.kind == BASE_CORRUPT || a.kind == PI_CORRUPT);
     OprojDesc od; memset(&od, 0, sizeof(od));
-    od.zc = M->zcodes + last_off(last, (long long)H * Kh); od.zc_is = inst_stride((long long)H * Kh);
+    od.zc = M->zcodes + last_off(last, (long long)H * M->Kz); od.zc_is = inst_stride((long long)H * M->Kz);
     od.zs = M->zscale + last_off(last, H); od.zs_is = inst_stride(H);
-    od.W = M->o_codes + (long long)l * H * d * Kh; od.ws = M->o_scale + (long long)l * H;
+    od.W = M->o_codes + o_codes_at(M, l, 0); od.w_ld = o_codes_ld(M); od.w_hs = o_codes_at(M, 0, 1); od.ws = M->o_scale + (long long)l * H;
     od.run_in = run.p + lo; od.run_in_is = run.is; od.run_out = nxt.p + lo; od.run_out_is = nxt.is;
     od.bias = M->b_O + (long long)l * d;
-    od.H = H; od.Kh = Kh; od.skip_mask = off8; od.rpi = last ? M->B : rpi; od.rp0 = last ? 0 : rp0; od.M = rows(last); od.N = d;
+    od.H = H; od.Kz = M->Kz; od.skip_mask = off8; od.rpi = last ? M->B : rpi; od.rp0 = last ? 0 : rp0; od.M = rows(last); od.N = d;
     od.aux_begin = -1; od.dh = M->dh;
     od.extra = deadsum ? deadsum + lo : nullptr; od.extra_is = 0;              // replaced below when fp32 heads are chained in front of it
     bool any_aux = false;
@@ -1082,12 +1082,12 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
       case OP_ATTN: {
         // o.i2 instances (0: all of the pass)
         HIPCHK(launch_attention(b.asrcs[o.i0], M->zcodes, M->zscale, M->zf32, o.u64, o.u64b, o.i2 ? o.i2 : n, B, S, M->H,
-                                M->dh, M->Kh, M->cfg.pos == PAHQ_POS_ROPE, M->rope_tab, st));
+                                M->dh, M->Kz, M->cfg.pos == PAHQ_POS_ROPE, M->rope_tab, st));
         break;
       }
       case OP_COMBINE: HIPCHK(launch_combine(d_cdesc, o.i0, d_csrc, o.i1 ? 1 : n, M->tile, (long long)b.rp0 * d, d, st)); break;
       case OP_OPROJ:
-        HIPCHK(launch_oproj_fused(d_odesc, o.i0, d_haux, o.i1, o.i2, M->H, M->dh, M->cfg.mma == PAHQ_MMA_F16_EXACT, M->qbits == 16, st));
+        HIPCHK(launch_oproj_fused(d_odesc, o.i0, b.odescs[o.i0].aux_begin < 0 ? nullptr : d_haux, o.i1, o.i2, M->H, M->dh, M->cfg.mma == PAHQ_MMA_F16_EXACT, M->qbits == 16, st));
         break;
       case OP_HIDQ:
         // the rows of all instances lie side by side: o.i1 of them

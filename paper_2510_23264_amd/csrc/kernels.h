@@ -119,17 +119,24 @@ struct CombineDesc {
 // Fused output projection + stream update of one layer (see oproj.hip).
 struct HeadAux { float* dst; long long dst_is; const float* sub; };   // per head: dst = out_h - sub (sub may be null)
 struct OprojDesc {
-  const uint8_t* zc;  long long zc_is;      // attention outputs, codes [inst][rpi][H][Kh]
+  const uint8_t* zc;  long long zc_is;      // attention outputs, codes [inst][rpi][H][Kz]
   const float* zs;    long long zs_is;      // their scales [inst][rpi][H]
-  const uint8_t* W;   const float* ws;      // W_O codes [H][N][Kh], scales [H]
+  const uint8_t* W;   const float* ws;      // W_O codes (row n of head h at h w_hs + n w_ld), scales [H]
+  long long w_hs; int w_ld, Kz;             // Kz: bytes from one head of a row to the next
   const float* extra; long long extra_is;   // fp32 head's output [inst][rpi][N] or null
   const float* run_in; long long run_in_is;
   float* run_out;      long long run_out_is;
   const float* bias;                        // [N] or null
-  int H, Kh, rpi, rp0;                      // rows of an instance, rows of instance 0 in front of them (as in GemmProb)
-  int M, N, aux_begin, dh;                  // M = rows over all instances; aux_begin: first of H HeadAux, or -1; dh = d_head (Kh = dh padded to 128)
+  int H, rpi, rp0;                          // rows of an instance, rows of instance 0 in front of them (as in GemmProb)
+  int M, N, aux_begin, dh;                  // M = rows over all instances; aux_begin: first of H HeadAux, or -1; dh = d_head
   unsigned long long skip_mask;             // bit h set: head h is computed in fp32 elsewhere (it arrives in `extra`)
 };
+
+// Whether a layer's heads (H of hb code bytes, output width d) go to oproj_x_k, which takes the heads of a row side by side without
+// padding and W_O's codes alike: a slab of 128 bytes of K is then one cache line of both.
+inline bool oproj_side_by_side(int H, int hb, int d, bool exact) {
+  return exact && (hb == 64 || hb == 128) && d % 4 == 0 && H % (128 / hb) == 0 && H <= 64;
+}
 
 // ---- launchers ---------------------------------------------------------------
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
@@ -186,6 +193,7 @@ hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int ma
 // C = (run_in + bias) + (add + sum over heads of A_h W_h), each head's own product to its aux (see gemm.hip); run_in may be null
 hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int N, const float* run_in, long long run_is,
                                  const float* bias, hipStream_t s);
+// auxs: null if the descriptor asks for no per-head results (aux_begin < 0)
 hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const HeadAux* auxs, int M, int N, int H, int dh,
                               int exact, int b16, hipStream_t s);
 

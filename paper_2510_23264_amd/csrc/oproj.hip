@@ -12,6 +12,7 @@
 #include "device_util.h"
 #include "mma_util.h"
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 namespace pahq {
@@ -40,12 +41,12 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
   for (int c = 0; c < 4; c++) {
     int m = m0 + (tid >> 3) + 32 * c;
     int inst, row; row_origin(m, D.rpi, D.rp0, inst, row);
-    pa[c] = (m < D.M) ? D.zc + (long long)inst * D.zc_is + (long long)row * D.H * D.Kh + kc * 16 : nullptr;
+    pa[c] = (m < D.M) ? D.zc + (long long)inst * D.zc_is + (long long)row * D.H * D.Kz + kc * 16 : nullptr;
   }
 #pragma unroll
   for (int c = 0; c < 2; c++) {
     int n = n0 + (tid >> 3) + 32 * c;
-    pb[c] = (n < D.N) ? D.W + (long long)n * D.Kh + kc * 16 : nullptr;
+    pb[c] = (n < D.N) ? D.W + (long long)n * D.w_ld + kc * 16 : nullptr;
   }
   uint4 ra[4], rb[2];
   // codes beyond d_head are zero padding: neither loaded nor (with the fp16 matrix cores) multiplied
@@ -54,10 +55,10 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
   auto load_head = [&](int h) {
 #pragma unroll
     for (int c = 0; c < 4; c++)
-      ra[c] = (pa[c] && real_chunk) ? *(const uint4*)(pa[c] + (long long)h * D.Kh) : make_uint4(0, 0, 0, 0);
+      ra[c] = (pa[c] && real_chunk) ? *(const uint4*)(pa[c] + (long long)h * D.Kz) : make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int c = 0; c < 2; c++)
-      rb[c] = (pb[c] && real_chunk) ? *(const uint4*)(pb[c] + (long long)h * D.N * D.Kh) : make_uint4(0, 0, 0, 0);
+      rb[c] = (pb[c] && real_chunk) ? *(const uint4*)(pb[c] + h * D.w_hs) : make_uint4(0, 0, 0, 0);
   };
   auto skipped = [&](int h) { return ((D.skip_mask >> h) & 1ull) != 0; };
   auto next_head = [&](int h) { h++; while (h < D.H && skipped(h)) h++; return h; };
@@ -210,7 +211,6 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
   constexpr int BN = 64, TM = BM == 128 ? 2 : 1, TN = 2, NI = 3, NS = OPX_STAGES, STAGE = opx_stage(BM);
   static_assert(BM == 128 || BM == 32, "waves: BM / (16 TM) x 2, three loads each");
   constexpr int HPS = 128 / DH;            // heads per slab
-  constexpr int CPH = 8 / HPS;             // 16-byte chunks per head
   static_assert(NI + 1 == 4, "four loads per slab and wave: the wait counts below assume it");
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const float* const e_ws = (const float*)(smem + NS * STAGE);
@@ -227,22 +227,19 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
   const uint32_t lds0 = lds_addr_of(smem);
 
   // lane l of a load instruction fills LDS row l >> 3, chunk position l & 7, i.e. logical chunk
-  // c = (l & 7) ^ (l >> 3) of the slab: head c / CPH of the slab, bytes 16 (c % CPH) of that head
+  // c = (l & 7) ^ (l >> 3) of the slab
   const int c = (lane & 7) ^ (lane >> 3);
   const uint8_t* src[NI];
-  long long stride[NI];                    // bytes from one slab to the next: activation or weight rows
 #pragma unroll
   for (int t = 0; t < NI; t++) {
     int r = 8 * (wave * NI + t) + (lane >> 3);
     if (r < BM) {
       int m = min(m0 + r, D.M - 1), inst, row;
       row_origin(m, D.rpi, D.rp0, inst, row);
-      src[t] = D.zc + (long long)inst * D.zc_is + (long long)row * D.H * D.Kh + (long long)(c / CPH) * D.Kh + (c % CPH) * 16;
-      stride[t] = (long long)HPS * D.Kh;
+      src[t] = D.zc + (long long)inst * D.zc_is + (long long)row * D.H * DH + c * 16;
     } else {
       int n = min(n0 + r - BM, D.N - 1);
-      src[t] = D.W + (long long)n * D.Kh + (long long)(c / CPH) * D.N * D.Kh + (c % CPH) * 16;
-      stride[t] = (long long)HPS * D.N * D.Kh;
+      src[t] = D.W + (long long)n * D.w_ld + c * 16;
     }
   }
   // row scales of a slab: entry [q][r] (head q of the slab, tile row r) is lane's if 64 wave + lane = BM q + r;
@@ -260,7 +257,7 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
     const uint32_t st = lds0 + si * STAGE;
     const uint32_t base = __builtin_amdgcn_readfirstlane(st + wave * NI * 1024);
 #pragma unroll
-    for (int t = 0; t < NI; t++) { slab_load16(src[t], base + t * 1024); src[t] += stride[t]; }
+    for (int t = 0; t < NI; t++) { slab_load16(src[t], base + t * 1024); src[t] += 128; }
     lds_load4(zsrc, __builtin_amdgcn_readfirstlane(st + opx_oper(BM) + (wave & 3) * 256));
     zsrc += HPS;
     si = (si == NS - 1) ? 0 : si + 1;
@@ -411,6 +408,156 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
   }
 }
 
+// The same projection for many rows without per-head results: 128 x 128 tile, four wavefronts of 64 x 64, two stages of 32 KB, two
+// workgroups per compute unit, so that one multiplies while the other reads and writes its stream tile.  It moves 0.7 GB of stream for 0.08 of codes (100 000 rows
+// of 768, 12 heads) and is bound by that: 318 -> 239 us, 3.3 TB/s.  Against the kernel above an operand is read half as often from
+// L2, a wave's conversions serve twice the products, and a lane's four columns are neighbours, so that 16 lanes read and write 256
+// bytes of a row of the stream instead of four lanes 64.  24 600 rows of 1024, 16 heads: 133 -> 100 us; 4096 rows of 4096, 32 heads of 128:
+// 190 -> 155.  Loading part or all of the stream tile in front of the last products gains nothing (252 us; 269 with half of it).
+// Same sums in the same order.
+template <int DH, bool B16>
+__global__ __launch_bounds__(256, 2) void oproj_w_k(const OprojDesc* descs, int di) {
+  constexpr int BM = 128, BN = 128, TM = 4, TN = 4, NI = 8, HPS = 128 / DH;
+  constexpr int OPER = (BM + BN) * 128, STAGE = OPER + HPS * BM * 4;         // operands, row scales [heads of the slab][BM]
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * STAGE + 256 + BM * 8];
+  float* const e_ws = (float*)(smem + 2 * STAGE);                            // weight scales [64]
+  int2* const e_row = (int2*)(smem + 2 * STAGE + 256);                       // a tile row's instance and element offset in it
+  const OprojDesc D = descs[di];
+  const int mt = (D.M + BM - 1) / BM, nt = (D.N + BN - 1) / BN;
+  const int lin = xcd_tile(blockIdx.x, mt * nt);
+  if (lin >= mt * nt) return;
+  const int m0 = (lin / nt) * BM, n0 = (lin % nt) * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int li = lane & 15, lg = lane >> 4;
+  const int nslab = D.H / HPS;
+  const uint32_t lds0 = lds_addr_of(smem);
+  int i0, r0; row_origin(m0, D.rpi, D.rp0, i0, r0);
+
+  // load t of a wave: eight rows of A (t < 4) or of W.  LDS row 16 q + i of a 64-row block of W holds row 4 i + q of the block, so
+  // that a lane's accumulators of four 16-column tiles are neighbouring columns.
+  const uint8_t* src[NI];
+  const int c = ((lane & 7) ^ (lane >> 3)) * 16;
+#pragma unroll
+  for (int t = 0; t < NI; t++) {
+    const int r = 8 * (wave * 4 + (t & 3)) + (lane >> 3);
+    if (t < 4) {
+      int inst, row; split_row(i0, r0, min(m0 + r, D.M - 1) - m0, D.rpi, D.rp0, inst, row);
+      src[t] = D.zc + (long long)inst * D.zc_is + (long long)row * D.H * DH + c;
+    } else {
+      src[t] = D.W + (long long)min(n0 + (r & 64) + (r & 15) * 4 + ((r >> 4) & 3), D.N - 1) * D.w_ld + c;
+    }
+  }
+  // row scales of a slab's heads: entry 64 wave + lane = BM q + r is head q's of tile row r (with one head per slab the upper two
+  // waves repeat the rows of the lower two)
+  const float* zsrc;
+  {
+    const int e = wave * 64 + lane;
+    int inst, row; split_row(i0, r0, min(m0 + e % BM, D.M - 1) - m0, D.rpi, D.rp0, inst, row);
+    zsrc = D.zs + (long long)inst * D.zs_is + (long long)row * D.H + (HPS == 2 ? e / BM : 0);
+    if (e < BM) e_row[e] = make_int2(inst, row * D.N);
+  }
+  auto issue = [&](int stage) {
+    const uint32_t st = lds0 + stage * STAGE;
+    const uint32_t a = __builtin_amdgcn_readfirstlane(st + wave * 4096);
+#pragma unroll
+    for (int t = 0; t < NI; t++) { slab_load16(src[t], a + (t < 4 ? 0 : BM * 128) + (t & 3) * 1024); src[t] += 128; }
+    lds_load4(zsrc, __builtin_amdgcn_readfirstlane(st + OPER + (HPS == 2 ? wave : wave & 1) * 256));
+    zsrc += HPS;
+  };
+  lds_load4(D.ws + min(lane, D.H - 1), __builtin_amdgcn_readfirstlane(lds0 + 2 * STAGE));
+  issue(0);
+
+  const int offA = (wm * 64 + li) * 128, offB = (BM + wn * 64 + li) * 128;
+  const int sw0 = (lg ^ (li & 7)) * 16, sw1 = ((4 + lg) ^ (li & 7)) * 16;
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+  v4f tot[TM][TN], acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) tot[i][j] = zero;
+  union U { uint4 u; v8bf h; };
+  for (int s = 0; s < nslab; s++) {
+    wait_vm_barrier<0>();                    // the slab has landed for everyone, the other stage is free
+    if (s + 1 < nslab) issue((s + 1) & 1);
+    const uint8_t* st = smem + (s & 1) * STAGE;
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const int sw = q ? sw1 : sw0;
+      U ra[TM], rb[TN];
+#pragma unroll
+      for (int i = 0; i < TM; i++) ra[i].u = *(const uint4*)(st + offA + i * 2048 + sw);
+#pragma unroll
+      for (int j = 0; j < TN; j++) rb[j].u = *(const uint4*)(st + offB + j * 2048 + sw);
+      const bool first = HPS == 2 || q == 0;
+      if constexpr (B16) {
+#pragma unroll
+        for (int j = 0; j < TN; j++)
+#pragma unroll
+          for (int i = 0; i < TM; i++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra[i].h, rb[j].h, first ? zero : acc[i][j], 0, 0, 0);
+      } else {
+        v8h ha[TM][2];
+#pragma unroll
+        for (int i = 0; i < TM; i++) { ha[i][0] = decode8(ra[i].u.x, ra[i].u.y); ha[i][1] = decode8(ra[i].u.z, ra[i].u.w); }
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          const v8h hb0 = decode8(rb[j].u.x, rb[j].u.y), hb1 = decode8(rb[j].u.z, rb[j].u.w);
+#pragma unroll
+          for (int i = 0; i < TM; i++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha[i][0], hb0, first ? zero : acc[i][j], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < TM; i++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha[i][1], hb1, acc[i][j], 0, 0, 0);
+        }
+      }
+      if (HPS == 1 && q == 0) continue;
+      const int h = HPS == 2 ? 2 * s + q : s;
+      if ((D.skip_mask >> h) & 1ull) continue;             // as in oproj_x_k
+      const float w = e_ws[h];
+      const float* z = (const float*)(st + OPER) + (HPS == 2 ? q * BM : 0) + wm * 64 + lg * 4;
+#pragma unroll
+      for (int i = 0; i < TM; i++) {
+        const float4 zi = *(const float4*)(z + i * 16);
+        const float f[4] = {zi.x * w, zi.y * w, zi.z * w, zi.w * w};
+#pragma unroll
+        for (int j = 0; j < TN; j++)
+#pragma unroll
+          for (int r = 0; r < 4; r++) { const float v = acc[i][j][r] * f[r]; tot[i][j][r] += v; }
+      }
+    }
+  }
+  // next = (stream + bias + sum of the heads) + fp32 head.  tot[i][q][r] of lane (li, lg) is row 64 wm + 16 i + 4 lg + r, column 64 wn + 4 li + q.
+  const int n = n0 + wn * 64 + li * 4;
+  if (n >= D.N) return;
+  const float4 bias = D.bias ? gload4(D.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int i = 0; i < TM; i++) {
+    const int rt = wm * 64 + i * 16 + lg * 4;
+    float4 x[4], e[4];
+    int2 at[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      at[r] = e_row[rt + r];
+      x[r] = gload4(D.run_in + at[r].x * D.run_in_is + at[r].y + n);
+      if (D.extra) e[r] = gload4(D.extra + at[r].x * D.extra_is + at[r].y + n);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      if (m0 + rt + r >= D.M) continue;
+      float4 v = x[r];
+      if (D.bias) { v.x += bias.x; v.y += bias.y; v.z += bias.z; v.w += bias.w; }
+      v.x += tot[i][0][r]; v.y += tot[i][1][r]; v.z += tot[i][2][r]; v.w += tot[i][3][r];
+      if (D.extra) { v.x += e[r].x; v.y += e[r].y; v.z += e[r].z; v.w += e[r].w; }
+      gstore4(D.run_out + at[r].x * D.run_out_is + at[r].y + n, v);
+    }
+  }
+}
+template <int DH, bool B16>
+static hipError_t launch_oproj_w(int M, int N, hipStream_t s, const OprojDesc* descs, int desc_index) {
+  const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  hipLaunchKernelGGL((oproj_w_k<DH, B16>), dim3((tiles + 7) / 8 * 8), dim3(256), 0, s, descs, desc_index);
+  return hipGetLastError();
+}
+
 // The kernel's 75 KB of dynamic LDS need the attribute, which belongs to the kernel's code object on one device:
 // set once per device and instantiation (atomically: models on several streams or host threads may launch at once).
 template <int DH, bool B16, int BM>
@@ -436,8 +583,12 @@ static hipError_t launch_oproj_bm(int M, int N, hipStream_t s, const OprojDesc* 
 // rows over that with 128, means over 1300 random sizes: up to 7 slabs 0.78 at 96 .. 127 tiles, 0.94 at 192 .. 255; from 8 on
 // 0.73 at 96 .. 127, 0.89 at 160 .. 191, 1.04 at 192 .. 255 (1.10 at the worst).  With bfloat16 rows, up to 3 slabs 0.84 and
 // 0.97; from 4 on 0.81, 0.93 and 1.07 (1.47), and from 12 on 1.00 at 128 .. 191 already (1.14).
+// 128 x 128 tiles (oproj_w_k, no per-head results): a round of 512 of them takes 1.5 times one of 128 x 64, a last round between
+// its share and a whole one.  Of 400 random sizes (150 tiles and more) 177 take them, at 0.68 to 1.04 of the other's time, mean 0.83.
 template <int DH, bool B16>
 static hipError_t launch_oproj_x(int M, int N, int H, hipStream_t s, const OprojDesc* descs, int desc_index, const HeadAux* auxs) {
+  auto rounds = [&](int bn) { const double t = (double)((M + 127) / 128) * ((N + bn - 1) / bn) / 512; return 0.5 * (std::ceil(t) + t); };
+  if (!auxs && 0.4 + 1.5 * rounds(128) <= rounds(64)) return launch_oproj_w<DH, B16>(M, N, s, descs, desc_index);
   const int slabs = H * DH / 128, few = slabs < (B16 ? 4 : 8) ? 256 : (!B16 || slabs < 12 ? 192 : 128);
   if (((M + 127) / 128) * ((N + 63) / 64) < few) return launch_oproj_bm<DH, B16, 32>(M, N, s, descs, desc_index, auxs);
   return launch_oproj_bm<DH, B16, 128>(M, N, s, descs, desc_index, auxs);
@@ -450,12 +601,11 @@ hipError_t launch_oproj_fused(const OprojDesc* descs, int desc_index, const Head
   dim3 grid((tiles + 7) / 8 * 8);
   if (b16) {
     // bfloat16 attention outputs: heads of 32 or 64 values (64 or 128 bytes)
-    if (!exact || (dh != 32 && dh != 64) || N % 4 != 0 || H % (64 / dh) != 0) return hipErrorInvalidValue;
-    if (H > 64) return hipErrorInvalidValue;
+    if (!oproj_side_by_side(H, 2 * dh, N, exact != 0)) return hipErrorInvalidValue;
     if (dh == 32) return launch_oproj_x<64, true>(M, N, H, s, descs, desc_index, auxs);
     return launch_oproj_x<128, true>(M, N, H, s, descs, desc_index, auxs);
   }
-  if (exact && (dh == 64 || dh == 128) && N % 4 == 0 && H % (128 / dh) == 0 && H <= 64) {
+  if (oproj_side_by_side(H, dh, N, exact != 0)) {
     if (dh == 64) return launch_oproj_x<64, false>(M, N, H, s, descs, desc_index, auxs);
     return launch_oproj_x<128, false>(M, N, H, s, descs, desc_index, auxs);
   } else if (exact) hipLaunchKernelGGL(oproj_fused_k<true>, grid, dim3(256), 0, s, descs, desc_index, auxs);

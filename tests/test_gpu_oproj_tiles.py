@@ -25,11 +25,32 @@ def takes_128_rows(rows, H, dh, d, options):
     (16, 64, 512, {}, (25, 24)), (2, 128, 704, {}, (25, 24)), (3, 128, 704, {}, (25, 24)), (4, 64, 448, dict(low_bits=4), (39, 38)),
     (4, 64, 448, dict(low_bits=16), (29, 28)), (6, 32, 640, dict(low_bits=16), (27, 26)), (14, 64, 512, dict(low_bits=16), (16, 15))])
 def test_scores_by_batch(H, dh, d, options, batches):
-    import paper_2510_23264_amd as P
     B, S = 8, 16
     large, small = batches
     assert takes_128_rows(B + large * (S - 1) * B, H, dh, d, options)
     assert not takes_128_rows(B + small * (S - 1) * B, H, dh, d, options) and not takes_128_rows(B * S, H, dh, d, options)
+    same_scores(H, dh, d, options, (large, small, 1))
+
+
+def takes_128_columns(rows, d):
+    """The rule of launch_oproj_x for tiles of 128 x 128."""
+    def rounds(bn):
+        t = -(-rows // 128) * -(-d // bn) / 512
+        return 0.5 * (-(-t // 1) + t)
+    return 0.4 + 1.5 * rounds(128) <= rounds(64)
+
+
+#                    whole tiles across; half a tile over; one head a slab; bfloat16 of 64 and of 128 bytes
+@pytest.mark.parametrize("H,dh,d,options,large", [
+    (8, 64, 512, {}, 128), (4, 64, 704, {}, 160), (3, 128, 704, {}, 160), (6, 32, 640, dict(low_bits=16), 176), (3, 64, 512, dict(low_bits=16), 128)])
+def test_scores_by_batch_in_wide_tiles(H, dh, d, options, large):
+    assert takes_128_columns(8 + large * 120, d) and not takes_128_columns(8 + 24 * 120, d)
+    same_scores(H, dh, d, options, (large, 24, 1))
+
+
+def same_scores(H, dh, d, options, batches):
+    import paper_2510_23264_amd as P
+    B, S = 8, 16
     shape = synth.ModelShape(n_layers=3, n_heads=H, d_head=dh, d_model=d, d_mlp=256, vocab=300, n_ctx=S, act=1)
     w = synth.make_weights(shape, 5, std=0.08, affine_std=0.1)
     rng = np.random.default_rng(5)
@@ -37,13 +58,13 @@ def test_scores_by_batch(H, dh, d, options, batches):
     corrupt = clean.copy()
     corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, 299, (B, 5))) % 300
     out = []
-    for batch in (large, small, 1):
+    for batch in batches:
         gm = P.Model(shape, w, B, S, max_batch_edges=batch, **options)
         try:
             gm.clean_cache(clean, corrupt)
             r = 3 * H
             n = P.n_upstream(gm.cfg, r)
-            senders = np.resize(np.arange(n, dtype=np.int32), large)
+            senders = np.resize(np.arange(n, dtype=np.int32), batches[0])
             before = gm.counters()[1]
             out.append(gm.eval_edges(r, senders[:batch]))
             assert gm.counters()[1] == before + 1              # one device batch: the rows above
