@@ -1222,24 +1222,26 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const GemmProb* probs) {
 
 // The fp32 product for K a multiple of 32 and 16-byte aligned rows of A.  Per element the same sum as gemm_f32_k: one
 // V_MFMA_F32_16X16X4_F32 per four k, ascending.  W is the first operand here, so that a lane owns one row and four
-// neighbouring columns (16-byte stores).  Slabs of 32 k go from global memory straight into LDS, two stages, one barrier
-// per slab; a lane reads its single k of a step (a wider read would hand it four k of one row and change the order of
-// the sum).  LDS rows have no padding: chunk c (16 bytes) of row r of A sits at chunk c ^ (r & 7), chunk c of row k of W
+// neighbouring columns (16-byte stores).  Slabs of 32 k go from global memory straight into LDS, two stages; a lane reads its single k of a step (a wider read would hand it four k of one row and change the order of
+// the sum).  STEP slabs make a step: they are requested together and one wait and barrier stand in front of them.
+// LDS rows have no padding: chunk c (16 bytes) of row r of A sits at chunk c ^ (r & 7), chunk c of row k of W
 // at c ^ swz(k), so that the 64 words a read of W takes lie in 64 banks and those of A in at least 32.
-// Bound by the fp32 matrix cores' issue once the chip is full (16384 x 2048 x 512: 390 -> 312 us, 110 of a nominal 157
-// TFLOP/s), by a wave's chain of reads and products before that: the tile is chosen for enough waves in flight (see
-// launch_gemm_f32; 2700 x 128 x 4096 165 -> 56 us, 1024 x 512 x 2048 89 -> 31 us, 16384 x 512 x 2048 376 -> 305 us).
-// Three or four stages instead of two gain nothing (the reads, not the loads, are waited for) and cost occupancy.
-// WV4: rows of W are 16-byte aligned too; otherwise (an unembedding with an odd vocabulary) W comes word by word.
-template <int WAVES_M, int WAVES_N, int TM, int TN, bool WV4>
+// Bound by the fp32 matrix cores' issue once the chip is full (121 to 130 TFLOP/s, where a loop of nothing but these
+// instructions reaches 138), by a wave's chain of waits, reads and products before that: the tile and the step are chosen by how
+// the launch fills the chip (see launch_gemm_f32).  Three or four stages instead of two, or the next operands read in front
+// of the present products, gain nothing there and cost up to a tenth where the chip is full.
+// STEP 0: the rows of W are not 16-byte aligned (an unembedding with an odd vocabulary) and W comes word by word, a slab a step.
+template <int WAVES_M, int WAVES_N, int TM, int TN, int STEP>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const GemmProb* probs, int n_probs, int mt, int nt, int col_first) {
-  constexpr int NW = WAVES_M * WAVES_N, NS = 2;
+  constexpr bool WV4 = STEP > 0;
+  constexpr int SUB = WV4 ? STEP : 1;
+  constexpr int NW = WAVES_M * WAVES_N;
   constexpr int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16;
   constexpr int IA = BM / 8 / NW;                       // load instructions per wave and slab: A (8 rows each)
   constexpr int IB = (WV4 ? BN / 8 : BN / 2) / NW;      // and W (256 or 64 words each)
   constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && BN >= 32, "rows must split evenly over the waves");
-  __shared__ __attribute__((aligned(1024))) uint8_t st[NS * STAGE];
+  __shared__ __attribute__((aligned(1024))) uint8_t st[2 * SUB * STAGE];
   // all problems' tiles of a row tile are neighbours on one XCD (heads read the same rows); with more columns than
   // rows the row tiles of one column tile are
   const int lin = xcd_tile(blockIdx.x, mt * nt * n_probs);
@@ -1272,7 +1274,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const Gemm
   }
   const long long stepB = 32LL * P.ldw * 4;
   const uint32_t lds0 = lds_addr_of(st);
-  auto issue = [&](int stage) {
+  auto issue_slab = [&](int stage) {
     const uint32_t ba = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + wave * IA * 1024);
     const uint32_t bb = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + ABYTES + wave * IB * (WV4 ? 1024 : 256));
 #pragma unroll
@@ -1307,16 +1309,22 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const Gemm
         for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
   };
-  const int nslab = P.K >> 5;
+  const int nslab = P.K >> 5, nstep = (nslab + SUB - 1) / SUB;
+  auto issue = [&](int step) {
 #pragma unroll
-  for (int k = 0; k < NS - 1; k++) if (k < nslab) issue(k);
-  int sc = 0, sr = NS - 1;                              // stage of the slab to multiply, of the next request
-  for (int k = 0; k < nslab; k++) {
-    wait_slab_barrier<NS, IA + IB>(nslab - 1 - k);      // the slab has landed for everyone, the previous one's stage is free
-    if (k + NS - 1 < nslab) issue(sr);
-    compute(st + sc * STAGE);
-    sr = sc;
-    sc = (sc == NS - 1) ? 0 : sc + 1;
+    for (int u = 0; u < SUB; u++) if (SUB == 1 || step * SUB + u < nslab) issue_slab((step & 1) * SUB + u);
+  };
+  issue(0);
+  for (int k = 0; k < nstep; k++) {
+    wait_vm_barrier<0>();                               // the step's slabs have landed for everyone, the previous one's stage is free
+    if (k + 1 < nstep) issue(k + 1);
+    const uint8_t* s = st + (k & 1) * (SUB * STAGE);
+    if (SUB == 1 || (k + 1) * SUB <= nslab) {
+#pragma unroll
+      for (int u = 0; u < SUB; u++) compute(s + u * STAGE);
+    } else {
+      for (int u = 0; k * SUB + u < nslab; u++) compute(s + u * STAGE);
+    }
   }
   // 16-byte accesses where rows, strides and pointers allow them
   const bool al = ((P.ldc | P.c_is | (P.add ? P.add_is : 0) | (P.aux ? P.aux_is : 0)) & 3) == 0 &&
@@ -1350,6 +1358,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const Gemm
   }
 }
 
+// The wait in front of a slab of gemm_f32_heads_k: LD loads and n times ST stores of this wave are younger than its loads.
+template <int LD, int ST>
+__device__ __forceinline__ void wait_heads(int n) {
+  if (n == 0) wait_vm_barrier<LD>();
+  else if (n == 1) wait_vm_barrier<LD + ST>();
+  else wait_vm_barrier<LD + 2 * ST>();
+}
+
 // Output projections of the fp32 heads of a layer, summed:
 //   C[m] = (run_in[m] + bias) + (((add[m] + z_0 W_0) + z_1 W_1) + ...)        (run_in null: the bracket alone)
 // probs[h] is head h's projection (A = the head's columns of the rows of all heads, which lie side by side: probs[0].A and
@@ -1357,14 +1373,19 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const Gemm
 // One launch per head moved the running sum through memory H times: with eight heads of 64 and 16384 rows of 512 the heads'
 // 25 us each were 20 us of traffic, and at 1024 rows 14 us each were latency.  Here the sum stays in registers.
 // Every head's product starts from zero and is then added, ascending: the bits of the launches one by one.
-// Slabs, operand layout and tiles as in gemm_f32_x_k; the slabs of all heads are one stream.
+// Slabs, operand layout and tiles as in gemm_f32_x_k; the slabs of all heads are one stream.  A head has few slabs (two of
+// 64 columns), so nothing may stand between the heads: the pointers of the next one come by scalar loads ahead of time,
+// aux_sub through LDS while the head's last slab is multiplied, and the stores of aux are not waited for, but counted: vector
+// memory operations retire in order, so the wait for a slab allows as many as were issued behind it.  Eight heads of 64 with
+// aux and aux_sub, us before / now: 1024 x 512 19.7 / 15.8, 2700 x 512 31.5 / 27.1; without them 14.1 / 12.8 and 23.4 / 22.3.
 template <int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, int n_heads, int mt, int nt, const float* run_in,
                                                          long long run_is, const float* bias) {
   constexpr int BM = 32 * TM, BN = 32 * TN, IA = BM / 32, IB = BN / 32;
+  constexpr int NS = TM == 2 ? 2 : 3;                   // stages; large tiles fill the chip and want the occupancy
   constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
   static_assert(BN == 64 || BN == 32, "swz below");
-  __shared__ __attribute__((aligned(1024))) uint8_t st[2 * STAGE];
+  __shared__ __attribute__((aligned(1024))) uint8_t st[NS * STAGE + 4 * TM * TN * 1024];
   const int lin = xcd_tile(blockIdx.x, mt * nt);
   if (lin >= mt * nt) return;
   const int m0 = (lin / nt) * BM, n0 = (lin % nt) * BN;
@@ -1390,8 +1411,11 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
   }
   const int spk = P.K >> 5, nslab = spk * n_heads;      // slabs of a head, of all
   const uint32_t lds0 = lds_addr_of(st);
+  // the heads' pointers by scalar loads (a vector load of them would wait for the requested slabs and the stores too)
+  const auto* const cp = (const __attribute__((address_space(4))) GemmProb*)(uintptr_t)probs;
   int rh = 0, rk = 0;                                   // head and slab of the next request
   const float* rw = (const float*)P.W;
+  const float* rw_next = (const float*)cp[min(1, n_heads - 1)].W;
   auto issue = [&](int stage) {
     const uint32_t ba = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + wave * IA * 1024);
     const uint32_t bb = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + ABYTES + wave * IB * 1024);
@@ -1400,7 +1424,7 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
 #pragma unroll
     for (int t = 0; t < IB; t++) slab_load16((const uint8_t*)(rw + offW[t]), bb + t * 1024);
     rw += 32LL * P.ldw;
-    if (++rk == spk) { rk = 0; rh++; if (rh < n_heads) rw = (const float*)probs[rh].W; }
+    if (++rk == spk) { rk = 0; rh++; rw = rw_next; rw_next = (const float*)cp[min(rh + 1, n_heads - 1)].W; }
   };
   int offB[TN];
 #pragma unroll
@@ -1417,17 +1441,45 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
     split_row(i0, r0, min(m, P.M - 1) - m0, P.rpi, P.rp0, inst[i], row[i]);
   }
   const int nb = n0 + wn * TN * 16 + lg * 4;
-  issue(0);
-  int slab = 0;
+  int nc[TN];                                           // those columns, or the last ones
+#pragma unroll
+  for (int j = 0; j < TN; j++) nc[j] = min(nb + j * 16, P.N - 4);
+  // -0 + x is x
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      tot[i][j] = (v4f){-0.f, -0.f, -0.f, -0.f};
+      if (P.add) { const float4 a = gload4(P.add + inst[i] * P.add_is + (long long)row[i] * P.ldc + nc[j]); tot[i][j] = (v4f){a.x, a.y, a.z, a.w}; }
+    }
+  const uint32_t lds_u = __builtin_amdgcn_readfirstlane(lds0 + NS * STAGE + wave * TM * TN * 1024);
+  const uint8_t* const own_u = st + NS * STAGE + wave * TM * TN * 1024 + lane * 16;
+#pragma unroll
+  for (int k = 0; k < NS - 1; k++) if (k < nslab) issue(k);
+  int slab = 0, sc = 0, sr = NS - 1;                    // stage of the slab to multiply, of the next request
+  int aux1 = 0, aux2 = 0;                               // second outputs stored behind the previous slab, the one before it
   for (int h = 0; h < n_heads; h++) {
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
       for (int j = 0; j < TN; j++) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+    float* const aux = cp[h].aux;
+    const float* const sub = cp[h].aux_sub;
+    const long long aux_is = cp[h].aux_is;
     for (int k = 0; k < spk; k++, slab++) {
-      wait_vm_barrier<0>();                             // the slab has landed for everyone, the other stage is free
-      if (slab + 1 < nslab) issue((slab + 1) & 1);
-      const uint8_t* s = st + (slab & 1) * STAGE;
+      // the slab has landed for everyone, the stage of the next request is free: younger than the slab's loads are those
+      // of the slabs behind it and the stores behind the last NS - 1 slabs
+      const int st_n = aux1 + (NS == 3 ? aux2 : 0);
+      if (NS == 3 && slab + 1 < nslab) wait_heads<IA + IB, TM * TN>(st_n);
+      else wait_heads<0, TM * TN>(st_n);
+      if (k == spk - 1 && aux && sub) {                 // each lane's own values, through LDS: in front of the next request
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) slab_load16((const uint8_t*)(sub + (long long)row[i] * P.ldc + nc[j]), lds_u + (i * TN + j) * 1024);
+      }
+      if (slab + NS - 1 < nslab) issue(sr);
+      const uint8_t* s = st + sc * STAGE;
 #pragma unroll
       for (int q = 0; q < 8; q++) {
         float fa[TM], fb[TN];
@@ -1441,27 +1493,31 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
 #pragma unroll
           for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
       }
+      sr = sc;
+      sc = (sc == NS - 1) ? 0 : sc + 1;
+      aux2 = aux1;
+      aux1 = 0;
     }
-    float* const aux = probs[h].aux;
-    const float* const sub = probs[h].aux_sub;
-    const long long aux_is = probs[h].aux_is;
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
-      for (int j = 0; j < TN; j++) {
-        const int n = nb + j * 16;
-        const bool st_on = on[i] && n < P.N;
-        const long long off = (long long)row[i] * P.ldc + n;
-        if (h == 0) {
-          tot[i][j] = acc[i][j];
-          if (P.add && st_on) { const float4 a = gload4(P.add + inst[i] * P.add_is + off); tot[i][j] += (v4f){a.x, a.y, a.z, a.w}; }
-        } else tot[i][j] += acc[i][j];
-        if (aux && st_on) {
-          float4 x = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-          if (sub) { const float4 u = gload4(sub + off); x.x -= u.x; x.y -= u.y; x.z -= u.z; x.w -= u.w; }
-          gstore4(aux + inst[i] * aux_is + off, x);
-        }
+      for (int j = 0; j < TN; j++) tot[i][j] += acc[i][j];
+    if (aux) {
+      aux1 = 1;
+      if (sub) {
+        if (slab + NS - 2 < nslab) wait_vm<IA + IB>(); else wait_vm<0>();
       }
+      // every lane stores, so that a wave has TM * TN stores whatever its rows and columns are: past the end a lane's
+      // operands, and so its value, are those of the last row or column
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          float4 x = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+          if (sub) { const float4 u = *(const float4*)(own_u + (i * TN + j) * 1024); x.x -= u.x; x.y -= u.y; x.z -= u.z; x.w -= u.w; }
+          gstore4(aux + inst[i] * aux_is + (long long)row[i] * P.ldc + nc[j], x);
+        }
+    }
   }
 #pragma unroll
   for (int i = 0; i < TM; i++)
@@ -1485,35 +1541,48 @@ hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int 
   auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   auto grid = [](long long t) { return dim3((unsigned)((t + 7) / 8 * 8)); };
   if (tiles(32, 32) > 0x7ffffff0LL) return hipErrorInvalidValue;
-  // the tile by the same counts as in launch_gemm_f32
+  // from two tiles of 64 x 64 per compute unit on those, below that smaller ones, so that every unit has waves to switch between
   if (tiles(64, 64) >= 512) hipLaunchKernelGGL((gemm_f32_heads_k<2, 2>), grid(tiles(64, 64)), dim3(256), 0, s, probs, n_heads, (M + 63) / 64, (N + 63) / 64, run_in, run_is, bias);
   else if (tiles(64, 64) >= 96) hipLaunchKernelGGL((gemm_f32_heads_k<1, 2>), grid(tiles(32, 64)), dim3(256), 0, s, probs, n_heads, (M + 31) / 32, (N + 63) / 64, run_in, run_is, bias);
   else hipLaunchKernelGGL((gemm_f32_heads_k<1, 1>), grid(tiles(32, 32)), dim3(256), 0, s, probs, n_heads, (M + 31) / 32, (N + 31) / 32, run_in, run_is, bias);
   return hipGetLastError();
 }
 
-template <int WAVES_M, int WAVES_N, int TM, int TN, bool WV4>
+template <int WAVES_M, int WAVES_N, int TM, int TN, int STEP>
 static hipError_t launch_f32_x(const GemmProb* probs, int n_probs, int M, int N, hipStream_t s) {
   const int BM = WAVES_M * TM * 16, BN = WAVES_N * TN * 16, mt = (M + BM - 1) / BM, nt = (N + BN - 1) / BN;
   const long long tiles = (long long)mt * nt * n_probs;
   if (tiles > 0x7ffffff0LL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((gemm_f32_x_k<WAVES_M, WAVES_N, TM, TN, WV4>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, probs,
+  hipLaunchKernelGGL((gemm_f32_x_k<WAVES_M, WAVES_N, TM, TN, STEP>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, probs,
                      n_probs, mt, nt, n_probs == 1 && N > M ? 1 : 0);
   return hipGetLastError();
 }
-// form: the smallest gemm32_form of the problems.  Tiles of 64 x 64 from two per compute unit on; below that smaller ones,
-// so that every unit has waves to switch between (us, 64 x 64 / 32 x 64 / 32 x 32; t = tiles of 64 x 64): 16384 x 2048 x 512
-// 312 / 385 / 439, t = 512 26 / 26 / 28, t = 384 43 / 38 / 41, t = 128 50 / 31 / 31, t = 48 26 / 16 / 12, t = 16 6.9 / 5.2 / 5.0.
+// form: the smallest gemm32_form of the problems.  What counts is how often 256 compute units are filled (us; "/4": steps of
+// four slabs):
+// - from two tiles of 64 x 64 per unit on those, or 128 x 128 (4 to 10% faster per product: half the reads from LDS) where their
+//   last round leaves no more idle: 16384 x 2048 x 512 284 / 276, 15616 x 512 x 2048 293 / 265, 4096 x 2048 x 512 77 / 73,
+//   but 5000 x 2048 x 512 93 / 107 and 2048 x 2048 x 512 (one tile of 128 x 128 per unit) 41 / 44.
+// - one workgroup per unit or less: a wave's chain of waiting, reading and multiplying is what is seen, and four slabs per wait
+//   shorten it (32 x 64 / the same /4 / 32 x 32 / the same /4): 1184 x 128 x 4096 three times 55 / 49 / 53 / 51,
+//   256 x 128 x 4096 three times 56 / 49 / 50 / 35, 512 x 512 x 512 10.3 / 9.4 / 8.2 / 7.6.
+// - between the two 32 x 64 or, where they fill the units more evenly, 32 x 32: 1024 x 768 x 512 14.8 / 13.8,
+//   1216 x 512 x 512 14.3 / 13.1, but 540 x 1536 x 1024 23.5 / 26.8.
 hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  const long long t = (long long)((max_M + 63) / 64) * ((max_N + 63) / 64) * n_probs;
+  auto tiles = [&](int bm, int bn) { return (long long)((max_M + bm - 1) / bm) * ((max_N + bn - 1) / bn) * n_probs; };
+  auto rounds = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256); };
+  const long long t = tiles(64, 64);
   if (form == 2) {
-    if (t >= 512) return launch_f32_x<2, 2, 2, 2, true>(probs, n_probs, max_M, max_N, s);
-    if (t >= 96) return launch_f32_x<2, 2, 1, 2, true>(probs, n_probs, max_M, max_N, s);
-    return launch_f32_x<2, 2, 1, 1, true>(probs, n_probs, max_M, max_N, s);
+    if (t >= 512)
+      return tiles(128, 128) > 256 && 3.8 * rounds(128, 128) <= rounds(64, 64) ? launch_f32_x<2, 2, 4, 4, 1>(probs, n_probs, max_M, max_N, s)
+                                                                               : launch_f32_x<2, 2, 2, 2, 1>(probs, n_probs, max_M, max_N, s);
+    if (tiles(32, 32) <= 256) return launch_f32_x<2, 2, 1, 1, 4>(probs, n_probs, max_M, max_N, s);
+    if (tiles(32, 64) <= 256) return launch_f32_x<2, 2, 1, 2, 4>(probs, n_probs, max_M, max_N, s);
+    return 1.1 * rounds(32, 32) < 2 * rounds(32, 64) ? launch_f32_x<2, 2, 1, 1, 1>(probs, n_probs, max_M, max_N, s)
+                                                     : launch_f32_x<2, 2, 1, 2, 1>(probs, n_probs, max_M, max_N, s);
   }
-  if (form == 1) return t >= 256 ? launch_f32_x<2, 2, 2, 2, false>(probs, n_probs, max_M, max_N, s)
-                                 : launch_f32_x<2, 2, 1, 1, false>(probs, n_probs, max_M, max_N, s);
+  if (form == 1) return t >= 256 ? launch_f32_x<2, 2, 2, 2, 0>(probs, n_probs, max_M, max_N, s)
+                                 : launch_f32_x<2, 2, 1, 1, 0>(probs, n_probs, max_M, max_N, s);
   dim3 grid((max_N + 63) / 64, (max_M + 63) / 64, n_probs);
   hipLaunchKernelGGL(gemm_f32_k, grid, dim3(256), 0, s, probs);
   return hipGetLastError();

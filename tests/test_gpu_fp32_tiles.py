@@ -56,3 +56,44 @@ def test_fp32_scores_by_batch_and_against_the_oracle(H, dh, d, m, V, frac):
         for u in range(n_up):
             want = oa.kl_edge(r2, u)
             assert abs(out[0][40 + u] - want) <= F32_ATOL + F32_RTOL * abs(want), u
+
+
+def takes_128_tiles(rows, cols):
+    """The rule of launch_gemm_f32, by rounds of 256 tiles."""
+    def tiles(b):
+        return -(-rows // b) * -(-cols // b)
+    return tiles(64) >= 512 and tiles(128) > 256 and 3.8 * -(-tiles(128) // 256) <= -(-tiles(64) // 256)
+
+
+# The MLP's products of the first layer: 68 candidates have 8168 rows, 20 have 2408, 1 has 128.  Slabs of 32: 10 and 32 of them
+# (input, output), whole tiles of columns; 6 and 31, the last step of four not full, ragged columns and rows.
+@pytest.mark.parametrize("H,dh,d,m", [(5, 64, 320, 1024), (6, 32, 192, 992)])
+def test_scores_in_large_tiles_and_in_steps_of_four_slabs(H, dh, d, m):
+    import paper_2510_23264_amd as P
+    B, S, V = 8, 16, 300
+    assert takes_128_tiles(8 + 68 * 120, m) and not takes_128_tiles(8 + 20 * 120, m)
+    shape = ModelShape(n_layers=2, n_heads=H, d_head=dh, d_model=d, d_mlp=m, vocab=V, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 13, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(13)
+    clean = rng.integers(0, V, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, V - 1, (B, 5))) % V      # position 0 is shared
+    r = 3 * H                                        # the first layer's MLP input
+    out = []
+    for batch in (68, 20, 1):
+        gm = P.Model(shape, w, B, S, precision=P.ALL_FP32, max_batch_edges=batch)
+        try:
+            gm.clean_cache(clean, corrupt)
+            senders = np.resize(np.arange(P.n_upstream(gm.cfg, r), dtype=np.int32), 68)[:batch]
+            before = gm.counters()[1]
+            out.append(gm.eval_edges(r, senders))
+            assert gm.counters()[1] == before + 1
+        finally:
+            gm.close()
+    for got in out[1:]:
+        assert np.array_equal(got.view(np.uint32), out[0][:got.size].view(np.uint32))
+    om = OModel(shape, w)
+    oa = Acdc(om, clean, corrupt, MODE_ALL_FP32)
+    for u in (0, P.n_upstream(gm.cfg, r) - 1):
+        want = oa.kl_edge(r, u)
+        assert abs(out[0][u] - want) <= F32_ATOL + F32_RTOL * abs(want), u
