@@ -27,13 +27,21 @@ typedef float v4f_a __attribute__((ext_vector_type(4)));
 // Rows are looked up (AttnSrc.row_of): a sequence's positions need not be neighbours in memory, and the rows below rp0
 // are instance 0's whichever instance the wave works for, so their keys and values come from the caches after the first
 // wave.  With last_only only the last query tile is computed and only its last row leaves.
-template <int ST, int DH, bool ROPE, bool STG>
+// OUT: 0 one-byte codes, 1 the same with operands and codes staged in LDS, 2 bfloat16 (a kernel of its own: the three ways of
+// leaving side by side were a fifth of the instructions that a first wave has to fetch).
+// A launch of few sequences is one wave's chain of loads and products, a large one is bound by memory (16-byte pieces of 16
+// rows a load).  The values are therefore requested with the queries and keys, not behind the softmax, where the registers allow
+// it, and without a branch per load: 32 positions of 64 columns, us before / now: 256 (sequence, head) pairs 11.3 / 9.2,
+// 7680 pairs 52.0 / 48.8.
+template <int ST, int DH, bool ROPE, int OUT>
 __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zcodes, float* zscale, float* zf32,
                                                          unsigned long long f32_mask, unsigned long long dead_mask,
                                                          int n_pairs, int B, int S, int H, int ldz, const float2* rope_tab) {
   constexpr int CH = DH / 4;        // columns of q / k per lane
   constexpr int NT = DH / 16;       // output column tiles
-  const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr bool STG = OUT == 1;    // operands through LDS
+  constexpr bool VEARLY = !STG && ST * NT <= 8;
+  const int pair = blockIdx.x * (STG ? 4 : blockDim.x >> 6) + (threadIdx.x >> 6);
   if (pair >= n_pairs) return;
   const int hl = pair % src.n_heads, sb = pair / src.n_heads;          // sb = inst * B + b
   const int h = src.h0 + hl;                                           // head index in the outputs
@@ -115,6 +123,19 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
     }
   }
   }
+  // values: vv[bk][r][t] = V[key 16bk + 4g + r][16t + i]; past the end the last position's, replaced by zero before use
+  float vv[ST][4][NT];
+  auto load_values = [&]() {
+#pragma unroll
+    for (int bk = 0; bk < ST; bk++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const float* row = at(v0, src.v_is, src.v_ld, __shfl(rw[bk], 4 * g + r, 64)) + i;
+#pragma unroll
+        for (int t = 0; t < NT; t++) vv[bk][r][t] = row[16 * t];
+      }
+  };
+  if (VEARLY) load_values();
   if (ROPE) {
 #pragma unroll
     for (int a = 0; a < ST; a++) {
@@ -182,23 +203,18 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
       for (int r = 0; r < 4; r++) sc[a][bk][r] *= rs;
   }
 
-  // values: vv[bk][r][t] = V[key 16bk + 4g + r][16t + i]
-  float vv[ST][4][NT];
   if (STG) { __builtin_amdgcn_s_waitcnt(0x0F70); __builtin_amdgcn_wave_barrier(); }
+  else if (!VEARLY) load_values();
 #pragma unroll
   for (int bk = 0; bk < ST; bk++)
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-      int kpos = 16 * bk + 4 * g + r;
-      if (STG) {
-        // V[kpos][16 t + i]: chunk 4 t + (i >> 2) of row kpos, word i & 3 of it
+      const int kpos = 16 * bk + 4 * g + r;
+      // staged: V[kpos][16 t + i] is chunk 4 t + (i >> 2) of row kpos, word i & 3 of it
 #pragma unroll
-        for (int t = 0; t < NT; t++)
-          vv[bk][r][t] = (kpos < S) ? sq[kpos * 64 + (((4 * t + (i >> 2)) ^ kpos) * 4) + (i & 3)] : 0.f;
-      } else {
-        const float* row = at(v0, src.v_is, src.v_ld, __shfl(rw[bk], 4 * g + r, 64)) + i;
-#pragma unroll
-        for (int t = 0; t < NT; t++) vv[bk][r][t] = (kpos < S) ? row[16 * t] : 0.f;
+      for (int t = 0; t < NT; t++) {
+        if (STG) vv[bk][r][t] = (kpos < S) ? sq[kpos * 64 + (((4 * t + (i >> 2)) ^ kpos) * 4) + (i & 3)] : 0.f;
+        else vv[bk][r][t] = (kpos < S) ? vv[bk][r][t] : 0.f;
       }
     }
 
@@ -240,9 +256,9 @@ __global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zc
         for (int t = 0; t < NT; t++) am = fmaxf(am, fabsf(z[t][rr]));
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) am = fmaxf(am, __shfl_xor(am, o, 64));
-        float scale = (am == 0.f || src.qbits == 16) ? 1.0f : am / q_top(src.qbits);
+        float scale = (am == 0.f || OUT == 2) ? 1.0f : am / q_top(src.qbits);
         float inv = 1.0f / scale;
-        if (!STG && src.qbits == 16) {
+        if (OUT == 2) {
           // bfloat16 patterns, two bytes per value, no scale
           if (on) {
             uint8_t* o = zcodes + (tok * H + h) * ldz + 2 * i;
@@ -494,12 +510,16 @@ hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, float* zscale, 
 #undef ATQ
     return hipGetLastError();
   }
-  dim3 grid((n_pairs + 3) / 4);
+  const bool staged = S <= 16 && dh == 64 && !rope && src.qbits != 16;
+  // up to four pairs per compute unit a workgroup is one wave, so that they spread over the units (with the kernel as it was
+  // otherwise, 256 pairs: 10.9 us in workgroups of four, 9.7 alone); many or staged pairs gain nothing from it, and workgroups
+  // of one staged wave cost (64000 pairs 161 / 173 us)
+  const int wpb = n_pairs <= 1024 && !staged ? 1 : 4;
   // the staged form (one tile, d_head 64, no rotation) collects one-byte codes in LDS: bfloat16 outputs take the plain form
-#define ATT0(ST_, DH_, R_, G_) hipLaunchKernelGGL((attention_mfma_k<ST_, DH_, R_, G_>), grid, dim3(256), 0, s, src, zcodes, zscale, zf32, \
+#define ATT0(ST_, DH_, R_, G_) hipLaunchKernelGGL((attention_mfma_k<ST_, DH_, R_, G_>), dim3((n_pairs + wpb - 1) / wpb), dim3(64 * wpb), 0, s, src, zcodes, zscale, zf32, \
                                               f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab)
-#define ATT1(ST_, DH_, R_) do { if ((ST_ == 1 && DH_ == 64 && !R_) && src.qbits != 16) ATT0(ST_, DH_, R_, (ST_ == 1 && DH_ == 64 && !R_)); \
-                                else ATT0(ST_, DH_, R_, false); } while (0)
+#define ATT1(ST_, DH_, R_) do { if (src.qbits == 16) ATT0(ST_, DH_, R_, 2); \
+                                else ATT0(ST_, DH_, R_, (ST_ == 1 && DH_ == 64 && !R_ ? 1 : 0)); } while (0)
 #define ATT(ST_, DH_) do { if (rope) ATT1(ST_, DH_, true); else ATT1(ST_, DH_, false); } while (0)
   if (S <= 16) {
     if (dh == 16) ATT(1, 16); else if (dh == 32) ATT(1, 32); else if (dh == 64) ATT(1, 64);

@@ -107,3 +107,26 @@ def test_limits():
     assert P.workspace_bytes(P.Config.from_shape(shape), 2, 128) > 0
     wide = ModelShape(n_layers=1, n_heads=1, d_head=128, d_model=128, d_mlp=0, vocab=50, n_ctx=128, act=0)
     assert P.workspace_bytes(P.Config.from_shape(wide), 2, 128) > 0
+
+
+# 40 candidates are up to 1600 pairs of a sequence and a head in a launch (workgroups of four waves), one is 40 (of one wave)
+@pytest.mark.parametrize("S,options", [(17, {}), (32, {}), (31, dict(low_bits=16)), (48, {}), (15, dict(low_bits=16))])
+def test_scores_do_not_depend_on_the_pairs_of_a_launch(S, options):
+    import paper_2510_23264_amd as P
+    H, B, V = 5, 8, 300
+    shape = ModelShape(n_layers=2, n_heads=H, d_head=64, d_model=320, d_mlp=128, vocab=V, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 7, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(7)
+    clean = rng.integers(0, V, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, V - 1, (B, 5))) % V
+    r = 3 * H                                        # the first layer's MLP input: the second layer's heads are each candidate's own
+    out = []
+    for batch in (40, 1):
+        gm = P.Model(shape, w, B, S, max_batch_edges=batch, **options)
+        try:
+            gm.clean_cache(clean, corrupt)
+            out.append(gm.eval_edges(r, np.resize(np.arange(P.n_upstream(gm.cfg, r), dtype=np.int32), 40)[:batch]))
+        finally:
+            gm.close()
+    assert np.isfinite(out[0]).all() and np.array_equal(out[1].view(np.uint32), out[0][:1].view(np.uint32))
