@@ -1073,7 +1073,7 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
       case OP_GEMM32: {
         int form = 2;
         for (int q = 0; q < o.i1; q++) form = std::min(form, gemm32_form(b.probs[o.i0 + q]));
-        HIPCHK(launch_gemm_f32(d_probs + o.i0, o.i1, o.i2, o.i3, form, st));
+        HIPCHK(launch_gemm_f32(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, form, st));
         break;
       }
       case OP_GEMM32H:

@@ -35,6 +35,7 @@
 #include "kernels.h"
 #include "device_util.h"
 #include "mma_util.h"
+#include "tile_rules.h"
 
 namespace pahq {
 
@@ -1223,13 +1224,14 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const GemmProb* probs) {
 
 // The fp32 product for K a multiple of 32 and 16-byte aligned rows of A.  Per element the same sum as gemm_f32_k: one
 // V_MFMA_F32_16X16X4_F32 per four k, ascending.  W is the first operand here, so that a lane owns one row and four
-// neighbouring columns (16-byte stores).  Slabs of 32 k go from global memory straight into LDS, two stages; a lane reads its single k of a step (a wider read would hand it four k of one row and change the order of
-// the sum).  STEP slabs make a step: they are requested together and one wait and barrier stand in front of them.
+// neighbouring columns (16-byte stores).  Slabs of 32 k go from global memory straight into LDS, two stages; a lane reads
+// its single k of a step (a wider read would hand it four k of one row and change the order of the sum).  STEP slabs make a
+// step: they are requested together and one wait and barrier stand in front of them.
 // LDS rows have no padding: chunk c (16 bytes) of row r of A sits at chunk c ^ (r & 7), chunk c of row k of W
 // at c ^ swz(k), so that the 64 words a read of W takes lie in 64 banks and those of A in at least 32.
 // Bound by the fp32 matrix cores' issue once the chip is full (121 to 130 TFLOP/s, where a loop of nothing but these
 // instructions reaches 138), by a wave's chain of waits, reads and products before that: the tile and the step are chosen by how
-// the launch fills the chip (see launch_gemm_f32).  Three or four stages instead of two, or the next operands read in front
+// the launch fills the chip (pick_f32_tile).  Three or four stages instead of two, or the next operands read in front
 // of the present products, gain nothing there and cost up to a tenth where the chip is full.
 // STEP 0: the rows of W are not 16-byte aligned (an unembedding with an odd vocabulary) and W comes word by word, a slab a step.
 template <int WAVES_M, int WAVES_N, int TM, int TN, int STEP>
@@ -1558,30 +1560,20 @@ static hipError_t launch_f32_x(const GemmProb* probs, int n_probs, int M, int N,
                      n_probs, mt, nt, n_probs == 1 && N > M ? 1 : 0);
   return hipGetLastError();
 }
-// form: the smallest gemm32_form of the problems.  What counts is how often 256 compute units are filled (us; "/4": steps of
-// four slabs):
-// - from two tiles of 64 x 64 per unit on those, or 128 x 128 (4 to 10% faster per product: half the reads from LDS) where their
-//   last round leaves no more idle: 16384 x 2048 x 512 284 / 276, 15616 x 512 x 2048 293 / 265, 4096 x 2048 x 512 77 / 73,
-//   but 5000 x 2048 x 512 93 / 107 and 2048 x 2048 x 512 (one tile of 128 x 128 per unit) 41 / 44.
-// - one workgroup per unit or less: a wave's chain of waiting, reading and multiplying is what is seen, and four slabs per wait
-//   shorten it (32 x 64 / the same /4 / 32 x 32 / the same /4): 1184 x 128 x 4096 three times 55 / 49 / 53 / 51,
-//   256 x 128 x 4096 three times 56 / 49 / 50 / 35, 512 x 512 x 512 10.3 / 9.4 / 8.2 / 7.6.
-// - between the two 32 x 64 or, where they fill the units more evenly, 32 x 32: 1024 x 768 x 512 14.8 / 13.8,
-//   1216 x 512 x 512 14.3 / 13.1, but 540 x 1536 x 1024 23.5 / 26.8.
-hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s) {
+// form: the smallest gemm32_form of the problems.  K: that of all of them.
+hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int form, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  auto tiles = [&](int bm, int bn) { return (long long)((max_M + bm - 1) / bm) * ((max_N + bn - 1) / bn) * n_probs; };
-  auto rounds = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256); };
-  const long long t = tiles(64, 64);
   if (form == 2) {
-    if (t >= 512)
-      return tiles(128, 128) > 256 && 3.8 * rounds(128, 128) <= rounds(64, 64) ? launch_f32_x<2, 2, 4, 4, 1>(probs, n_probs, max_M, max_N, s)
-                                                                               : launch_f32_x<2, 2, 2, 2, 1>(probs, n_probs, max_M, max_N, s);
-    if (tiles(32, 32) <= 256) return launch_f32_x<2, 2, 1, 1, 4>(probs, n_probs, max_M, max_N, s);
-    if (tiles(32, 64) <= 256) return launch_f32_x<2, 2, 1, 2, 4>(probs, n_probs, max_M, max_N, s);
-    return 1.1 * rounds(32, 32) < 2 * rounds(32, 64) ? launch_f32_x<2, 2, 1, 1, 1>(probs, n_probs, max_M, max_N, s)
-                                                     : launch_f32_x<2, 2, 1, 2, 1>(probs, n_probs, max_M, max_N, s);
+    switch (pick_f32_tile(n_probs, max_M, max_N, K)) {
+      case F32_128x128: return launch_f32_x<2, 2, 4, 4, 1>(probs, n_probs, max_M, max_N, s);
+      case F32_64x64: return launch_f32_x<2, 2, 2, 2, 1>(probs, n_probs, max_M, max_N, s);
+      case F32_32x64_STEP4: return launch_f32_x<2, 2, 1, 2, 4>(probs, n_probs, max_M, max_N, s);
+      case F32_32x64: return launch_f32_x<2, 2, 1, 2, 1>(probs, n_probs, max_M, max_N, s);
+      case F32_32x32_STEP4: return launch_f32_x<2, 2, 1, 1, 4>(probs, n_probs, max_M, max_N, s);
+      case F32_32x32: return launch_f32_x<2, 2, 1, 1, 1>(probs, n_probs, max_M, max_N, s);
+    }
   }
+  const long long t = tile_count(n_probs, max_M, max_N, 64, 64);
   if (form == 1) return t >= 256 ? launch_f32_x<2, 2, 2, 2, 0>(probs, n_probs, max_M, max_N, s)
                                  : launch_f32_x<2, 2, 1, 1, 0>(probs, n_probs, max_M, max_N, s);
   dim3 grid((max_N + 63) / 64, (max_M + 63) / 64, n_probs);

@@ -189,7 +189,7 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
 // on the bf16 matrix cores, fp32 sums)
 // wide: gemm8_wide_ok of every one of them
 hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, bool wide, hipStream_t s);
-hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int form, hipStream_t s);
+hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int form, hipStream_t s);
 // C = (run_in + bias) + (add + sum over heads of A_h W_h), each head's own product to its aux (see gemm.hip); run_in may be null
 hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int N, const float* run_in, long long run_is,
                                  const float* bias, hipStream_t s);

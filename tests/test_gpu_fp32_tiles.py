@@ -9,6 +9,7 @@ import pytest
 
 sys.path.insert(0, os.path.dirname(__file__))
 import synth                                        # noqa: E402
+import tile_rules as T                              # noqa: E402
 from synth import ModelShape                        # noqa: E402
 from oracle.acdc import Acdc, MODE_ALL_FP32         # noqa: E402
 from oracle.model import Model as OModel            # noqa: E402
@@ -58,20 +59,16 @@ def test_fp32_scores_by_batch_and_against_the_oracle(H, dh, d, m, V, frac):
             assert abs(out[0][40 + u] - want) <= F32_ATOL + F32_RTOL * abs(want), u
 
 
-def takes_128_tiles(rows, cols):
-    """The rule of launch_gemm_f32, by rounds of 256 tiles."""
-    def tiles(b):
-        return -(-rows // b) * -(-cols // b)
-    return tiles(64) >= 512 and tiles(128) > 256 and 3.8 * -(-tiles(128) // 256) <= -(-tiles(64) // 256)
-
-
 # The MLP's products of the first layer: 68 candidates have 8168 rows, 20 have 2408, 1 has 128.  Slabs of 32: 10 and 32 of them
-# (input, output), whole tiles of columns; 6 and 31, the last step of four not full, ragged columns and rows.
-@pytest.mark.parametrize("H,dh,d,m", [(5, 64, 320, 1024), (6, 32, 192, 992)])
+# (input, output), whole tiles of columns; 6 and 31, the last step of four not full, ragged columns and rows; 16 and 18 slabs of
+# the input product in tiles of 128 x 128 (8168 rows), whole and ragged columns.
+@pytest.mark.parametrize("H,dh,d,m", [(5, 64, 320, 1024), (6, 32, 192, 992), (8, 64, 512, 1024), (18, 32, 576, 992)])
 def test_scores_in_large_tiles_and_in_steps_of_four_slabs(H, dh, d, m):
     import paper_2510_23264_amd as P
     B, S, V = 8, 16, 300
-    assert takes_128_tiles(8 + 68 * 120, m) and not takes_128_tiles(8 + 20 * 120, m)
+    large = [T.f32_tile(1, rows, m, d) == T.F32_128x128 for rows in (8 + 68 * 120, 8 + 20 * 120, 128)]
+    assert large == [d >= 512, False, False]
+    assert T.f32_tile(1, 128, d, m) in (T.F32_32x32_STEP4, T.F32_32x64_STEP4)
     shape = ModelShape(n_layers=2, n_heads=H, d_head=dh, d_model=d, d_mlp=m, vocab=V, n_ctx=S, act=1)
     w = synth.make_weights(shape, 13, std=0.08, affine_std=0.1)
     rng = np.random.default_rng(13)
