@@ -33,14 +33,26 @@ typedef float v4f_a __attribute__((ext_vector_type(4)));
 // rows a load).  The values are therefore requested with the queries and keys, not behind the softmax, where the registers allow
 // it, and without a branch per load: 32 positions of 64 columns, us before / now: 256 (sequence, head) pairs 11.3 / 9.2,
 // 7680 pairs 52.0 / 48.8.
+// The values in flight must not cost waves where many pairs fill the chip: left to itself the compiler spends up to 40 registers
+// more on them than this kernel had with the values behind the softmax, and four tiles of 32 rotated columns lost one of two waves
+// per SIMD (8192 pairs: 95 us before, 134 with values early, 84 with two waves kept; not rotated, three waves: 71 / 79 / 68; four
+// tiles of 16, rotated: 59 / 66 / 56).  The floors below are the waves without early values, where holding them costs nothing.
+constexpr int attn_min_waves(int st, int dh, bool rope) {
+  if (st == 4 && dh <= 32) return dh == 32 && rope ? 2 : 3;
+  if (st == 2 && dh == 16) return rope ? 6 : 1;
+  if (st == 2 && !rope) return dh == 32 ? 6 : dh == 64 ? 4 : 1;
+  if (st == 1 && rope) return dh == 32 ? 8 : dh == 64 ? 5 : dh == 128 ? 3 : 1;
+  return 1;
+}
 template <int ST, int DH, bool ROPE, int OUT>
-__global__ __launch_bounds__(256) void attention_mfma_k(AttnSrc src, uint8_t* zcodes, float* zscale, float* zf32,
+__global__ __launch_bounds__(256, attn_min_waves(ST, DH, ROPE)) void attention_mfma_k(AttnSrc src, uint8_t* zcodes, float* zscale, float* zf32,
                                                          unsigned long long f32_mask, unsigned long long dead_mask,
                                                          int n_pairs, int B, int S, int H, int ldz, const float2* rope_tab) {
   constexpr int CH = DH / 4;        // columns of q / k per lane
   constexpr int NT = DH / 16;       // output column tiles
   constexpr bool STG = OUT == 1;    // operands through LDS
-  constexpr bool VEARLY = !STG && ST * NT <= 8;
+  // (three tiles of 32 columns not rotated: 4096 pairs 21.7 us before, 23.0 with early values, 21.2 without, 768 9.9 / 9.1 / 9.3)
+  constexpr bool VEARLY = !STG && ST * NT <= 8 && !(ST == 3 && DH == 32 && !ROPE);
   const int pair = blockIdx.x * (STG ? 4 : blockDim.x >> 6) + (threadIdx.x >> 6);
   if (pair >= n_pairs) return;
   const int hl = pair % src.n_heads, sb = pair / src.n_heads;          // sb = inst * B + b
@@ -511,10 +523,11 @@ hipError_t launch_attention(const AttnSrc& src, uint8_t* zcodes, float* zscale, 
     return hipGetLastError();
   }
   const bool staged = S <= 16 && dh == 64 && !rope && src.qbits != 16;
-  // up to four pairs per compute unit a workgroup is one wave, so that they spread over the units (with the kernel as it was
-  // otherwise, 256 pairs: 10.9 us in workgroups of four, 9.7 alone); many or staged pairs gain nothing from it, and workgroups
-  // of one staged wave cost (64000 pairs 161 / 173 us)
-  const int wpb = n_pairs <= 1024 && !staged ? 1 : 4;
+  // up to three pairs per compute unit a workgroup is one wave, so that they spread over the units (32 positions of 128 columns in
+  // fp32, workgroups of four / one wave: 512 pairs 14.1 / 11.1 us, 768 16.4 / 15.6, 896 17.6 / 17.4, 1024 18.6 / 19.7; 64 of 64
+  // columns 17.9 / 15.9, 19.2 / 18.6, 19.9 / 20.2, 20.5 / 21.6); more pairs gain nothing from it, and workgroups of one staged
+  // wave cost (64000 pairs 161 / 173 us)
+  const int wpb = n_pairs <= 768 && !staged ? 1 : 4;
   // the staged form (one tile, d_head 64, no rotation) collects one-byte codes in LDS: bfloat16 outputs take the plain form
 #define ATT0(ST_, DH_, R_, G_) hipLaunchKernelGGL((attention_mfma_k<ST_, DH_, R_, G_>), dim3((n_pairs + wpb - 1) / wpb), dim3(64 * wpb), 0, s, src, zcodes, zscale, zf32, \
                                               f32_mask, dead_mask, n_pairs, B, S, H, ldz, (const float2*)rope_tab)

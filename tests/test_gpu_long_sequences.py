@@ -110,11 +110,12 @@ def test_limits():
 
 
 # 40 candidates are up to 1600 pairs of a sequence and a head in a launch (workgroups of four waves), one is 40 (of one wave)
-@pytest.mark.parametrize("S,options", [(17, {}), (32, {}), (31, dict(low_bits=16)), (48, {}), (15, dict(low_bits=16))])
-def test_scores_do_not_depend_on_the_pairs_of_a_launch(S, options):
+@pytest.mark.parametrize("S,options,dh", [(17, {}, 64), (32, {}, 64), (31, dict(low_bits=16), 64), (48, {}, 64), (15, dict(low_bits=16), 64),
+                                          (33, {}, 32), (47, {}, 32), (64, {}, 32), (64, {}, 16)])
+def test_scores_do_not_depend_on_the_pairs_of_a_launch(S, options, dh):
     import paper_2510_23264_amd as P
     H, B, V = 5, 8, 300
-    shape = ModelShape(n_layers=2, n_heads=H, d_head=64, d_model=320, d_mlp=128, vocab=V, n_ctx=S, act=1)
+    shape = ModelShape(n_layers=2, n_heads=H, d_head=dh, d_model=320, d_mlp=128, vocab=V, n_ctx=S, act=1)
     w = synth.make_weights(shape, 7, std=0.08, affine_std=0.1)
     rng = np.random.default_rng(7)
     clean = rng.integers(0, V, (B, S)).astype(np.int32)
