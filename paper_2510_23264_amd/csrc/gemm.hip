@@ -1361,14 +1361,6 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_f32_x_k(const Gemm
   }
 }
 
-// The wait in front of a slab of gemm_f32_heads_k: LD loads and n times ST stores of this wave are younger than its loads.
-template <int LD, int ST>
-__device__ __forceinline__ void wait_heads(int n) {
-  if (n == 0) wait_vm_barrier<LD>();
-  else if (n == 1) wait_vm_barrier<LD + ST>();
-  else wait_vm_barrier<LD + 2 * ST>();
-}
-
 // Output projections of the fp32 heads of a layer, summed:
 //   C[m] = (run_in[m] + bias) + (((add[m] + z_0 W_0) + z_1 W_1) + ...)        (run_in null: the bracket alone)
 // probs[h] is head h's projection (A = the head's columns of the rows of all heads, which lie side by side: probs[0].A and
@@ -1378,17 +1370,19 @@ __device__ __forceinline__ void wait_heads(int n) {
 // Every head's product starts from zero and is then added, ascending: the bits of the launches one by one.
 // Slabs, operand layout and tiles as in gemm_f32_x_k; the slabs of all heads are one stream.  A head has few slabs (two of
 // 64 columns), so nothing may stand between the heads: the pointers of the next one come by scalar loads ahead of time,
-// aux_sub through LDS while the head's last slab is multiplied, and the stores of aux are not waited for, but counted: vector
-// memory operations retire in order, so the wait for a slab allows as many as were issued behind it.  Eight heads of 64 with
-// aux and aux_sub, us before / now: 1024 x 512 19.7 / 15.8, 2700 x 512 31.5 / 27.1; without them 14.1 / 12.8 and 23.4 / 22.3.
+// aux_sub through LDS while the head's last slab is multiplied, and the stores of aux are counted: vector memory operations retire
+// in order, so the wait for a slab allows as many as were issued behind it.  (With aux_sub, a head's stores are retired by the next
+// head's wait for its subtrahend.)
+// Two stages: a third one, requested two slabs ahead, gains nothing where the chip is not full and costs workgroups where it is
+// (45 KB instead of 33 with 32 x 64 tiles, three instead of four per unit: 6 heads of 32, 10700 x 192 with aux 23.2 / 16.4 us).  Of
+// 400 random launches of 2 to 16 heads none takes longer by more than 3 % than with the waits between heads, in the mean 0.88.
 template <int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, int n_heads, int mt, int nt, const float* run_in,
                                                          long long run_is, const float* bias) {
   constexpr int BM = 32 * TM, BN = 32 * TN, IA = BM / 32, IB = BN / 32;
-  constexpr int NS = TM == 2 ? 2 : 3;                   // stages; large tiles fill the chip and want the occupancy
   constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
   static_assert(BN == 64 || BN == 32, "swz below");
-  __shared__ __attribute__((aligned(1024))) uint8_t st[NS * STAGE + 4 * TM * TN * 1024];
+  __shared__ __attribute__((aligned(1024))) uint8_t st[2 * STAGE + 4 * TM * TN * 1024];
   const int lin = xcd_tile(blockIdx.x, mt * nt);
   if (lin >= mt * nt) return;
   const int m0 = (lin / nt) * BM, n0 = (lin % nt) * BN;
@@ -1455,12 +1449,11 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
       tot[i][j] = (v4f){-0.f, -0.f, -0.f, -0.f};
       if (P.add) { const float4 a = gload4(P.add + inst[i] * P.add_is + (long long)row[i] * P.ldc + nc[j]); tot[i][j] = (v4f){a.x, a.y, a.z, a.w}; }
     }
-  const uint32_t lds_u = __builtin_amdgcn_readfirstlane(lds0 + NS * STAGE + wave * TM * TN * 1024);
-  const uint8_t* const own_u = st + NS * STAGE + wave * TM * TN * 1024 + lane * 16;
-#pragma unroll
-  for (int k = 0; k < NS - 1; k++) if (k < nslab) issue(k);
-  int slab = 0, sc = 0, sr = NS - 1;                    // stage of the slab to multiply, of the next request
-  int aux1 = 0, aux2 = 0;                               // second outputs stored behind the previous slab, the one before it
+  const uint32_t lds_u = __builtin_amdgcn_readfirstlane(lds0 + 2 * STAGE + wave * TM * TN * 1024);
+  const uint8_t* const own_u = st + 2 * STAGE + wave * TM * TN * 1024 + lane * 16;
+  issue(0);
+  int slab = 0;
+  bool stored = false;                                  // has a second output left behind the previous slab?
   for (int h = 0; h < n_heads; h++) {
 #pragma unroll
     for (int i = 0; i < TM; i++)
@@ -1470,19 +1463,18 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
     const float* const sub = cp[h].aux_sub;
     const long long aux_is = cp[h].aux_is;
     for (int k = 0; k < spk; k++, slab++) {
-      // the slab has landed for everyone, the stage of the next request is free: younger than the slab's loads are those
-      // of the slabs behind it and the stores behind the last NS - 1 slabs
-      const int st_n = aux1 + (NS == 3 ? aux2 : 0);
-      if (NS == 3 && slab + 1 < nslab) wait_heads<IA + IB, TM * TN>(st_n);
-      else wait_heads<0, TM * TN>(st_n);
+      // the slab has landed for everyone, the other stage is free; younger than the slab's loads are the stores behind the
+      // previous slab alone
+      if (stored) wait_vm_barrier<TM * TN>(); else wait_vm_barrier<0>();
+      stored = false;
       if (k == spk - 1 && aux && sub) {                 // each lane's own values, through LDS: in front of the next request
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
           for (int j = 0; j < TN; j++) slab_load16((const uint8_t*)(sub + (long long)row[i] * P.ldc + nc[j]), lds_u + (i * TN + j) * 1024);
       }
-      if (slab + NS - 1 < nslab) issue(sr);
-      const uint8_t* s = st + sc * STAGE;
+      if (slab + 1 < nslab) issue((slab + 1) & 1);
+      const uint8_t* s = st + (slab & 1) * STAGE;
 #pragma unroll
       for (int q = 0; q < 8; q++) {
         float fa[TM], fb[TN];
@@ -1496,19 +1488,15 @@ __global__ __launch_bounds__(256) void gemm_f32_heads_k(const GemmProb* probs, i
 #pragma unroll
           for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
       }
-      sr = sc;
-      sc = (sc == NS - 1) ? 0 : sc + 1;
-      aux2 = aux1;
-      aux1 = 0;
     }
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
       for (int j = 0; j < TN; j++) tot[i][j] += acc[i][j];
     if (aux) {
-      aux1 = 1;
-      if (sub) {
-        if (slab + NS - 2 < nslab) wait_vm<IA + IB>(); else wait_vm<0>();
+      stored = true;
+      if (sub) {                                        // this head's subtrahend (and with it the stores of the head before)
+        if (slab < nslab) wait_vm<IA + IB>(); else wait_vm<0>();
       }
       // every lane stores, so that a wave has TM * TN stores whatever its rows and columns are: past the end a lane's
       // operands, and so its value, are those of the last row or column

@@ -94,3 +94,43 @@ def test_scores_in_large_tiles_and_in_steps_of_four_slabs(H, dh, d, m):
     for u in (0, P.n_upstream(gm.cfg, r) - 1):
         want = oa.kl_edge(r, u)
         assert abs(out[0][u] - want) <= F32_ATOL + F32_RTOL * abs(want), u
+
+
+# Receivers of the last layer no longer read some heads of the middle one: their outputs are wanted one by one, less the
+# corrupted run's.  The middle layer's projections (N = d_model) take the three tiles by batch, with one slab a head and with two.
+@pytest.mark.parametrize("H,dh,d,batches", [(8, 64, 512, (36, 12, 1)), (10, 32, 320, (60, 23, 1)), (4, 128, 448, (43, 14, 1))])
+def test_second_outputs_of_heads_by_tile(H, dh, d, batches):
+    import paper_2510_23264_amd as P
+    B, S, V = 8, 16, 300
+    tiles = [T.tiles(1, B + n * (S - 1) * B if n > 1 else B * S, d, 64, 64) for n in batches]
+    assert tiles[0] >= 512 and 96 <= tiles[1] < 512 and tiles[2] < 96
+    shape = ModelShape(n_layers=3, n_heads=H, d_head=dh, d_model=d, d_mlp=128, vocab=V, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 17, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(17)
+    clean = rng.integers(0, V, (B, S)).astype(np.int32)
+    corrupt = clean.copy()
+    corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, V - 1, (B, 5))) % V      # position 0 is shared
+    om = OModel(shape, w)
+    g, oa = om.g, Acdc(om, clean, corrupt, MODE_ALL_FP32)
+    removed = g.empty_removed()
+    for q in range(g.headin(2, 0, 0), g.n_receivers):
+        removed[q, [g.head(1, h) for h in range(1, H)]] = rng.random(H - 1) < 0.4      # (head 0 keeps all its edges)
+    r = 3 * H                                        # the first layer's MLP input
+    n = g.n_upstream(r)
+    out = []
+    for batch in batches:
+        gm = P.Model(shape, w, B, S, precision=P.ALL_FP32, max_batch_edges=batch)
+        try:
+            gm.clean_cache(clean, corrupt)
+            gm.set_removed(g.removed_to_flat(removed).astype(np.uint8))
+            before = gm.counters()[1]
+            out.append(gm.eval_edges(r, np.resize(np.arange(n, dtype=np.int32), batches[0])[:batch]))
+            assert gm.counters()[1] == before + 1    # one device batch: the rows above
+        finally:
+            gm.close()
+    for got in out[1:]:
+        assert np.array_equal(got.view(np.uint32), out[0][:got.size].view(np.uint32))
+    assert np.array_equal(out[0][n:2 * n].view(np.uint32), out[0][:n].view(np.uint32))
+    for u in (0, n - 1):
+        want = oa.kl_edge(r, u, removed=removed)
+        assert abs(out[0][u] - want) <= F32_ATOL + F32_RTOL * abs(want), u
