@@ -1135,7 +1135,7 @@ int pahq_gemm_codes(pahq_model* M, const uint8_t* a, const uint8_t* w, int32_t m
   if (!gemm8_prob_ok(p)) return PAHQ_EINVAL;
   void* dp = nullptr;
   PCHK(upload_table(M, &p, sizeof(p), &dp));
-  HIPCHK(launch_gemm_fp8((const GemmProb*)dp, 1, m, n, k, M->cfg.mma == PAHQ_MMA_F16_EXACT, 0, gemm8_wide_ok(p), M->stream));
+  HIPCHK(launch_gemm_fp8((const GemmProb*)dp, 1, m, n, k, M->cfg.mma == PAHQ_MMA_F16_EXACT, 0, gemm8_wide_ok(p), false, M->stream));
   HIPCHK(hipMemcpy2DAsync(out, (size_t)n * sizeof(float), M->logits, ldc * sizeof(float), (size_t)n * sizeof(float), m,
                           hipMemcpyDeviceToHost, M->stream));
   HIPCHK(hipStreamSynchronize(M->stream));

@@ -1052,12 +1052,13 @@ int run_pass(pahq_model* M, const PassArgs& a, const RecvPlan* plan) {
             return PAHQ_EINVAL;
         if (o.p0) HIPCHK(launch_gemm_fp8_kl(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, b.probs[o.i0].b16, st));      // log-softmax / KL epilogue
         else {
-          bool wide = true;
+          bool wide = true, residual = false;
           for (int q = 0; q < o.i1; q++) {
             if (b.probs[o.i0 + q].kl_part || !b.probs[o.i0 + q].C) return PAHQ_EINVAL;
             wide = wide && gemm8_wide_ok(b.probs[o.i0 + q]);
+            residual = residual || b.probs[o.i0 + q].add;
           }
-          HIPCHK(launch_gemm_fp8(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, M->cfg.mma == PAHQ_MMA_F16_EXACT, b.probs[o.i0].b16, wide, st));
+          HIPCHK(launch_gemm_fp8(d_probs + o.i0, o.i1, o.i2, o.i3, b.probs[o.i0].K, M->cfg.mma == PAHQ_MMA_F16_EXACT, b.probs[o.i0].b16, wide, residual, st));
         }
         break;
       case OP_KLRED:

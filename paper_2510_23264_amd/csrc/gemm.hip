@@ -11,7 +11,7 @@
 //   straight into LDS (GLOBAL_LOAD_LDS_DWORDX4), two stages, one barrier per
 //   slab.  128 x 128 tile, four wavefronts of 64 x 64 (two decodes per MFMA; a
 //   smaller wave tile is bound by instruction issue, not by the matrix cores), or
-//   smaller ones where those would leave compute units idle (pick_tile).
+//   smaller ones where those would leave compute units idle (pick_exact_tile).
 //   gemm_s_k: the smallest tiles, one per workgroup; gemm_p_k: the large problems; gemm_w_k: the
 //   large plain ones (gemm8_wide_ok).
 //
@@ -31,7 +31,6 @@
 //   fp32 multiply-accumulate) for the heads in fp32 and the all-fp32 mode.
 #include <algorithm>
 #include <atomic>
-#include <cmath>
 #include "kernels.h"
 #include "device_util.h"
 #include "mma_util.h"
@@ -855,7 +854,6 @@ __global__ __launch_bounds__(512, 2) void gemm_w_k(const GemmProb* probs) {
       else step(1, false, true, true, at_a, at_b);
       request_end();
     }
-    if (nslab == 1) { wait_vm<0>(); wg_barrier(); }        // the scales were requested in this very slab
 
     // ---- epilogue.  Accumulator acc[i][4 b + q][r] of lane (li, lg) is tile row 64 wm + 16 i + 4 lg + r and column
     // 128 wn + 64 b + 4 li + q: a lane stores 16 bytes of a row, the 16 lanes of a group 256 contiguous ones.
@@ -1012,52 +1010,6 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_k(const GemmPr
   epi_store<TM, TN>(E, P, acc, mbase, nbase, li, lg);
 }
 
-// Which tile a launch of the exact-sum kernels takes.  With r = tiles per compute unit, rounded up, the time of a launch
-// is close to a + b r in units of a 128 x 128 tile of a full chip; a is what a tile's dependent steps take when nothing
-// else runs beside it.  (a, b) are fits to timings of M 128 .. 50000, N 64 .. 12288, K 128 .. 11008.  The choice is within
-// 5 % of the best of the six at most of these sizes.  Measured, us (128 x 128 or 256 x 128, which was the rule before,
-// against what is taken now): 1024 x 512 x 2048 23.8 -> 8.8, 1024 x 2048 x 512 12.4 -> 7.6, 3000 x 768 x 3072 35 -> 26,
-// 8192 x 512 x 2048 32 -> 25, 512 x 4096 x 11008 102 -> 61, 9000 x 2304 x 768 50 -> 45.  From five tiles of 256 x 128 per unit
-// on that kernel is the fastest whatever the remainder (50000 x 3072 x 768: 261 against 355 and more).
-// A smaller tile reads more per product, which the fit does not know: where the larger one's tiles fill the chip already
-// (r > 1) and rows of K are longer than 1024 bytes, it is taken only if it promises 6 %.  Of 38 such sizes that promise less
-// 26 took 4 % longer or more with it and 4 that much less (2178 x 3264 x 1408 in bfloat16 33 -> 44, 7143 x 2880 x 3840 177 ->
-// 192); with shorter rows it is the other way round (59 sizes: 4 and 33, 860 x 7104 x 128 0.95 of the larger tile's time).
-// 256 x 256 (plain problems with rows of whole cache lines): one workgroup per unit; because the clock rises where units run out of
-// tiles, a last round costs between its share and a whole one, and an epilogue counts for more the fewer slabs a tile has.  It is taken
-// where it promises 6 %.  Of 277 random plain sizes (60 to 5000 such tiles) in codes 129 take it: 0.75 to 1.07 of the others' time, mean
-// 0.89, four of them more than 1.03 (short rows with a residual); without the 6 % nine of 162 would.  In bfloat16 153 of 223, 0.51 to
-// 1.09, mean 0.77, three above 1.03.  One-slab rows (K = 128: 0.88 to 1.15) never do.
-enum ExactTile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_64x128, TILE_128x64, TILE_64x64, TILE_32x64 };
-static ExactTile pick_tile(int n_probs, int M, int N, int K, bool b16, bool kl, bool wide) {
-  auto per_cu = [&](int bm, int bn) {
-    const long long t = (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * n_probs;
-    return (double)((t + 255) / 256);
-  };
-  const bool narrow = N <= 64 && !kl;
-  ExactTile best = narrow ? TILE_128x64 : TILE_128x128;
-  double r = narrow ? per_cu(128, 64) : per_cu(128, 128);
-  double cost = narrow ? 0.37 + 0.48 * r : 0.5 + 0.85 * r;
-  bool large = false;
-  if (!narrow && !b16 && !kl && M >= 8192 && N >= 128) {
-    const double rp = per_cu(256, 128);
-    if (rp >= 5 || 0.1 + 1.8 * rp <= cost) { best = TILE_256x128; r = rp; cost = 0.1 + 1.8 * rp; large = rp >= 5; }
-  }
-  if (!large) {
-    if (r > 1 && K > 1024) cost *= 0.94;
-    auto consider = [&](ExactTile t, double c) { if (c < cost) { best = t; cost = c; } };
-    if (!narrow) consider(TILE_64x128, 0.37 + 0.48 * per_cu(64, 128));
-    if (!kl) {         // (the parts of a row of the KL epilogue are 64 columns of one wave)
-      consider(TILE_64x64, 0.3 + 0.26 * per_cu(64, 64));
-      consider(TILE_32x64, 0.27 + 0.17 * per_cu(32, 64));
-    }
-  }
-  if (wide && K >= 256) {
-    const double t = (double)((M + 255) / 256) * ((N + 255) / 256) * n_probs / 256;
-    if (0.6 + (b16 ? 1.2 + 40.0 / K : 1.25 + 120.0 / K) * (std::ceil(t) + t) <= 0.94 * cost) best = TILE_256x256;
-  }
-  return best;
-}
 // grid of the persistent kernel: at most `per` workgroups (limited by LDS) per compute unit
 template <int WAVES_M, int WAVES_N, int TM, int TN, bool B16>
 static hipError_t launch_x(const GemmProb* probs, int n_probs, int M, int N, int per, hipStream_t s) {
@@ -1089,7 +1041,7 @@ static hipError_t launch_tile(ExactTile t, const GemmProb* probs, int n_probs, i
 // (kl_parts_per_row) is derived from.
 hipError_t launch_gemm_fp8_kl(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int b16, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
-  const ExactTile t = pick_tile(n_probs, max_M, max_N, K, b16 != 0, true, false);
+  const ExactTile t = pick_exact_tile(n_probs, max_M, max_N, K, b16 != 0, true, false, false);
   return b16 ? launch_tile<true>(t, probs, n_probs, max_M, max_N, s) : launch_tile<false>(t, probs, n_probs, max_M, max_N, s);
 }
 
@@ -1114,11 +1066,11 @@ static hipError_t launch_w(const GemmProb* probs, int n_probs, int M, int N, hip
   return launch_one_per_cu((const void*)gemm_w_k<B16>, set, 2 * 512 * 128 + 2 * 768 * 4, ((M + 255) / 256) * ((N + 255) / 256), n_probs, probs, s);
 }
 
-hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, bool wide, hipStream_t s) {
+hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, bool wide, bool residual, hipStream_t s) {
   if (n_probs == 0 || max_M == 0 || max_N == 0) return hipSuccess;
   if (b16 && !exact) return hipErrorInvalidValue;        // bfloat16 operands: exact sums only
   if (exact) {
-    const ExactTile t = pick_tile(n_probs, max_M, max_N, K, b16 != 0, false, wide);
+    const ExactTile t = pick_exact_tile(n_probs, max_M, max_N, K, b16 != 0, false, wide, residual);
     if (t == TILE_256x256) return b16 ? launch_w<true>(probs, n_probs, max_M, max_N, s) : launch_w<false>(probs, n_probs, max_M, max_N, s);
     if (t == TILE_256x128) {
       // three 48 KB stages + 2 KB of scales

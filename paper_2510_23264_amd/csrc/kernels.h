@@ -77,11 +77,11 @@ inline bool gemm8_prob_ok(const GemmProb& p) {
                          (!p.kl_ref == !p.kl_ref_logz) && !p.add && !p.aux && p.act == 0));
 }
 // What gemm_w_k assumes beyond that: rows of one instance at equal distances, no second output, no activation, whole groups of four
-// columns, and at least one tile in both directions (its edge tiles overlap their neighbours, so the result may not be the
-// residual either).  Rows of the result are whole cache lines: with others its stores, a half of a line here and there, cost up to
+// columns, at least two slabs (a tile's scales come with its first one) and at least one tile in both directions (its edge tiles
+// overlap their neighbours, so the result may not be the residual either).  Rows of the result are whole cache lines: with others its stores, a half of a line here and there, cost up to
 // twice the time of gemm_x_k (42203 x 1140 x 64 in bfloat16).
 inline bool gemm8_wide_ok(const GemmProb& p) {
-  return p.M >= 256 && p.N >= 256 && p.N % 4 == 0 && p.rpi == p.M && p.rp0 == 0 && p.as_stride == 1 && p.act == 0 && p.C && !p.aux &&
+  return p.M >= 256 && p.N >= 256 && p.K >= 256 && p.N % 4 == 0 && p.rpi == p.M && p.rp0 == 0 && p.as_stride == 1 && p.act == 0 && p.C && !p.aux &&
          !p.kl_part && p.C != p.add && p.ldc % 32 == 0 && (((uintptr_t)p.C | (uintptr_t)p.add) & 127) == 0 &&
          p.lda < (1 << 24) && p.ldw < (1 << 24) && p.ldc < (1 << 24);
 }
@@ -187,8 +187,8 @@ hipError_t launch_tile_sub(float* out, const float* a, const float* b, long long
 // products, fp32 sums).
 // K: bytes of an operand row (for the choice of the tile).  b16: the problems' operands are bfloat16 patterns (exact products
 // on the bf16 matrix cores, fp32 sums)
-// wide: gemm8_wide_ok of every one of them
-hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, bool wide, hipStream_t s);
+// wide: gemm8_wide_ok of every one of them; residual: one of them adds one
+hipError_t launch_gemm_fp8(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int exact, int b16, bool wide, bool residual, hipStream_t s);
 hipError_t launch_gemm_f32(const GemmProb* probs, int n_probs, int max_M, int max_N, int K, int form, hipStream_t s);
 // C = (run_in + bias) + (add + sum over heads of A_h W_h), each head's own product to its aux (see gemm.hip); run_in may be null
 hipError_t launch_gemm_f32_heads(const GemmProb* probs, int n_heads, int M, int N, const float* run_in, long long run_is,
