@@ -48,8 +48,18 @@ def test_scores_by_batch_in_wide_tiles(H, dh, d, options, large):
     same_scores(H, dh, d, options, (large, 24, 1))
 
 
-def same_scores(H, dh, d, options, batches):
+# The middle layer's first head and last one feed nobody: the projection leaves them out (their codes are what an earlier pass
+# left) and adds the corrupted run's outputs in their place.
+@pytest.mark.parametrize("H,dh,d,options,large", [
+    (8, 64, 512, {}, 128), (3, 128, 704, {}, 160), (6, 32, 640, dict(low_bits=16), 176), (3, 64, 512, dict(low_bits=16), 128)])
+def test_dead_heads_in_wide_tiles(H, dh, d, options, large):
+    assert takes_128_columns(8 + large * 120, d) and not takes_128_columns(8 + 24 * 120, d)
+    same_scores(H, dh, d, options, (large, 24, 1), dead=(0, H - 1))
+
+
+def same_scores(H, dh, d, options, batches, dead=()):
     import paper_2510_23264_amd as P
+    from oracle.graph import Graph
     B, S = 8, 16
     shape = synth.ModelShape(n_layers=3, n_heads=H, d_head=dh, d_model=d, d_mlp=256, vocab=300, n_ctx=S, act=1)
     w = synth.make_weights(shape, 5, std=0.08, affine_std=0.1)
@@ -57,11 +67,17 @@ def same_scores(H, dh, d, options, batches):
     clean = rng.integers(0, 300, (B, S)).astype(np.int32)
     corrupt = clean.copy()
     corrupt[:, 1:6] = (clean[:, 1:6] + 1 + rng.integers(0, 299, (B, 5))) % 300
+    g = Graph(3, H, True)
+    removed = np.zeros((g.n_receivers, g.n_senders), bool)
+    for h in dead:
+        removed[list(g.receivers_downstream_of(g.head(1, h))), g.head(1, h)] = True
     out = []
     for batch in batches:
         gm = P.Model(shape, w, B, S, max_batch_edges=batch, **options)
         try:
             gm.clean_cache(clean, corrupt)
+            if dead:
+                gm.set_removed(g.removed_to_flat(removed).astype(np.uint8))
             r = 3 * H
             n = P.n_upstream(gm.cfg, r)
             senders = np.resize(np.arange(n, dtype=np.int32), batches[0])
