@@ -105,7 +105,7 @@ size_t layout(pahq_model* M, char* base) {
   Bump b{base, 0};
   const size_t L = M->L, H = M->H, dh = M->dh, d = M->d, m = M->m, V = M->V, T = M->T, B = M->B;
   const size_t Kdo = M->Kd_o, Kmo = M->Km_o;
-  const size_t Kd = M->Kd, Kh = M->Kh, Km = M->Km, n = M->nmax, G = M->G, Ns = M->g.Ns, tile = M->tile, Vp = M->Vp;
+  const size_t Kd = M->Kd, Km = M->Km, n = M->nmax, G = M->G, Ns = M->g.Ns, tile = M->tile, Vp = M->Vp;
   const bool mlp = m > 0, swi = M->cfg.act == PAHQ_ACT_SWIGLU, learned = M->cfg.pos == PAHQ_POS_LEARNED;
   M->W_E = b.take<float>(V * d);
   M->W_pos = learned ? b.take<float>((size_t)M->cfg.n_ctx * d) : nullptr;

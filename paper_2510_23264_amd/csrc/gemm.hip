@@ -699,6 +699,9 @@ __global__ __launch_bounds__(512, 1) void gemm_p_k(const GemmProb* probs) {
 // 498 -> 353, 102400 x 3072 x 768 582 -> 431, 102400 x 768 x 3072 521 -> 423, 24576 x 4096 x 1024 224 -> 169, 4096 x 12288 x 4096
 // 354 -> 292 (1.4 PFLOP/s).  What bounds it now: at K = 768 the stores (1.26 GB of them; a slab requested behind the stores of
 // a tile is not seen to have landed before they have), at long K the chip's power: the shader clock falls to 1.75 GHz.
+// The wave's 256 registers do not quite suffice: 18 (bfloat16: 13) spill, 72 and 56 bytes of scratch a lane, and a few come back
+// inside the K loop.  The counted waits bear that: operations the compiler adds make them stricter.  Recomputing such values
+// instead was slower.
 // Measured and not kept: two workgroups of 256 x 128 per unit with slabs of 64 bytes (530 us where this takes 431), one wave of
 // 64 x 128 per SIMD whose finished tile leaves during the next one (747), V_MFMA_F32_32X32X16_F16 (the same bits, 15 % slower: the
 // clock falls further).

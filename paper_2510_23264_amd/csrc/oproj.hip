@@ -1,9 +1,9 @@
 // Output projection of all heads of a layer fused with the stream update:
 //   next[m][:] = run[m][:] + b_O + extra[m][:] + sum_h (z_h[m] W_O^h) * s_z[m][h] * s_w[h]
 // Each head is a part of K (in oproj_fused_k a slab of 128 bytes padded with zeros, in
-// oproj_x_k and oproj_w_k its codes alone, the heads side by side) with its own row and weight scale, so the MFMA result of a head is scaled and added to
-// the running total in registers; the per-head sender outputs never go to HBM
-// unless a receiver needs one (HeadAux: the head's output, optionally minus the
+// oproj_x_k and oproj_w_k its codes alone, the heads side by side) with its own row and
+// weight scale, so the MFMA result of a head is scaled and added to the running total in
+// registers; the per-head sender outputs never go to HBM unless a receiver needs one (HeadAux: the head's output, optionally minus the
 // corrupted run's, is written next to the total).  `extra` carries the fp32
 // head's contribution, computed by the fp32 GEMM.
 // oproj_fused_k, for other head sizes: tile 128 x 64, four wavefronts of 32 x 64; operands staged
@@ -183,8 +183,8 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
 
 // ------------------------------------------------------------------ exact sums, d_head 64 or 128
 // The same projection with the slab pipeline of the exact GEMM: slabs of 128 code bytes (one head
-// of 128, or two heads of 64: only the real codes are fetched, the padding of the stored rows is
-// skipped) go straight into swizzled LDS.  128 x 64 tile, eight wavefronts of 32 x 32 (two workgroups
+// of 128, or two heads of 64, which lie side by side in the rows of both operands) go straight into
+// swizzled LDS.  128 x 64 tile, eight wavefronts of 32 x 32 (two workgroups
 // per compute unit, four waves per SIMD: a tile is a chain of short dependent steps - six slabs of 16
 // matrix instructions per wave, then the stream tile - and it is the number of waves in flight that
 // hides their latencies; four waves of 32 x 64 took a tenth longer).  A head's
@@ -408,13 +408,15 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
   }
 }
 
-// The same projection for many rows without per-head results: 128 x 128 tile, four wavefronts of 64 x 64, two stages of 32 KB, two
-// workgroups per compute unit, so that one multiplies while the other reads and writes its stream tile.  It moves 0.7 GB of stream for 0.08 of codes (100 000 rows
-// of 768, 12 heads) and is bound by that: 318 -> 239 us, 3.3 TB/s.  Against the kernel above an operand is read half as often from
-// L2, a wave's conversions serve twice the products, and a lane's four columns are neighbours, so that 16 lanes read and write 256
-// bytes of a row of the stream instead of four lanes 64.  24 600 rows of 1024, 16 heads: 133 -> 100 us; 4096 rows of 4096, 32 heads of 128:
-// 190 -> 155.  Loading part or all of the stream tile in front of the last products gains nothing (252 us; 269 with half of it).
-// Same sums in the same order.
+// The same projection for many rows without per-head results: 128 x 128 tile, four wavefronts of 64 x 64, two stages of 32 KB,
+// two workgroups per compute unit, so that one multiplies while the other reads and writes its stream tile.  It moves 0.7 GB of
+// stream for 0.08 of codes (100 000 rows of 768, 12 heads) and is bound by that: 318 -> 239 us, 3.3 TB/s.  Against the kernel
+// above an operand is read half as often from L2, a wave's conversions serve twice the products, and a lane's four columns are
+// neighbours, so that 16 lanes read and write 256 bytes of a row of the stream instead of four lanes 64.  24 600 rows of 1024, 16
+// heads: 133 -> 100 us; 4096 rows of 4096, 32 heads of 128: 190 -> 155.  Loading part or all of the stream tile in front of the
+// last products gains nothing (252 us; 269 with half of it).  Same sums in the same order.
+// A tile row's offset in its instance (row * N) is kept in 32 bits: a handle's tile (rows of an instance * N floats) would have to be
+// 8 GB for more, and its workspace beyond 290 GB with the fewest and smallest heads there can be.
 template <int DH, bool B16>
 __global__ __launch_bounds__(256, 2) void oproj_w_k(const OprojDesc* descs, int di) {
   constexpr int BM = 128, BN = 128, TM = 4, TN = 4, NI = 8, HPS = 128 / DH;
