@@ -493,7 +493,7 @@ struct Builder {
       OprojDesc od; memset(&od, 0, sizeof(od));
       od.zc = M->zcodes + last_off(last, (long long)H * M->Kz); od.zc_is = (long long)T * H * M->Kz;
       od.zs = M->zscale + last_off(last, H); od.zs_is = (long long)T * H;
-      od.W = M->o_codes + o_codes_at(M, l, 0); od.w_ld = o_codes_ld(M); od.w_hs = o_codes_at(M, 0, 1); od.ws = M->o_scale + (long long)l * H;
+      od.W = M->o_codes + o_codes_at(M, l, 0); od.ws = M->o_scale + (long long)l * H;
       od.run_in = run.p + lo; od.run_in_is = run.is; od.run_out = nxt.p + (long long)h * nxt.is + lo; od.run_out_is = nxt.is;
       od.bias = M->b_O + (long long)l * d;
       od.H = H; od.Kz = M->Kz; od.skip_mask = 1ull << h; od.rpi = od.M = last ? M->B : T; od.N = d;
@@ -654,7 +654,7 @@ struct Builder {
     OprojDesc od; memset(&od, 0, sizeof(od));
     od.zc = M->zcodes + last_off(last, (long long)H * M->Kz); od.zc_is = inst_stride((long long)H * M->Kz);
     od.zs = M->zscale + last_off(last, H); od.zs_is = inst_stride(H);
-    od.W = M->o_codes + o_codes_at(M, l, 0); od.w_ld = o_codes_ld(M); od.w_hs = o_codes_at(M, 0, 1); od.ws = M->o_scale + (long long)l * H;
+    od.W = M->o_codes + o_codes_at(M, l, 0); od.ws = M->o_scale + (long long)l * H;
     od.run_in = run.p + lo; od.run_in_is = run.is; od.run_out = nxt.p + lo; od.run_out_is = nxt.is;
     od.bias = M->b_O + (long long)l * d;
     od.H = H; od.Kz = M->Kz; od.skip_mask = off8; od.rpi = last ? M->B : rpi; od.rp0 = last ? 0 : rp0; od.M = rows(last); od.N = d;

@@ -121,13 +121,12 @@ struct HeadAux { float* dst; long long dst_is; const float* sub; };   // per hea
 struct OprojDesc {
   const uint8_t* zc;  long long zc_is;      // attention outputs, codes [inst][rpi][H][Kz]
   const float* zs;    long long zs_is;      // their scales [inst][rpi][H]
-  const uint8_t* W;   const float* ws;      // W_O codes (row n of head h at h w_hs + n w_ld), scales [H]
-  long long w_hs; int w_ld, Kz;             // Kz: bytes from one head of a row to the next
+  const uint8_t* W;   const float* ws;      // W_O codes (oproj_side_by_side: [N][H][Kz], else [H][N][Kz]), scales [H]
   const float* extra; long long extra_is;   // fp32 head's output [inst][rpi][N] or null
   const float* run_in; long long run_in_is;
   float* run_out;      long long run_out_is;
   const float* bias;                        // [N] or null
-  int H, rpi, rp0;                          // rows of an instance, rows of instance 0 in front of them (as in GemmProb)
+  int H, Kz, rpi, rp0;                      // Kz: bytes of a head in a row of zc and W; rows of an instance, of instance 0 in front (as in GemmProb)
   int M, N, aux_begin, dh;                  // M = rows over all instances; aux_begin: first of H HeadAux, or -1; dh = d_head
   unsigned long long skip_mask;             // bit h set: head h is computed in fp32 elsewhere (it arrives in `extra`)
 };

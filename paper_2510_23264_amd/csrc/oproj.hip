@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
 #pragma unroll
   for (int c = 0; c < 2; c++) {
     int n = n0 + (tid >> 3) + 32 * c;
-    pb[c] = (n < D.N) ? D.W + (long long)n * D.w_ld + kc * 16 : nullptr;
+    pb[c] = (n < D.N) ? D.W + (long long)n * D.Kz + kc * 16 : nullptr;
   }
   uint4 ra[4], rb[2];
   // codes beyond d_head are zero padding: neither loaded nor (with the fp16 matrix cores) multiplied
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void oproj_fused_k(const OprojDesc* descs, int
       ra[c] = (pa[c] && real_chunk) ? *(const uint4*)(pa[c] + (long long)h * D.Kz) : make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int c = 0; c < 2; c++)
-      rb[c] = (pb[c] && real_chunk) ? *(const uint4*)(pb[c] + h * D.w_hs) : make_uint4(0, 0, 0, 0);
+      rb[c] = (pb[c] && real_chunk) ? *(const uint4*)(pb[c] + (long long)h * D.N * D.Kz) : make_uint4(0, 0, 0, 0);
   };
   auto skipped = [&](int h) { return ((D.skip_mask >> h) & 1ull) != 0; };
   auto next_head = [&](int h) { h++; while (h < D.H && skipped(h)) h++; return h; };
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(BM == 128 ? 512 : 256, 4) void oproj_x_k(const Opro
       src[t] = D.zc + (long long)inst * D.zc_is + (long long)row * D.H * DH + c * 16;
     } else {
       int n = min(n0 + r - BM, D.N - 1);
-      src[t] = D.W + (long long)n * D.w_ld + c * 16;
+      src[t] = D.W + (long long)n * D.H * DH + c * 16;
     }
   }
   // row scales of a slab: entry [q][r] (head q of the slab, tile row r) is lane's if 64 wave + lane = BM q + r;
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256, 2) void oproj_w_k(const OprojDesc* descs, int 
       int inst, row; split_row(i0, r0, min(m0 + r, D.M - 1) - m0, D.rpi, D.rp0, inst, row);
       src[t] = D.zc + (long long)inst * D.zc_is + (long long)row * D.H * DH + c;
     } else {
-      src[t] = D.W + (long long)min(n0 + (r & 64) + (r & 15) * 4 + ((r >> 4) & 3), D.N - 1) * D.w_ld + c;
+      src[t] = D.W + (long long)min(n0 + (r & 64) + (r & 15) * 4 + ((r >> 4) & 3), D.N - 1) * D.H * DH + c;
     }
   }
   // row scales of a slab's heads: entry 64 wave + lane = BM q + r is head q's of tile row r (with one head per slab the upper two
