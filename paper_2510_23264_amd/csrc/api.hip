@@ -76,7 +76,8 @@ void set_dims(pahq_model* M, const pahq_config* c, int B, int S) {
   M->side_by_side = oproj_side_by_side(M->H, hb, M->d, c->mma == PAHQ_MMA_F16_EXACT);
   M->Kz = M->side_by_side ? hb : M->Kh;
   M->Kd_o = M->nb16 ? pad128(2 * M->d) : M->Kd;
-  M->Km_o = M->nb16 ? pad128(2 * (M->m > 0 ? M->m : 1)) : M->Km;
+  // (at 16 bits in the all-fp32 mode too, which multiplies none of them: the weights are written as patterns there as well)
+  M->Km_o = (M->nb16 || M->qbits == 16) ? pad128(2 * (M->m > 0 ? M->m : 1)) : M->Km;
   M->deadsum_tag.assign(M->L, -1);
   M->f32_groups = M->all_f32 ? 3 * M->H : 3;
   M->f32_heads_max = M->all_f32 ? M->H : 1;

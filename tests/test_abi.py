@@ -90,3 +90,17 @@ def test_argument_validation_without_a_device():
     assert p.lib().pahq_clean_cache(None, None, None) == -1
     assert p.lib().pahq_eval_edges(None, 0, None, 0, None) == -1
     assert p.lib().pahq_acdc_sweep(None, C.c_float(0.1), None, 0, None, None, None, 0) == -1
+
+
+@pytest.mark.parametrize("precision", ["PAHQ", "ALL_FP32"])
+def test_workspace_has_room_for_sixteen_bit_weights(precision):
+    """128 more hidden units are 128 more rows of W_in and columns of W_out in every layer: one byte more per element of each,
+    and per hidden activation, at 16 bits than at 8."""
+    import paper_2510_23264_amd as p
+    L, d, B, S, n = 3, 256, 4, 64, 8
+
+    def bytes_at(m, bits):
+        shape = synth.ModelShape(n_layers=L, n_heads=4, d_head=64, d_model=d, d_mlp=m, vocab=512, n_ctx=S, act=1)
+        return p.workspace_bytes(p.Config.from_shape(shape, getattr(p, precision), n, low_bits=bits), B, S)
+    extra = [bytes_at(m, 16) - bytes_at(m, 8) for m in (1024, 1152)]
+    assert extra[1] - extra[0] >= 128 * (2 * L * d + n * B * S)
