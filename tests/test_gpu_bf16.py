@@ -246,3 +246,25 @@ def test_rows_of_an_odd_number_of_half_slabs(d_model, n_heads):
         check_kl_cases(np.concatenate(got), want, sigma, what="d_model %d, bf16 non-attention" % d_model)
     finally:
         pr.close(); one.close(); many.close()
+
+
+@pytest.mark.parametrize("dh", [16, 128])
+def test_sixteen_bits_beside_all_fp32_take_every_head_size(dh):
+    """Sixteen bits are refused for these heads only where heads are quantised; with every head in fp32 the scores are those
+    of the eight-bit setting (the attention kernel's bfloat16 form runs, and stores no pattern)."""
+    import paper_2510_23264_amd as P
+    B, S, H = 4, 12, 3
+    shape = synth.ModelShape(n_layers=2, n_heads=H, d_head=dh, d_model=192, d_mlp=64, vocab=300, n_ctx=S, act=1)
+    w = synth.make_weights(shape, 3, std=0.08, affine_std=0.1)
+    rng = np.random.default_rng(3)
+    clean = rng.integers(0, 300, (B, S)).astype(np.int32)
+    corrupt = (clean + 1 + rng.integers(0, 299, (B, S))).astype(np.int32) % 300
+    out = []
+    for bits in (8, 16):
+        gm = P.Model(shape, w, B, S, precision=P.ALL_FP32, low_bits=bits, max_batch_edges=8)
+        try:
+            gm.clean_cache(clean, corrupt)
+            out.append(gm.eval_edges(3 * H, np.arange(P.n_upstream(gm.cfg, 3 * H), dtype=np.int32)))
+        finally:
+            gm.close()
+    assert (out[0] > 0).any() and np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
