@@ -78,8 +78,8 @@ inline bool gemm8_prob_ok(const GemmProb& p) {
 }
 // What gemm_w_k assumes beyond that: rows of one instance at equal distances, no second output, no activation, whole groups of four
 // columns, at least two slabs (a tile's scales come with its first one) and at least one tile in both directions (its edge tiles
-// overlap their neighbours, so the result may not be the residual either).  Rows of the result are whole cache lines: with others its stores, a half of a line here and there, cost up to
-// twice the time of gemm_x_k (42203 x 1140 x 64 in bfloat16).
+// overlap their neighbours, so the result may not be the residual either).  Rows of the result are whole cache lines: with others
+// its stores, a half of a line here and there, cost up to twice the time of gemm_x_k (42203 x 1140 x 64 in bfloat16).
 inline bool gemm8_wide_ok(const GemmProb& p) {
   return p.M >= 256 && p.N >= 256 && p.K >= 256 && p.N % 4 == 0 && p.rpi == p.M && p.rp0 == 0 && p.as_stride == 1 && p.act == 0 && p.C && !p.aux &&
          !p.kl_part && p.C != p.add && p.ldc % 32 == 0 && (((uintptr_t)p.C | (uintptr_t)p.add) & 127) == 0 &&

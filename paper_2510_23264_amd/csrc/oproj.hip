@@ -3,9 +3,9 @@
 // Each head is a part of K (in oproj_fused_k a slab of 128 bytes padded with zeros, in
 // oproj_x_k and oproj_w_k its codes alone, the heads side by side) with its own row and
 // weight scale, so the MFMA result of a head is scaled and added to the running total in
-// registers; the per-head sender outputs never go to HBM unless a receiver needs one (HeadAux: the head's output, optionally minus the
-// corrupted run's, is written next to the total).  `extra` carries the fp32
-// head's contribution, computed by the fp32 GEMM.
+// registers; the per-head sender outputs never go to HBM unless a receiver needs one
+// (HeadAux: the head's output, optionally minus the corrupted run's, is written next to the
+// total).  `extra` carries the fp32 head's contribution, computed by the fp32 GEMM.
 // oproj_fused_k, for other head sizes: tile 128 x 64, four wavefronts of 32 x 64; operands staged
 // through LDS as in the fp8 GEMM (144-byte rows), next head prefetched into registers.
 #include "kernels.h"
